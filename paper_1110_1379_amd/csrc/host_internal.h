@@ -145,6 +145,7 @@ struct mgfr_ctx {
     // TSC assignment scratch (keys, indices, sorted positions, cell table, sort storage)
     void* tsc = nullptr;
     size_t tsc_bytes = 0;
+    hipEvent_t tsc_ev = nullptr;  // recorded after the last call that used tsc
     // device blocks of finished batched solves, reused by later ones (smallest that fits)
     std::vector<std::pair<void*, size_t>> spare;
 

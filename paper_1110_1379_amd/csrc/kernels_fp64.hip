@@ -464,6 +464,12 @@ hipError_t fold_partials(const double* partial, int nb, double* out, hipStream_t
     return hipGetLastError();
 }
 
+hipError_t fold_sums(const double* partial, int nb, double* out, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_fold, dim3(1), dim3(kBlock), 0, s, partial, nb, 1, out);
+    return hipGetLastError();
+}
+
 hipError_t fill(double* x, double v, long long n, hipStream_t s)
 {
     hipLaunchKernelGGL(k_fill, dim3(reduction_blocks(n)), dim3(kBlock), 0, s, x, v, n);

@@ -313,6 +313,8 @@ hipError_t residual_cast(const Grid& g, const double* u, const double* src, floa
                          double* partial, double* out, hipStream_t s);
 // out[0..1] from `nb` partial pairs (sum, max).
 hipError_t fold_partials(const double* partial, int nb, double* out, hipStream_t s);
+// out[0..1] = the sums of `nb` partial pairs.
+hipError_t fold_sums(const double* partial, int nb, double* out, hipStream_t s);
 
 // tau = fH - R f_src on the level below the fine grid g (fH = L^H(R u) - R d there), written
 // to tau if not null; block partials (sum tau^2, max |tau|).  Returns their number, or -1 if

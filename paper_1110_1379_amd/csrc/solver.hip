@@ -383,6 +383,7 @@ void mgfr_destroy(mgfr_ctx* c)
     c->free_poisson();
     c->free_masked();
     (void)hipFree(c->tsc);
+    if (c->tsc_ev) (void)hipEventDestroy(c->tsc_ev);
     delete c;
 }
 

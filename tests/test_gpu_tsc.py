@@ -86,6 +86,55 @@ def test_density_rows_of_several_segments(mg, ctx, N):
     assert err <= 1e-12 * ref.max()
 
 
+@pytest.mark.parametrize("N,layout", [(64, "uniform"), (128, "uniform"), (64, "two tiles"), (256, "corners")])
+def test_force_of_scattered_particles(mg, ctx, N, layout):
+    """Particles in no order go through tiles of the potential staged in LDS (N >= 64, at least
+    375 thousand jumps and 32 particles per tile): every tile of a grid, more particles in a
+    tile than a workgroup takes, empty tiles between, particles on the tile and box edges, and
+    a ragged count; the sums are those of the direct path, so the bar is the same 1e-13."""
+    say(f"[tsc] scattered {layout} on {N}^3")
+    rng = np.random.default_rng(N)
+    n = 420_001
+    pos = rng.random((n, 3))
+    if layout == "two tiles":
+        pos = pos * (16.0 / N)
+        pos[1::2] += 1.0 - 16.0 / N
+    elif layout == "corners":  # cell and tile edges, and their neighbours one ulp away
+        pos = np.round(pos * (N // 16)) / (N // 16)
+        pos[1::3] = np.nextafter(pos[1::3], 2.0)
+        pos[2::3] = np.nextafter(pos[2::3], -1.0)
+    phi = rng.standard_normal((N, N, N))
+    F = tsc.force(phi, pos)
+    G = mg.mgfr_tsc_force(ctx, dev(phi), dev(pos)).cpu().numpy()
+    ferr = np.abs(G - F).max()
+    say(f"  force max err {ferr:.2e}, bit-identical {np.array_equal(G, F)}")
+    assert ferr <= 1e-13 * N * np.abs(phi).max()
+
+
+def test_density_and_force_on_two_streams(mg, ctx):
+    """A density on one stream and the force of scattered particles on another share the
+    context's scratch: the second waits for the first."""
+    say("[tsc] two streams")
+    import torch
+    N, n = 128, 600_001
+    g = torch.Generator(device="cuda:0").manual_seed(4)
+    pos = torch.rand((n, 3), generator=g, device="cuda:0", dtype=torch.float64)
+    phi = torch.randn((N, N, N), generator=g, device="cuda:0", dtype=torch.float64)
+    rho0 = mg.mgfr_tsc_density(ctx, pos, N, 1.0)
+    acc0 = mg.mgfr_tsc_force(ctx, phi, pos)
+    torch.cuda.synchronize()
+    a, b = torch.cuda.Stream(), torch.cuda.Stream()
+    rho, acc = torch.empty_like(rho0), torch.empty_like(acc0)
+    for _ in range(3):
+        rho.zero_()
+        acc.zero_()
+        torch.cuda.synchronize()
+        mg.mgfr_tsc_density(ctx, pos, N, 1.0, rho=rho, stream=a)
+        mg.mgfr_tsc_force(ctx, phi, pos, acc=acc, stream=b)
+        torch.cuda.synchronize()
+        assert torch.equal(rho, rho0) and torch.equal(acc, acc0)
+
+
 def test_gpu_pair_conserves_momentum(mg, ctx):
     """GPU density -> GPU Poisson solve (background scalaron) -> GPU forces: the total force
     vanishes (the TSC pair is momentum conserving; the Poisson operator is symmetric)."""
