@@ -58,7 +58,7 @@ struct P64 {
         return gload(base + off);
     }
     __device__ __forceinline__ static Raw cell(const BGrid& g, unsigned off) { return gload(g.u + off); }
-    __device__ __forceinline__ static Lds make(Raw v, bool) { return make_double2(v, exp(v)); }
+    __device__ __forceinline__ static Lds make(Raw v, bool) { return make_double2(v, dev::exp_(v)); }
     __device__ __forceinline__ static Rhs rhs(const BGrid& g, unsigned q) { return gload(g.src + q); }
 
     // bcell's L - f and dL with the neighbours (i-1, i+1, j-1, j+1, k-1, k+1) and the cell
@@ -73,7 +73,7 @@ struct P64 {
         for (int x = 0; x < 6; ++x) {
             if (__builtin_expect(out[x], 0)) {
                 const double ug = (1.0 - kR) * nb[x].x + kR * ui;
-                const double bg = exp(ug);
+                const double bg = dev::exp_(ug);
                 lg_ += (bg + bi) * (ug - ui);
                 dlg += (kR * bg + bi) * (ug - ui) + (bg + bi) * (kR - 1.0);
             } else {
@@ -84,7 +84,7 @@ struct P64 {
                 ++nreg;
             }
         }
-        const double S = g.A * exp(-ui * g.inv_np1);
+        const double S = g.A * dev::exp_(-ui * g.inv_np1);
         L = g.C * (fma(bi, su, sbu) + lg_) + S - fma(g.fscale, src - g.sref, g.fshift);
         dL = g.C * (fma(bi, su, -sb) - nreg * bi + dlg) - S * g.inv_np1;
     }

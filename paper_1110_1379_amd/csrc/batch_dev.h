@@ -68,7 +68,7 @@ __device__ inline OpVal bcell(const BGrid& g, const double* __restrict__ u, int 
 {
     const int n = g.n, m = n - 1;
     const double ui = u[idx3(g.lg, i, j, k)];
-    const double bi = exp(ui);
+    const double bi = dev::exp_(ui);
     double su = 0.0, sb = 0.0, sbu = 0.0, lg_ = 0.0, dlg = 0.0;
     int nreg = 0;
     const int di[6] = {-1, 1, 0, 0, 0, 0}, dj[6] = {0, 0, -1, 1, 0, 0}, dk[6] = {0, 0, 0, 0, -1, 1};
@@ -78,19 +78,19 @@ __device__ inline OpVal bcell(const BGrid& g, const double* __restrict__ u, int 
         const bool out = ii < 0 || ii > m || jj < 0 || jj > m || kk < 0 || kk > m;
         if (out && !g.periodic) {
             const double ug = (1.0 - kR) * face_ub(g, q, i, j, k) + kR * ui;
-            const double bg = exp(ug);
+            const double bg = dev::exp_(ug);
             lg_ += (bg + bi) * (ug - ui);
             dlg += (kR * bg + bi) * (ug - ui) + (bg + bi) * (kR - 1.0);
         } else {
             const double un = u[idx3(g.lg, ii & m, jj & m, kk & m)];
-            const double bn = exp(un), du = un - ui;
+            const double bn = dev::exp_(un), du = un - ui;
             su += du;
             sb += bn;
             sbu = fma(bn, du, sbu);
             ++nreg;
         }
     }
-    const double S = g.A * exp(-ui * g.inv_np1);
+    const double S = g.A * dev::exp_(-ui * g.inv_np1);
     OpVal r;
     r.L = g.C * (fma(bi, su, sbu) + lg_) + S - f;
     r.dL = g.C * (fma(bi, su, -sb) - nreg * bi + dlg) - S * g.inv_np1;
@@ -191,7 +191,7 @@ __device__ void coarsest64_core(const BGrid& g, int cap, double rtol, const C64&
             const bool out = ii < 0 || ii > m || jj < 0 || jj > m || kk < 0 || kk > m;
             if (out && !g.periodic) {
                 const double ug = (1.0 - kR) * face(f, i, j, k) + kR * ui;
-                const double bg = exp(ug);
+                const double bg = dev::exp_(ug);
                 lg_ += (bg + bi) * (ug - ui);
                 dlg += (kR * bg + bi) * (ug - ui) + (bg + bi) * (kR - 1.0);
             } else {
@@ -266,8 +266,8 @@ __device__ void coarsest64_core(const BGrid& g, int cap, double rtol, const C64&
                     const OpVal r = cell(q);
                     const double u = sm.su[q] + dev::bounded(-r.L / r.dL, g.max_step);
                     sm.su[q] = u;
-                    sm.sb[q] = exp(u);
-                    sm.sS[q] = g.A * exp(-u * g.inv_np1);
+                    sm.sb[q] = dev::exp_(u);
+                    sm.sS[q] = g.A * dev::exp_(-u * g.inv_np1);
                 }
                 if constexpr (WAVE) wave_sync();
                 else __syncthreads();
@@ -291,8 +291,8 @@ __device__ void coarsest64(const BGrid& g, int cap, double rtol, Coarse64<NT>& s
     const int nc = 1 << (3 * g.lg);
     for (int q = threadIdx.x; q < nc; q += NT) {
         sm.su[q] = g.u[q];
-        sm.sb[q] = exp(sm.su[q]);
-        sm.sS[q] = g.A * exp(-sm.su[q] * g.inv_np1);
+        sm.sb[q] = dev::exp_(sm.su[q]);
+        sm.sS[q] = g.A * dev::exp_(-sm.su[q] * g.inv_np1);
         sm.sf[q] = brhs(g, q);
     }
     __syncthreads();

@@ -201,11 +201,11 @@ __global__ void __launch_bounds__(kBlock) k_coarsest(Grid g, double* __restrict_
             const double ui = su[q];
             const OpVal r = cell_op(g, ui, un, sf[q]);
             s += r.L * r.L;
-            const double bi = exp(ui);
+            const double bi = dev::exp_(ui);
             double t = 0.0;
 #pragma unroll
-            for (int v = 0; v < 6; ++v) t += g.C * (exp(un[v]) + bi) * fabs(un[v] - ui);
-            t += g.A * exp(-ui * g.inv_np1) + fabs(sf[q]);
+            for (int v = 0; v < 6; ++v) t += g.C * (dev::exp_(un[v]) + bi) * fabs(un[v] - ui);
+            t += g.A * dev::exp_(-ui * g.inv_np1) + fabs(sf[q]);
             const double f1 = 2.220446049250313e-16 * (fabs(r.dL) * fabs(ui) + t);
             fl += f1 * f1;
         }

@@ -42,7 +42,7 @@ __device__ __forceinline__ void masked_face(double mi, double mn, double wn, dou
     const double r = mn / mi;
     const double ubv = (mi * wn - mn * wi) / (mi - mn);
     const double ug = (1.0 - r) * ubv + r * ui;
-    const double bg = exp(ug), du = ug - ui;
+    const double bg = dev::exp_(ug), du = ug - ui;
     L = fma(bg + bi, du, L);
     // chain rule: du_g/du_i = r, db_g/du_i = r b_g
     dL += (r * bg + bi) * du + (bg + bi) * (r - 1.0);
@@ -57,14 +57,14 @@ __device__ __forceinline__ OpVal masked_op(const Grid& g, const M* __restrict__ 
     const int m = g.n - 1;
     const long long qn[6] = {at(g, (i - 1) & m, j, k), at(g, (i + 1) & m, j, k), at(g, i, (j - 1) & m, k),
                              at(g, i, (j + 1) & m, k), at(g, i, j, (k - 1) & m), at(g, i, j, (k + 1) & m)};
-    const double bi = exp(ui);
+    const double bi = dev::exp_(ui);
     double L = 0.0, dL = 0.0, wi = 0.0;
     bool have_wi = false;
 #pragma unroll
     for (int v = 0; v < 6; ++v) {
         const double mn = mval(mask, qn[v]);
         if (mn > 0.0) {
-            const double un = u[qn[v]], bn = exp(un), du = un - ui;
+            const double un = u[qn[v]], bn = dev::exp_(un), du = un - ui;
             L = fma(bn + bi, du, L);
             dL += bi * du - bn - bi;
         } else {
@@ -90,7 +90,7 @@ __device__ double masked_mag(const Grid& g, const float* mask, const double* w, 
     const int m = g.n - 1;
     const long long qn[6] = {at(g, (i - 1) & m, j, k), at(g, (i + 1) & m, j, k), at(g, i, (j - 1) & m, k),
                              at(g, i, (j + 1) & m, k), at(g, i, j, (k - 1) & m), at(g, i, j, (k + 1) & m)};
-    const double bi = exp(ui), wi = w[at(g, i, j, k)];
+    const double bi = dev::exp_(ui), wi = w[at(g, i, j, k)];
     double t = 0.0;
     for (int v = 0; v < 6; ++v) {
         const double mn = mask[qn[v]];
@@ -101,9 +101,9 @@ __device__ double masked_mag(const Grid& g, const float* mask, const double* w, 
             const double r = mn / mi;
             un = (1.0 - r) * ((mi * w[qn[v]] - mn * wi) / (mi - mn)) + r * ui;
         }
-        t += g.C * (exp(un) + bi) * fabs(un - ui);
+        t += g.C * (dev::exp_(un) + bi) * fabs(un - ui);
     }
-    return t + g.A * exp(-ui * g.inv_np1) + fabs(f);
+    return t + g.A * dev::exp_(-ui * g.inv_np1) + fabs(f);
 }
 
 __device__ __forceinline__ void cell_of(const Grid& g, long long q, int& i, int& j, int& k)
@@ -255,7 +255,7 @@ __global__ void __launch_bounds__(NT) km_ngs_fused(Grid g, const u8* __restrict_
     }
     auto offset = [&](int p, const ColM& q) -> unsigned { return ((unsigned)(p & m) << (2 * lg)) + q.col; };
     auto buf = [&](int p) { return (p - i0 + 3) % 3; };
-    auto bval = [](double u, int active) { return active ? exp(u) : -1.0; };
+    auto bval = [](double u, int active) { return active ? dev::exp_(u) : -1.0; };
     auto prologue = [&](ColM& q) {
         if (!q.fl) return;
         for (int t = 1; t < 4; ++t) {
@@ -303,7 +303,7 @@ __global__ void __launch_bounds__(NT) km_ngs_fused(Grid g, const u8* __restrict_
             const double bn[6] = {A.b[M1], A.b[P1], BA[c - LK], BA[c + LK], BA[c - 1], BA[c + 1]};
             const OpVal r = masked_op_staged(g, A.u[P0], A.b[P0], un, bn, A.f[P0], A.w[P0]);
             const double v = A.u[P0] + bounded(-r.L / r.dL, ms);
-            const double bv = exp(v);
+            const double bv = dev::exp_(v);
             A.u[P0] = v;
             A.b[P0] = bv;
             LA[c] = v;
@@ -486,7 +486,7 @@ __global__ void __launch_bounds__(NT) km_norm_fused(Grid g, const u8* __restrict
     const bool in = on && jj >= 1 && jj <= TJ && kk >= 1 && kk <= kMK;
     const unsigned col = (unsigned)((((j0 - 1 + jj) & m) << lg) | ((k0 - 1 + kk) & m));
     auto off = [&](int p) -> unsigned { return ((unsigned)(p & m) << (2 * lg)) + col; };
-    auto bval = [](double v, int a) { return a ? exp(v) : -1.0; };
+    auto bval = [](double v, int a) { return a ? dev::exp_(v) : -1.0; };
     double um = 0.0, uc = 0.0, up = 0.0, bm = 0.0, bc = 0.0, bp = 0.0, fc = 0.0, wc = 0.0;
     double ru = 0.0, rf = 0.0, rw = 0.0;
     int rm = 0;

@@ -7,7 +7,7 @@
 // Linear multigrid (Sec. V.A.3, correction scheme): red-black Gauss-Seidel, x_i =
 // (sum_nb x_nb - h^2 b_i) / 6, the residual restricted by 8-child means, the coarse
 // correction prolongated 27/9/3/1 (prolong.hip).  Every level is periodic.
-#include "mgfr_impl.h"
+#include "device_fp64.h"
 
 namespace mgfr {
 namespace {
@@ -28,7 +28,7 @@ __global__ void __launch_bounds__(kB) kp_source(PoissonSource c, long long n3, c
     __shared__ double rs[kB], rm[kB];
     double s = 0.0, mx = 0.0;
     for (long long q = (long long)blockIdx.x * kB + threadIdx.x; q < n3; q += (long long)gridDim.x * kB) {
-        const double v = 2.0 * c.D * (rho[q] - 1.0) - 0.5 * (c.A * exp(-u[q] * c.inv_np1) - c.Sbar);
+        const double v = 2.0 * c.D * (rho[q] - 1.0) - 0.5 * (c.A * dev::exp_(-u[q] * c.inv_np1) - c.Sbar);
         S[q] = v;
         s += v;
         const double av = fabs(v);

@@ -86,9 +86,9 @@ __global__ void __launch_bounds__(NT) k_resid_stream(Grid g, const double* __res
             up1[s] = load_u(i0 + 1, s);
             un2[s] = uin[offset(i0 + 2, s)];
             en2[s] = load_e(i0 + 2, s);
-            bm1[s] = exp(um1[s]);
-            b0[s] = exp(u0[s]);
-            bp1[s] = exp(up1[s]);
+            bm1[s] = dev::exp_(um1[s]);
+            b0[s] = dev::exp_(u0[s]);
+            bp1[s] = dev::exp_(up1[s]);
             lu[0][threadIdx.x + s * NT] = u0[s];
             lb[0][threadIdx.x + s * NT] = b0[s];
         }
@@ -172,7 +172,7 @@ __global__ void __launch_bounds__(NT) k_resid_stream(Grid g, const double* __res
             b0[s] = bp1[s];
             if (more2 && fl[s]) {
                 up1[s] = UPDATE ? un2[s] + (double)en2[s] : un2[s];
-                bp1[s] = exp(up1[s]);
+                bp1[s] = dev::exp_(up1[s]);
             }
             un2[s] = un3[s];
             en2[s] = en3[s];

@@ -95,7 +95,7 @@ __global__ void __launch_bounds__(NT) k_ngs_fused(Grid g, const double* __restri
         }
         q.ru[1] = uin[offset(i0 + 1, q)];
         q.rf[1] = src[offset(i0 + 1, q)];  // raw: transformed when it becomes plane p+1
-        for (int t = 1; t < 4; ++t) q.b[t] = exp(q.u[t]);
+        for (int t = 1; t < 4; ++t) q.b[t] = dev::exp_(q.u[t]);
         lu[buf(i0 - 1)][q.c] = q.u[2];
         lb[buf(i0 - 1)][q.c] = q.b[2];
     };
@@ -131,7 +131,7 @@ __global__ void __launch_bounds__(NT) k_ngs_fused(Grid g, const double* __restri
             const double bn[6] = {A.b[M1], A.b[P1], BA[c - LK], BA[c + LK], BA[c - 1], BA[c + 1]};
             const OpVal r = dev::cell_op_b(g, A.u[P0], A.b[P0], un, bn, A.f[P0]);
             const double v = A.u[P0] + dev::bounded(-r.L / r.dL, ms);
-            const double bv = exp(v);
+            const double bv = dev::exp_(v);
             A.u[P0] = v;
             A.b[P0] = bv;
             LA[c] = v;
@@ -162,7 +162,7 @@ __global__ void __launch_bounds__(NT) k_ngs_fused(Grid g, const double* __restri
                 BC[q.c] = q.b[P1];
                 if (more2) {
                     q.u[M2] = q.ru[N2];
-                    q.b[M2] = exp(q.ru[N2]);
+                    q.b[M2] = dev::exp_(q.ru[N2]);
                     q.f[M2] = dev::rhs_value(g, q.rf[N2]);
                 }
             }

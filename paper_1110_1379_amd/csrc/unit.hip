@@ -548,7 +548,7 @@ __device__ __forceinline__ OpVal rcell64(const BGrid& g, const double* u, const 
         const bool out = ii < 0 || ii > m || jj < 0 || jj > m || kk < 0 || kk > m;
         if (out && !g.periodic) {
             const double ug = (1.0 - kR) * fc[face_index(g.lg, x, i, j, k)] + kR * ui;
-            const double bg = exp(ug);
+            const double bg = dev::exp_(ug);
             lg_ += (bg + bi) * (ug - ui);
             dlg += (kR * bg + bi) * (ug - ui) + (bg + bi) * (kR - 1.0);
         } else {
@@ -560,7 +560,7 @@ __device__ __forceinline__ OpVal rcell64(const BGrid& g, const double* u, const 
             ++nreg;
         }
     }
-    const double S = g.A * exp(-ui * g.inv_np1);
+    const double S = g.A * dev::exp_(-ui * g.inv_np1);
     OpVal r;
     r.L = g.C * (fma(bi, su, sbu) + lg_) + S - f;
     r.dL = g.C * (fma(bi, su, -sb) - nreg * bi + dlg) - S * g.inv_np1;
@@ -577,7 +577,7 @@ __device__ void rsweep64(const BGrid& g, double* u, double* b, const double* f, 
         const OpVal r = rcell64(g, u, b, fc, i, j, k, f[q]);
         const double v = u[q] + dev::bounded(-r.L / r.dL, g.max_step);
         u[q] = v;
-        b[q] = exp(v);
+        b[q] = dev::exp_(v);
     }
     __syncthreads();
 }
@@ -615,7 +615,7 @@ __device__ void rcoarsen64(const BGrid& g, const BGrid& c, double* lds, const Of
                     }
             lds[z.u + qc] = 0.125 * su;
             lds[z.uh + qc] = 0.125 * su;
-            lds[z.b + qc] = exp(0.125 * su);
+            lds[z.b + qc] = dev::exp_(0.125 * su);
             lds[z.f + qc] = 0.125 * sd;
         }
         __syncthreads();
@@ -654,7 +654,7 @@ __device__ void rcorrect64(const BGrid& g, const BGrid& c, double* lds, const Of
                          (1.0 / 64.0) * E(I + si, J + sj, K + sk);
         const double v = lds[a.u + q] + p;
         lds[a.u + q] = v;
-        lds[a.b + q] = exp(v);
+        lds[a.b + q] = dev::exp_(v);
     }
     __syncthreads();
 }
@@ -691,7 +691,7 @@ __device__ void rvcycle64(const BGrid* G, int nl, const UnitCfg& cfg, double* ld
         const BGrid& g = G[nl - 1];
         const Off64 a = off64<W>(nl - 1);
         const int nc = 1 << (3 * g.lg);
-        for (int q = threadIdx.x; q < nc; q += NT) cS[q] = g.A * exp(-lds[a.u + q] * g.inv_np1);
+        for (int q = threadIdx.x; q < nc; q += NT) cS[q] = g.A * dev::exp_(-lds[a.u + q] * g.inv_np1);
         __syncthreads();
         const double* fc = lds + a.fc;
         coarsest64_core<NT>(g, cfg.cap, cfg.rtol, C64{lds + a.u, lds + a.b, cS, lds + a.f, ra, rb},
@@ -718,7 +718,7 @@ __device__ void rload64(const BGrid* G, int nl, double* lds)
     for (int q = threadIdx.x; q < cube(W); q += NT) {
         const double v = g.u[q];
         lds[a.u + q] = v;
-        lds[a.b + q] = exp(v);
+        lds[a.b + q] = dev::exp_(v);
         lds[a.f + q] = brhs(g, q);
     }
     if (!g.periodic)

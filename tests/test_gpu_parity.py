@@ -272,3 +272,58 @@ def test_maximum_size_sine_matches_one_dimensional_newton(mg, ctx, precision):
     assert err <= 1e-10  # |u| ~ 11: 1e-11 relative (measured 4.6e-12 FP64, 1.8e-13 mixed)
     del u_d
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("lo,hi", [(-45.0, 0.0), (-745.0, -600.0), (0.0, 40.0), (600.0, 709.0)])
+def test_exponential_over_its_range(lo, hi):
+    """The kernels' own exp: a field of two values on a checkerboard, u = x and x + 1/2, gives
+    d = 6 C (b_x + b_(x + 1/2)) / 2 + A exp(-x/(n+1)) - f at the cells of value x.  The sums are
+    at most a dozen roundings of 1.1e-16 around two exponentials good to 2.3e-16, so the bar is
+    4e-15 of the sum of the terms' sizes (denormal exponentials: plus their spacing).  With n = 2
+    the curvature term is an exponential of its own; with n = 1 it is 1 / sqrt(b)."""
+    import torch
+    from paper_1110_1379_amd import mgfr
+    ctx = mgfr.Context(0)
+    N = 4
+    i = np.arange(N)
+    black = (i[:, None, None] + i[None, :, None] + i[None, None, :]) % 2 == 1
+    for n in (1.0, 2.0):
+        if n == 1.0 and lo < -700.0:
+            continue  # 1 / sqrt(b) of a denormal b
+        params = mgfr.Params(n=n, fr0_abs=1e-5, box_mpc_h=32.0)
+        c = mgfr.mgfr_constants(params, N)
+        for x in np.concatenate([np.linspace(lo, hi, 61), [lo + 0.3465735902799726, hi - 0.34657359027997264]]):
+            u = np.where(black, x + 0.5, x)
+            d = mgfr.mgfr_residual(ctx, torch.ones((N,) * 3, dtype=torch.float64, device="cuda:0"),
+                                   torch.from_numpy(u).to("cuda:0"), params).cpu().numpy()
+            L = np.longdouble
+            flux = 3 * L(c["C"]) * (np.exp(L(x)) + np.exp(L(x + 0.5)))
+            curv = L(c["A"]) * np.exp(L(-x * (1.0 / (n + 1.0))))  # of the argument as the kernels round it
+            size = float(flux + curv + c["Sbar"])
+            err = abs(float(L(d[0, 0, 0]) - (flux + curv - L(c["Sbar"]))))
+            assert err <= 4e-15 * size + 6 * c["C"] * 5e-324, (n, x, err / size)
+
+
+def test_exponential_outside_its_range():
+    """exp overflows to infinity, vanishes far below the smallest denormal and keeps NaN."""
+    import torch
+    from paper_1110_1379_amd import mgfr
+    ctx = mgfr.Context(0)
+    N = 4
+    params = mgfr.Params(n=2.0, fr0_abs=1e-5, box_mpc_h=32.0)
+    rho = torch.ones((N,) * 3, dtype=torch.float64, device="cuda:0")
+
+    def d(v):
+        return mgfr.mgfr_residual(ctx, rho, torch.full_like(rho, v), params)[0, 0, 0].item()
+    S = mgfr.mgfr_constants(params, N)["Sbar"]
+    for v in (-2200.0, -1e4, -1e300, -np.inf):      # the curvature term exp(-v/3)
+        assert d(v) == np.inf if np.isfinite(v) else not np.isfinite(d(v))
+    assert np.isnan(d(np.nan))
+    assert abs(d(700.0) + S) <= 1e-12 * S               # exp(-233)
+    # neighbours of -800 and -799: both b vanish, no flux is left
+    u = torch.full_like(rho, -800.0)
+    u[0, 0, 0] = -799.0
+    p1 = mgfr.Params(n=9.0, fr0_abs=1e-5, box_mpc_h=32.0)
+    c = mgfr.mgfr_constants(p1, N)
+    r = mgfr.mgfr_residual(ctx, rho, u, p1)[2, 2, 2].item()
+    assert abs(r - (c["A"] * np.exp(80.0) - c["Sbar"])) <= 1e-13 * c["A"] * np.exp(80.0)
