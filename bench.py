@@ -101,7 +101,7 @@ def batch_traffic(prec, settings=None):
 def _tile_shape(prec, tile):
     """Tile shape a finest-level sweep setting selects (0 is the automatic choice)."""
     if prec == "fp64":
-        return "8x64" if tile == 2 else "16x64"
+        return "16x32" if tile == 2 else "16x64"
     return {2: "32x32", 3: "16x64", 4: "8x32", 5: "32x64"}.get(tile, "16x32")
 
 

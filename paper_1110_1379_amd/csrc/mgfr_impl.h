@@ -289,8 +289,8 @@ int fused_sweep_min_n();
 int fused_sweep_planes(int n);
 
 // One red-black sweep from uin into uout (distinct arrays), on 16 x 64 tiles (kTile64x16x64)
-// or 8 x 64 tiles (kTile64x8x64).
-constexpr int kTile64x16x64 = 1, kTile64x8x64 = 2;
+// or 16 x 32 tiles (kTile64x16x32).
+constexpr int kTile64x16x64 = 1, kTile64x16x32 = 2;
 hipError_t ngs_sweep_fused(const Grid& g, const double* uin, double* uout, const double* src, int ti, int tile,
                            hipStream_t s);
 

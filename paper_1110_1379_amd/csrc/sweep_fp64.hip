@@ -1,10 +1,9 @@
 // Fused red-black Newton-Gauss-Seidel sweep, double precision, for levels with n >= 64.
 //
 // One sweep (red cells, then black cells, Sec. V.B.1) in one pass over HBM: each workgroup
-// owns a TJ x 64 tile of (j,k) columns and a chunk of planes i, and streams the planes in
+// owns a TJ x TK tile of (j,k) columns and a chunk of planes i, and streams the planes in
 // order.  Per plane it stages u and b = exp(u) of the tile plus an in-plane halo of two
-// cells in LDS (three plane buffers, so one barrier per plane suffices); the i-neighbours of
-// a column stay in the registers of the thread that owns the column.  At step p it updates
+// cells in LDS (three plane buffers, so one barrier per plane suffices).  At step p it updates
 // the red cells of plane p (tile + 1-cell ring), then the black cells of plane p-1 (tile
 // only), whose red neighbours are all final by then, and stages plane p+1:
 //   red(p)   needs black(p-1), black(p+1), black in-plane            (all old)
@@ -13,6 +12,11 @@
 // them, so they are bit-identical to the owner's, and the sweep equals the two-pass
 // red-then-black sweep cell for cell.  The sweep reads `uin` and writes `uout` (never the
 // same array) so that halo reads always see the values from before the sweep.
+//
+// A thread owns two k-adjacent columns.  At step p the column whose cell on plane p is red
+// does both updates of the step (red on plane p, black on plane p-1, the same column); the
+// other column has nothing to do until the next step.  The roles alternate, so every lane
+// updates at every step.
 #include "device_fp64.h"
 
 #include <type_traits>
@@ -22,29 +26,50 @@ namespace {
 
 using dev::OpVal;
 
-constexpr int kTK = 64;  // tile width along k (contiguous)
-
-// State of one column of a thread's pair.  Plane q of u and b = exp(u) sits in slot
-// (q - i0 + 3) & 3 (planes p-2 .. p+1 at step p), its right-hand side in the same slot
-// (planes p-1 .. p+1 used), and the raw loads of planes p+2 and p+3 in slot (q - i0) & 1.
+// One column of a thread's pair between steps p-1 and p: u and b = exp(u) of plane p+1, the red
+// value it updated last (plane p-2 for the column with the red cell of plane p, p-1 for the
+// other), the raw loads of planes p+2 and p+3 (plane q in slot (q - i0) & 1), and the raw
+// right-hand sides of the red and the black cell of its next active step.  The planes p-1 and
+// p are in LDS.
 struct Col64 {
-    double u[4], b[4], f[4];
-    double ru[2], rf[2];
+    double u1, b1, vr, br, ru[2], fr, fb;
     unsigned col;  // (j,k) offset within a plane
-    int c, fl;     // LDS cell; 1 loaded, 2 red range (tile + ring), 4 tile
+    int c;         // LDS cell
 };
 
-template <int TJ, int NT>
-__global__ void __launch_bounds__(NT) k_ngs_fused(Grid g, const double* __restrict__ uin,
-                                                  double* __restrict__ uout,
-                                                  const double* __restrict__ src, FusedSweep a)
+// An extra column of a thread: a cell of the red ring around the tile (updated on the planes
+// where it is red) or of the halo around that (only staged).
+struct Edge64 {
+    double u1, b1, ru[2], fr;
+    unsigned col;
+    int c, cm, cp;   // LDS cells: its own and its k-neighbours' of the ring
+    bool on, ring;
+};
+
+// Thread t < TJ TK / 2 owns the pair t of k-adjacent tile columns; the ring and the halo are
+// extra columns of some of the threads, the ring cells of one parity side by side so that the
+// wavefronts that update them are full.  A plane's values are (u, b) pairs, a row's even
+// columns before its odd ones: the active columns of neighbouring lanes are then neighbours
+// in LDS, and a neighbour is one 16-byte read.
+// At 16 x 64: 512 threads, 65 KB of LDS and at most 128 VGPRs, so that two workgroups share a
+// compute unit and one computes while the other waits at its barrier; with the pairs laid over
+// the tile and its halo (704 threads) and four planes of (u, b, f) in registers it was one.
+// Bound by its double-precision arithmetic (about 190 instructions per thread and step, 24 B of
+// traffic per cell).  Measured at 512^3, 128 planes: 0.834 ms per sweep (3.86 TB/s at 24 B per
+// cell), 1.045 ms before; at 256^3 111 against 153 us.
+template <int TJ, int TK, int NT>
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4)))
+k_ngs_fused(Grid g, const double* __restrict__ uin, double* __restrict__ uout, const double* __restrict__ src,
+            FusedSweep a)
 {
     if (g.halt && *g.halt) return;
-    constexpr int LJ = TJ + 4, LK = kTK + 4, NL = LJ * LK, NP = NL / 2;
-    static_assert(NP <= NT, "one column pair per thread");
-    // three plane buffers: plane p (red update), plane p-1 (black update), plane p+1 (staged)
-    __shared__ double lu[3][NL];
-    __shared__ double lb[3][NL];
+    constexpr int LJ = TJ + 4, LK = TK + 4, HK = LK / 2, NL = LJ * LK, NP = TJ * TK / 2;
+    constexpr int NR = 2 * (TK + 2) + 2 * TJ;             // ring around the tile
+    constexpr int NH = 2 * (TK + 4) + 2 * (TJ + 2);       // halo around the ring
+    constexpr int NR2 = NR / 2, R1 = (NR2 + 63) / 64 * 64;  // ring cells of one parity; first thread of the second
+    static_assert(NP <= NT && R1 + NR2 <= NT && NR + NH <= NT, "one pair and one extra column per thread");
+    // three plane buffers: plane p-1 (black update), plane p (red update), plane p+1 (staged)
+    __shared__ double2 lv[3][NL];
 
     // workgroup -> (plane chunk, j tile, k tile); consecutive workgroups go to different
     // XCDs, so hand each XCD a contiguous range of tiles (their halos share its L2)
@@ -55,173 +80,203 @@ __global__ void __launch_bounds__(NT) k_ngs_fused(Grid g, const double* __restri
     lid /= a.ntk;
     const int tj = lid % a.ntj;
     const int ci = lid / a.ntj;
-    const int i0 = ci * a.ti, j0 = tj * TJ, k0 = tk * kTK;
+    const int i0 = ci * a.ti, j0 = tj * TJ, k0 = tk * TK;
     const int lg = g.lg, m = g.n - 1;
     const int last = i0 + a.ti + 1;  // last plane read
+    const int t = threadIdx.x;
+    const bool own = NP == NT || t < NP;
 
-    // A thread owns the k-adjacent columns (kk0, kk0+1) of one tile row.  At step p the
-    // column whose cell on plane p is red does both updates of the step (red on plane p,
-    // black on plane p-1, the same column); the other column's cells there are black on p
-    // and red on p-1, so it has nothing to do until the next step.  X is the column with
-    // the red cell on plane i0-1, Y the other; as the roles alternate, every lane updates
-    // at every step.
+    // LDS cell of tile cell (jj, kk), 0 <= jj < LJ, 0 <= kk < LK
+    auto cell = [&](int jj, int kk) { return jj * LK + (kk & 1) * HK + (kk >> 1); };
+    // X is the column of the pair with the red cell on plane i0-1, Y the other
     Col64 X{}, Y{};
-    const int pc = threadIdx.x;
-    if (pc < NP) {
-        const int jj = pc / (LK / 2), kk0 = 2 * (pc - jj * (LK / 2));
-        const int gj = (j0 - 2 + jj) & m, gk0 = (k0 - 2 + kk0) & m;
-        const int sx = (i0 - 1 + gj + gk0) & 1;
-        auto setup = [&](Col64& q, int d) {
-            const int kk = kk0 + d;
-            q.col = (unsigned)((gj << lg) | (gk0 + d));
-            q.c = jj * LK + kk;
-            q.fl = 1;
-            if (jj >= 1 && jj <= LJ - 2 && kk >= 1 && kk <= LK - 2) q.fl |= 2;
-            if (jj >= 2 && jj <= LJ - 3 && kk >= 2 && kk <= LK - 3) q.fl |= 4;
-        };
-        setup(X, sx);
-        setup(Y, 1 - sx);
+    int xm, xp, ym, yp;  // LDS cells of their k-neighbours
+    {
+        const int jj = 2 + t / (TK / 2), kk = 2 + 2 * (t - (jj - 2) * (TK / 2));
+        const int gj = (j0 - 2 + jj) & m, gk = (k0 - 2 + kk) & m;
+        const int sx = (i0 - 1 + gj + gk) & 1;
+        X.col = (unsigned)((gj << lg) | (gk + sx));
+        Y.col = (unsigned)((gj << lg) | (gk + 1 - sx));
+        X.c = cell(jj, kk + sx);
+        xm = cell(jj, kk + sx - 1);
+        xp = cell(jj, kk + sx + 1);
+        Y.c = cell(jj, kk + 1 - sx);
+        ym = cell(jj, kk - sx);
+        yp = cell(jj, kk + 2 - sx);
+    }
+    // E: the ring cells in the order of a walk around it, whose parity alternates: even ones
+    // to threads 0 .., odd ones to threads R1 ..; the halo cells to the threads left over
+    Edge64 E{};
+    int epar = 0;  // parity of (j + k) of E's column
+    {
+        int w = -1;
+        if (t < NR2) w = 2 * t;
+        else if (t >= R1 && t < R1 + NR2) w = 2 * (t - R1) + 1;
+        E.ring = w >= 0;
+        if (!E.ring) w = t < R1 ? t - NR2 : t - 2 * NR2;
+        E.on = E.ring || w < NH;
+        // rectangle of ra x rb cells starting at (o, o)
+        const int o = E.ring ? 1 : 0, ra = LJ - 2 * o, rb = LK - 2 * o;
+        int ej, ek;
+        if (w < rb) { ej = 0; ek = w; }
+        else if (w < rb + ra - 1) { ej = w - rb + 1; ek = rb - 1; }
+        else if (w < 2 * rb + ra - 2) { ej = ra - 1; ek = rb - 2 - (w - (rb + ra - 1)); }
+        else { ej = ra - 2 - (w - (2 * rb + ra - 2)); ek = 0; }
+        if (!E.on) { ej = 0; ek = 0; }
+        ej += o;
+        ek += o;
+        const int gj = (j0 - 2 + ej) & m, gk = (k0 - 2 + ek) & m;
+        E.col = (unsigned)((gj << lg) | gk);
+        E.c = cell(ej, ek);
+        E.cm = cell(ej, ek > 0 ? ek - 1 : 0);
+        E.cp = cell(ej, ek < LK - 1 ? ek + 1 : LK - 1);
+        epar = (gj + gk) & 1;
     }
 
     // element offsets fit in 32 bits (n <= 1024)
-    auto offset = [&](int p, const Col64& q) -> unsigned { return ((unsigned)(p & m) << (2 * lg)) + q.col; };
+    auto offset = [&](int p, unsigned col) -> unsigned { return ((unsigned)(p & m) << (2 * lg)) + col; };
     auto buf = [&](int p) { return (p - i0 + 3) % 3; };
-    auto prologue = [&](Col64& q) {
-        if (!q.fl) return;
-        // planes i0-2, i0-1, i0 in slots 1, 2, 3; plane i0+1 raw in slot 1
-        for (int t = 1; t < 4; ++t) {
-            q.u[t] = uin[offset(i0 - 3 + t, q)];
-            q.f[t] = dev::rhs_value(g, src[offset(i0 - 3 + t, q)]);
-        }
-        q.ru[1] = uin[offset(i0 + 1, q)];
-        q.rf[1] = src[offset(i0 + 1, q)];  // raw: transformed when it becomes plane p+1
-        for (int t = 1; t < 4; ++t) q.b[t] = dev::exp_(q.u[t]);
-        lu[buf(i0 - 1)][q.c] = q.u[2];
-        lb[buf(i0 - 1)][q.c] = q.b[2];
+    auto prologue = [&](auto& q) {
+        // planes i0-2 and i0-1 to LDS, plane i0 in (u1, b1), plane i0+1 raw
+        const double um2 = uin[offset(i0 - 2, q.col)], um1 = uin[offset(i0 - 1, q.col)];
+        q.u1 = uin[offset(i0, q.col)];
+        q.ru[1] = uin[offset(i0 + 1, q.col)];
+        q.b1 = dev::exp_(q.u1);
+        lv[buf(i0 - 2)][q.c] = make_double2(um2, dev::exp_(um2));
+        lv[buf(i0 - 1)][q.c] = make_double2(um1, dev::exp_(um1));
     };
-    prologue(X);
-    prologue(Y);
+    if (own) {
+        X.fr = src[offset(i0 - 1, X.col)];
+        Y.fr = src[offset(i0, Y.col)];
+        prologue(X);
+        prologue(Y);
+    }
+    if (E.on) {
+        if (E.ring) E.fr = src[offset(((i0 - 1 + epar) & 1) ? i0 : i0 - 1, E.col)];
+        prologue(E);
+    }
     __syncthreads();
 
     const double ms = g.max_step;
-    // One plane step, R = (p - i0 + 1) mod 4 fixed at compile time so that the register
-    // planes rotate by renaming.  A holds the red cell of plane p and the black cell of
-    // plane p-1.
-    auto step = [&](auto Rc, int p, Col64& A, Col64& B) {
-        constexpr int R = decltype(Rc)::value;
-        constexpr int M2 = R, M1 = (R + 1) & 3, P0 = (R + 2) & 3, P1 = (R + 3) & 3;
-        constexpr int N2 = (R + 1) & 1, N3 = R & 1;  // raw slots of planes p+2, p+3
-        // issue the loads of plane p+3 two steps ahead of their use
+    // One plane step.  N2 = (p - i0) & 1 is fixed at compile time (the raw slots rotate by
+    // renaming).  A holds the red cell of plane p and the black cell of plane p-1; l = p - i0
+    // mod 3 selects the buffers.
+    auto step = [&](auto N2c, int p, Col64& A, Col64& B, int am, int ap) {
+        constexpr int N2 = decltype(N2c)::value, N3 = N2 ^ 1;  // raw slots of planes p+2, p+3
+        double2* L0 = lv[buf(p)];
+        const double2* Lm = lv[buf(p - 1)];
+        double2* L1 = lv[buf(p + 1)];
+        // the loads of plane p+3, two steps ahead of their use
         if (p + 3 <= last) {
-            if (A.fl) {
-                A.ru[N3] = uin[offset(p + 3, A)];
-                A.rf[N3] = src[offset(p + 3, A)];
+            if (own) {
+                A.ru[N3] = uin[offset(p + 3, A.col)];
+                B.ru[N3] = uin[offset(p + 3, B.col)];
             }
-            if (B.fl) {
-                B.ru[N3] = uin[offset(p + 3, B)];
-                B.rf[N3] = src[offset(p + 3, B)];
-            }
+            if (E.on) E.ru[N3] = uin[offset(p + 3, E.col)];
         }
-        // red cell of plane p (tile + ring); its black neighbours are all old
-        double* LA = lu[buf(p)];
-        double* BA = lb[buf(p)];
-        if (A.fl & 2) {
+        const bool moref = p + 2 <= i0 + a.ti;
+        if (own) {
             const int c = A.c;
-            const double un[6] = {A.u[M1], A.u[P1], LA[c - LK], LA[c + LK], LA[c - 1], LA[c + 1]};
-            const double bn[6] = {A.b[M1], A.b[P1], BA[c - LK], BA[c + LK], BA[c - 1], BA[c + 1]};
-            const OpVal r = dev::cell_op_b(g, A.u[P0], A.b[P0], un, bn, A.f[P0]);
-            const double v = A.u[P0] + dev::bounded(-r.L / r.dL, ms);
-            const double bv = dev::exp_(v);
-            A.u[P0] = v;
-            A.b[P0] = bv;
-            LA[c] = v;
-            BA[c] = bv;
-        }
-        // black cell of plane p-1 (tile); its red neighbours are all new.  Plane p-1 is then
-        // final in both columns.
-        if (p - 1 >= i0) {
-            if (A.fl & 4) {
-                const double* LB = lu[buf(p - 1)];
-                const double* BB = lb[buf(p - 1)];
-                const int c = A.c;
-                const double un[6] = {A.u[M2], A.u[P0], LB[c - LK], LB[c + LK], LB[c - 1], LB[c + 1]};
-                const double bn[6] = {A.b[M2], A.b[P0], BB[c - LK], BB[c + LK], BB[c - 1], BB[c + 1]};
-                const OpVal r = dev::cell_op_b(g, A.u[M1], A.b[M1], un, bn, A.f[M1]);
-                A.u[M1] = A.u[M1] + dev::bounded(-r.L / r.dL, ms);
-                uout[offset(p - 1, A)] = A.u[M1];
+            // red cell of plane p; its black neighbours are all old
+            const double2 m1 = Lm[c], p0 = L0[c];
+            double v, bv;
+            {
+                const double2 jm = L0[c - LK], jp = L0[c + LK], km = L0[am], kp = L0[ap];
+                const double un[6] = {m1.x, A.u1, jm.x, jp.x, km.x, kp.x};
+                const double bn[6] = {m1.y, A.b1, jm.y, jp.y, km.y, kp.y};
+                const OpVal r = dev::cell_op_b(g, p0.x, p0.y, un, bn, dev::rhs_value(g, A.fr));
+                v = p0.x + dev::bounded(-r.L / r.dL, ms);
+                bv = dev::exp_(v);
+                L0[c] = make_double2(v, bv);
             }
-            if (B.fl & 4) uout[offset(p - 1, B)] = B.u[M1];
+            // black cell of plane p-1; its red neighbours are all new.  Plane p-1 is then final
+            // in both columns.
+            if (p - 1 >= i0) {
+                const double2 jm = Lm[c - LK], jp = Lm[c + LK], km = Lm[am], kp = Lm[ap];
+                const double un[6] = {A.vr, v, jm.x, jp.x, km.x, kp.x};
+                const double bn[6] = {A.br, bv, jm.y, jp.y, km.y, kp.y};
+                const OpVal r = dev::cell_op_b(g, m1.x, m1.y, un, bn, dev::rhs_value(g, A.fb));
+                uout[offset(p - 1, A.col)] = m1.x + dev::bounded(-r.L / r.dL, ms);
+                uout[offset(p - 1, B.col)] = B.vr;
+            }
+            A.vr = v;
+            A.br = bv;
+            // A is active again at step p+2
+            if (moref) {
+                A.fr = src[offset(p + 2, A.col)];
+                A.fb = src[offset(p + 1, A.col)];
+            }
         }
-        // stage plane p+1 for the next step; plane p+2 takes the slot of plane p-2
-        double* LC = lu[buf(p + 1)];
-        double* BC = lb[buf(p + 1)];
+        if (E.ring && ((p + epar) & 1) == 0) {
+            const int c = E.c;
+            const double2 m1 = Lm[c], p0 = L0[c], jm = L0[c - LK], jp = L0[c + LK], km = L0[E.cm], kp = L0[E.cp];
+            const double un[6] = {m1.x, E.u1, jm.x, jp.x, km.x, kp.x};
+            const double bn[6] = {m1.y, E.b1, jm.y, jp.y, km.y, kp.y};
+            const OpVal r = dev::cell_op_b(g, p0.x, p0.y, un, bn, dev::rhs_value(g, E.fr));
+            const double v = p0.x + dev::bounded(-r.L / r.dL, ms);
+            L0[c] = make_double2(v, dev::exp_(v));
+            if (moref) E.fr = src[offset(p + 2, E.col)];
+        }
+        // stage plane p+1 for the next step; plane p+2 follows in the registers
         const bool more2 = p + 2 <= last;
-        auto advance = [&](Col64& q) {
-            if (q.fl) {
-                LC[q.c] = q.u[P1];
-                BC[q.c] = q.b[P1];
-                if (more2) {
-                    q.u[M2] = q.ru[N2];
-                    q.b[M2] = dev::exp_(q.ru[N2]);
-                    q.f[M2] = dev::rhs_value(g, q.rf[N2]);
-                }
+        auto advance = [&](auto& q) {
+            L1[q.c] = make_double2(q.u1, q.b1);
+            if (more2) {
+                q.u1 = q.ru[N2];
+                q.b1 = dev::exp_(q.u1);
             }
         };
-        advance(A);
-        advance(B);
+        if (own) {
+            advance(A);
+            advance(B);
+        }
+        if (E.on) advance(E);
         __syncthreads();
     };
     using I0 = std::integral_constant<int, 0>;
     using I1 = std::integral_constant<int, 1>;
-    using I2 = std::integral_constant<int, 2>;
-    using I3 = std::integral_constant<int, 3>;
-    // a.ti + 2 steps (a.ti a multiple of 4): two, then groups of four so that the register
-    // planes and the column roles are back in place at the end of every iteration
-    step(I0{}, i0 - 1, X, Y);
-    step(I1{}, i0, Y, X);
-    for (int p = i0 + 1; p <= i0 + a.ti; p += 4) {
-        step(I2{}, p, X, Y);
-        step(I3{}, p + 1, Y, X);
-        step(I0{}, p + 2, X, Y);
-        step(I1{}, p + 3, Y, X);
+    // a.ti + 2 steps (a.ti even), two by two so that the column roles and the raw slots are
+    // back in place at the end of every iteration
+    for (int p = i0 - 1; p <= i0 + a.ti; p += 2) {
+        step(I1{}, p, X, Y, xm, xp);
+        step(I0{}, p + 1, Y, X, ym, yp);
     }
 }
 
-template <int TJ, int NT>
+template <int TJ, int TK, int NT>
 hipError_t launch(const Grid& g, const double* uin, double* uout, const double* src, FusedSweep a,
                   hipStream_t s)
 {
     a.ntj = g.n / TJ;
-    a.ntk = g.n / kTK;
+    a.ntk = g.n / TK;
     const int nti = g.n / a.ti;
     const unsigned nb = (unsigned)(nti * a.ntj * a.ntk);
-    hipLaunchKernelGGL((k_ngs_fused<TJ, NT>), dim3(nb), dim3(NT), 0, s, g, uin, uout, src, a);
+    hipLaunchKernelGGL((k_ngs_fused<TJ, TK, NT>), dim3(nb), dim3(NT), 0, s, g, uin, uout, src, a);
     return hipGetLastError();
 }
 
 }  // namespace
 
-int fused_sweep_min_n() { return kTK; }
+int fused_sweep_min_n() { return 64; }
 
 int fused_sweep_planes(int n)
 {
-    // planes per workgroup: long enough to amortise the 4 halo planes, short enough to
-    // give >= 1024 workgroups
-    const int tiles = (n / 16) * (n / kTK);
-    int ti = 64;
-    while (ti > 8 && (long long)tiles * (n / ti) < 1024) ti /= 2;
-    return ti > n ? n : ti;
+    // Planes per workgroup: long enough to amortise the 4 planes a chunk reads beyond its own,
+    // short enough to fill the chip (two workgroups of 512 threads to each of 256 compute
+    // units).  Measured, us per sweep at 8 / 16 / 32 / 64 / 128 planes: 128^3 20.5 / 30.9 / 55.5,
+    // 256^3 132.8 / 121.2 / 111.4 / 129.1, 512^3 1047 / 925 / 866 / 839 / 834.
+    return n <= 128 ? 8 : n == 256 ? 32 : 128;
 }
 
 hipError_t ngs_sweep_fused(const Grid& g, const double* uin, double* uout, const double* src, int ti, int tile,
                            hipStream_t s)
 {
-    if (g.n < kTK || g.n > 1024 || uin == uout || ti < 4 || (ti & 3) || ti > g.n || (g.n % ti) != 0)
+    if (g.n < 64 || g.n > 1024 || uin == uout || ti < 4 || (ti & 3) || ti > g.n || (g.n % ti) != 0)
         return hipErrorInvalidValue;
     FusedSweep a{};
     a.ti = ti;
-    if (tile == kTile64x8x64) return launch<8, 448>(g, uin, uout, src, a, s);  // 408 column pairs per 12 x 68
-    return launch<16, 704>(g, uin, uout, src, a, s);  // 680 column pairs per 20 x 68 tile
+    if (tile == kTile64x16x32) return launch<16, 32, 256>(g, uin, uout, src, a, s);
+    return launch<16, 64, 512>(g, uin, uout, src, a, s);
 }
 
 }  // namespace mgfr
