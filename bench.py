@@ -99,7 +99,8 @@ def batch_traffic(prec, settings=None):
 
 
 def _tile_shape(prec, tile):
-    """Tile shape a finest-level sweep setting selects (0 is the automatic choice)."""
+    """Tile shape a finest-level sweep setting selects.  The automatic choice (0) counts as 16x32
+    for the mixed solver, whose counted traffic then holds for an explicit tile only."""
     if prec == "fp64":
         return "16x32" if tile == 2 else "16x64"
     return {2: "32x32", 3: "16x64", 4: "8x32", 5: "32x64"}.get(tile, "16x32")

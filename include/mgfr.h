@@ -99,7 +99,7 @@ typedef struct mgfr_opts {
                              of two; values below coarsest_n count as coarsest_n    [0]      */
     int tile;             /* tile of the finest level's fused sweeps (N >= 64).  FP64: 0 =
                              automatic (16 x 64), 1 = 16 x 64, 2 = 16 x 32 (3 - 5 as 0).  Mixed, the single-precision
-                             correction sweep: 0 = automatic (16 x 32), 1 = 16 x 32, 2 = 32 x
+                             correction sweep: 0 = automatic (16 x 64), 1 = 16 x 32, 2 = 32 x
                              32, 3 = 16 x 64, 5 = 32 x 64 (one tile column pair per thread),
                              4 = 8 x 32 (column pairs over the tile and its halo).
                              Batched solves, launched sweeps of unit levels of side >=

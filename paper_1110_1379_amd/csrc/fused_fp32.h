@@ -44,7 +44,7 @@ struct Col32 {
     float f[4];               // right-hand side, same slots (planes p-1 .. p+1 used)
     float rub[2], re[2], rf[2];  // raw loads of planes p+2 and p+3, plane q in [(q - i0) & 1]
     unsigned col;             // (j,k) offset within a plane
-    int c, fl;                // LDS cell; 1 loaded, 2 red range (tile + ring), 4 tile
+    int c, cl, fl;            // LDS cell, its k-neighbour below (the one above follows it); 1 loaded, 2 red range
 };
 
 // A column of a patch tile: also its position, whether it lies inside the patch, and for a
@@ -104,7 +104,7 @@ __device__ __forceinline__ void sweep_tile(const Op32& o, int n, int lg, int i0,
                                            double* __restrict__ uadd = nullptr)
 {
     constexpr int NT = TJ * TK / 2;
-    constexpr int LK = TK + 4;
+    constexpr int LK = TK + 4, HK = LK / 2;
     constexpr int NR = 2 * (TK + 2) + 2 * TJ;        // ring around the tile
     constexpr int NH = 2 * (TK + 4) + 2 * (TJ + 2);  // outer halo
     static_assert(NR + NH <= NT, "one extra column per thread");
@@ -113,6 +113,13 @@ __device__ __forceinline__ void sweep_tile(const Op32& o, int n, int lg, int i0,
     const int last = i0 + ti + 1;  // last plane read
     const int t = threadIdx.x;
 
+    // A row's even columns lie before its odd ones in LDS: the active columns of neighbouring
+    // lanes are then neighbours there (side by side they are two cells apart, and every 16-byte
+    // read meets its bank twice).
+    auto place = [](Col& q, int jj, int kk) {
+        q.c = jj * LK + (kk & 1) * HK + (kk >> 1);
+        q.cl = jj * LK + ((kk & 1) ? kk >> 1 : HK + (kk >> 1) - 1);
+    };
     // X: the tile column of the pair whose cell on plane i0-1 is red; Y: the other one
     Col X{}, Y{}, E{};
     {
@@ -121,8 +128,8 @@ __device__ __forceinline__ void sweep_tile(const Op32& o, int n, int lg, int i0,
         const int sx = (i0 - 1 + gj + gk0) & 1;
         auto setup = [&](Col& q, int d) {
             q.col = (unsigned)((gj << lg) | (gk0 + d));
-            q.c = (jj + 2) * LK + kk0 + 2 + d;
-            q.fl = 7;
+            place(q, jj + 2, kk0 + 2 + d);
+            q.fl = 3;
             if constexpr (PATCH) {
                 q.j = gj;
                 q.k = gk0 + d;
@@ -149,7 +156,7 @@ __device__ __forceinline__ void sweep_tile(const Op32& o, int n, int lg, int i0,
         ek += off;
         const int gj = (j0 - 2 + ej) & m, gk = (k0 - 2 + ek) & m;
         E.col = (unsigned)((gj << lg) | gk);
-        E.c = ej * LK + ek;
+        place(E, ej, ek);
         E.fl = ring ? 3 : 1;
         epar = (gj + gk) & 1;
         if constexpr (PATCH) {
@@ -269,7 +276,7 @@ __device__ __forceinline__ void sweep_tile(const Op32& o, int n, int lg, int i0,
         const bool pin = !PATCH || (p >= 0 && p <= m);  // a patch's planes -1 and n are not relaxed
         auto red = [&](Col& q) {
             const int c = q.c;
-            const V32 nbv[6] = {q.v[M1], q.v[P1], LA[c - LK], LA[c + LK], LA[c - 1], LA[c + 1]};
+            const V32 nbv[6] = {q.v[M1], q.v[P1], LA[c - LK], LA[c + LK], LA[q.cl], LA[q.cl + 1]};
             const Res32 r = op(p, q, q.v[P0], nbv, q.f[P0]);
             q.v[P0] = make_v(q.v[P0].ub, q.v[P0].e + newton32(r, o.max_step));
             LA[c] = q.v[P0];
@@ -281,7 +288,7 @@ __device__ __forceinline__ void sweep_tile(const Op32& o, int n, int lg, int i0,
         if (p - 1 >= i0) {
             const V32* LB = lv[buf(p - 1)];
             const int c = A.c;
-            const V32 nbv[6] = {A.v[M2], A.v[P0], LB[c - LK], LB[c + LK], LB[c - 1], LB[c + 1]};
+            const V32 nbv[6] = {A.v[M2], A.v[P0], LB[c - LK], LB[c + LK], LB[A.cl], LB[A.cl + 1]};
             const Res32 r = op(p - 1, A, A.v[M1], nbv, A.f[M1]);
             A.v[M1].e = A.v[M1].e + newton32(r, o.max_step);
             if constexpr (ADDU) {

@@ -26,8 +26,9 @@ int planes_for(const mgfr_opts* o, size_t m, int n)
     return mgfr::fused_sweep_planes(n);
 }
 
-// The same for the single-precision sweep, whose 8 x 32 tiles give more workgroups per plane
-// chunk: measured best at 8 planes up to 128^3, 32 at 256^3 and 64 from 512^3.
+// The same for the single-precision sweep.  Measured on 16 x 64 tiles, us per sweep at 8 / 16 /
+// 32 / 64 planes: 128^3 18.4 / 27.3 / 47.5, 256^3 95.6 / 82.4 / 76.8 / 90.3, 512^3 871 / 758 /
+// 697 / 690.
 int planes_for32(const mgfr_opts* o, size_t m, int n)
 {
     if (m == 0 && o->planes > 0 && o->planes <= n) return o->planes;
@@ -73,10 +74,20 @@ int read_red(mgfr_ctx* c, const Hier& h, hipStream_t s, double* out2)
     return MGFR_OK;
 }
 
-// Tile of the single-precision fused sweep: the option on the finest level, else automatic.
+// Tile of the single-precision fused sweep: the option on the finest level, else 16 x 64, the
+// fastest or within 3% of it at every size (16 x 32: 128^3 19.6, 256^3 82.2, 512^3 733 us).
 int tile_for32(const mgfr_opts* o, size_t m)
 {
-    return m == 0 && o->tile > 0 ? o->tile : mgfr::kTile16x32;
+    return m == 0 && o->tile > 0 ? o->tile : mgfr::kTile16x64;
+}
+
+// Whether a level's single-precision sweeps are fused.  At 64^3 the fused sweep takes 10.7 us at
+// its best (16.2 on 16 x 64 tiles), the two colour launches 7.3 us; from 128^3 (18.4 against 23.4
+// us) it is the faster one.  The finest level's options ask for it.
+bool fused32(const mgfr_opts* o, size_t m, int n)
+{
+    const int least = mgfr::fused_sweep_min_n();
+    return n > least || (n == least && m == 0 && (o->planes > 0 || o->tile > 0));
 }
 
 struct Cycle {
@@ -94,7 +105,7 @@ struct Cycle {
         // At 64^3 the fused sweep has 8 columns of tiles and takes 12.8 us at its best, the two
         // colour launches 7.7 us; from 128^3 (20.5 against 29.4 us) it is the faster one.
         const bool fused = L.alt != nullptr && !o_simple &&
-                           (L.g.n > mgfr::fused_sweep_min_n() || o_fused || (m == 0 && o->planes > 0));
+                           (L.g.n > mgfr::fused_sweep_min_n() || o_fused || (m == 0 && (o->planes > 0 || o->tile > 0)));
         const bool timed = m == 0 && (o->flags & MGFR_PROFILE);
         if (timed) {
             if ((size_t)c->ev_used + 2 > c->ev.size()) {
@@ -198,7 +209,8 @@ struct Cycle32 {
             }
             MGFR_TRY(hip_check(c, hipEventRecord(c->ev[c->ev_used], s), "hipEventRecord"));
         }
-        if (L.ealt) {
+        const bool fused = L.ealt && fused32(o, m, L.g.n);
+        if (fused) {
             float* out = cur == L.e ? L.ealt : L.e;
             MGFR_TRY(hip_check(c, mgfr::ngs_sweep32_fused(L.g, L.ub, cur, out, L.f, planes_for32(o, m, L.g.n), tile_for32(o, m), s),
                                "ngs_sweep32_fused"));
@@ -209,7 +221,7 @@ struct Cycle32 {
         if (timed) {
             MGFR_TRY(hip_check(c, hipEventRecord(c->ev[c->ev_used + 1], s), "hipEventRecord"));
             c->ev_used += 2;
-            c->stats.sweep_launches += L.ealt ? 1 : 2;
+            c->stats.sweep_launches += fused ? 1 : 2;
             c->stats.sweep_bytes += 12.0 * (double)mgfr::cells(L.g);
         }
         c->stats.cell_updates += mgfr::cells(L.g);
@@ -591,7 +603,7 @@ int mgfr_smooth32(mgfr_ctx* c, const float* ub, float* e, const float* f, int N,
     if (derive_model(params, &md) != MGFR_OK) return c->fail(MGFR_EINVAL, "invalid model parameters");
     if (!ub || !e || !f || !is_pow2(N) || N < 2 || N > 1024 || nsweeps < 0 || variant < 0 || variant > 2)
         return c->fail(MGFR_EINVAL, "invalid arguments");
-    const bool fused = variant == 2 || (variant == 0 && N >= mgfr::fused_sweep_min_n());
+    const bool fused = variant == 2 || (variant == 0 && fused32(o, 0, N));
     if (fused && N < mgfr::fused_sweep_min_n())
         return c->fail(MGFR_EINVAL, "the fused sweep needs N >= %d", mgfr::fused_sweep_min_n());
     if (fused && o->planes > 0 && (o->planes > N || (o->planes & 3)))
