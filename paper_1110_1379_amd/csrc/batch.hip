@@ -1042,7 +1042,7 @@ struct Batch {
                 ts = c->tail;
             }
             MGFR_TRY(hip_check(c, mgfr::unit_tail(uset(), (const int2*)(dmeta + D.tails), D.ntail, W, dactive, ucfg(),
-                                                  mixed, ts),
+                                                  mixed, units.front().periodic, ts),
                                "unit_tail"));
             if (fork) MGFR_TRY(hip_check(c, hipEventRecord(c->ev_tj[m], c->tail), "hipEventRecord"));
         }
@@ -1168,8 +1168,8 @@ struct Batch {
             MGFR_TRY(hip_check(c, hipStreamWaitEvent(c->side, c->ev_fork, 0), "hipStreamWaitEvent"));
             for (size_t r = 0; r < up.ranges.size(); ++r) {
                 const int3 g = up.ranges[r];
-                MGFR_TRY(hip_check(c, mgfr::unit_whole(uset(), g.x, g.y, g.z, dqueue(r), uout(), ucfg(), mixed, max_wg,
-                                                       c->side),
+                MGFR_TRY(hip_check(c, mgfr::unit_whole(uset(), g.x, g.y, g.z, dqueue(r), uout(), ucfg(), mixed,
+                                                       units.front().periodic, max_wg, c->side),
                                    "unit_whole"));
             }
             MGFR_TRY(hip_check(c, hipEventRecord(c->ev_join, c->side), "hipEventRecord"));

@@ -208,14 +208,14 @@ constexpr int kUnitResidentMax = 16;
 inline bool unit_resident(int side) { return side <= kUnitResidentMax; }
 // The whole units us.order[begin, end), all of side `side`, solved completely by at most
 // max_wg persistent workgroups taking units from the device counter *queue (reset here);
-// results into out.
+// results into out.  periodic: every unit is a box, else a patch.
 hipError_t unit_whole(const UnitSet& us, int begin, int end, int side, int* queue, const UnitOut& out,
-                      const UnitCfg& cfg, bool mixed, int max_wg, hipStream_t s);
+                      const UnitCfg& cfg, bool mixed, bool periodic, int max_wg, hipStream_t s);
 // One workgroup per tails[b] = (index of a large unit's tail level, of side `side`, in
 // us.grids; levels from there): the rest of its V-cycle (the single-precision correction
 // cycle when mixed, with the coarse bases below the tail level).
 hipError_t unit_tail(const UnitSet& us, const int2* tails, int ntail, int side, const int* active, const UnitCfg& cfg,
-                     bool mixed, hipStream_t s);
+                     bool mixed, bool periodic, hipStream_t s);
 // Coarse bases R ub of the tail levels (from each tail level down), for tails the resident
 // kernels do not take.
 hipError_t unit_tail_base32(const UnitSet& us, const int2* tails, int ntail, const int* active, hipStream_t s);

@@ -24,7 +24,7 @@
 // The per-cell arithmetic is that of the batched kernels (batch_dev.h), in the same order.
 #include <algorithm>
 
-#include "batch_dev.h"
+#include "resident.h"
 
 namespace mgfr {
 namespace {
@@ -453,297 +453,61 @@ __global__ void __launch_bounds__(kU) ku_judge(const double* __restrict__ sums, 
 }
 
 // ---- LDS-resident solves -------------------------------------------------------------------
-// A unit of side W, or a large unit's levels from its tail level (side W) down, with level d
-// (side W >> d) held in LDS:
-//   double precision: u, b = exp(u) (rewritten with every update of u) and f, and below the
-//     top uh;
-//   single precision: ub, e, f, b = exp(ub) and S = A exp(-ub/(n+1)) (both fixed while the
-//     base is), and below the top eh.
-// b and S are exactly the values the device-memory kernels evaluate at every visit, so every
-// result is theirs bit for bit; only where the operands wait changes.
-constexpr int cube(int s) { return s * s * s; }
+// A unit of side W, or a large unit's levels from its tail level (side W) down, with every level
+// in LDS (resident.h).  PER: every unit of the launch is a periodic box, else a patch.
+using res::cube;
 
-// workgroup size of the resident kernels of side W
-constexpr int res_threads(int W) { return W >= 16 ? 512 : 256; }
-// The tails relax one unit's lower levels per launch (no persistent loop): twice the threads,
-// for more waves to hide the LDS and arithmetic latency of their sweeps.
-constexpr int tail_threads(int W) { return W >= 16 ? 1024 : res_threads(W); }
-
-// element offsets of level d in the LDS array (double precision: top u, b, f; below + uh;
-// every level its boundary values fc [6][s][s])
-struct Off64 {
-    int u, b, f, uh, fc;
-};
-constexpr int sq6(int s) { return 6 * s * s; }
-template <int W>
-__device__ __forceinline__ Off64 off64(int d)
+// Global element of the cell at storage index q of a level of side S.
+template <int S>
+__device__ __forceinline__ int element(int q)
 {
-    int at = 3 * cube(W) + sq6(W);
-    Off64 o{0, cube(W), 2 * cube(W), -1, 3 * cube(W)};
-    for (int e = 1, s = W / 2; e <= d; ++e, s /= 2) {
-        o = Off64{at, at + cube(s), at + 2 * cube(s), at + 3 * cube(s), at + 4 * cube(s)};
-        at += 4 * cube(s) + sq6(s);
-    }
-    return o;
-}
-template <int W>
-constexpr int res64_size()
-{
-    int t = 3 * cube(W) + sq6(W);
-    for (int s = W / 2; s >= 2; s /= 2) t += 4 * cube(s) + sq6(s);
-    return t;
+    int i, j, k;
+    res::cell_at<S>(q, i, j, k);
+    return (i * S + j) * S + k;
 }
 
-// single precision: top ub, e, f, b, S; below + eh; every level its boundary values fc
-struct Off32 {
-    int ub, e, f, b, S, eh, fc;
-};
-template <int W>
-__device__ __forceinline__ Off32 off32(int d)
+// The boundary values of levels 0 .. nl - 1 of a patch (G[d]: level d) from side S down.
+template <int S, bool PER, int NT, class L, class Below>
+__device__ void load_faces(const BGrid* G, int nl, L& l, Below& below)
 {
-    int at = 5 * cube(W) + sq6(W);
-    Off32 o{0, cube(W), 2 * cube(W), 3 * cube(W), 4 * cube(W), -1, 5 * cube(W)};
-    for (int e = 1, s = W / 2; e <= d; ++e, s /= 2) {
-        o = Off32{at, at + cube(s), at + 2 * cube(s), at + 3 * cube(s), at + 4 * cube(s), at + 5 * cube(s),
-                  at + 6 * cube(s)};
-        at += 6 * cube(s) + sq6(s);
-    }
-    return o;
-}
-template <int W>
-constexpr int res32_size()
-{
-    int t = 5 * cube(W) + sq6(W);
-    for (int s = W / 2; s >= 2; s /= 2) t += 6 * cube(s) + sq6(s);
-    return t;
-}
-
-template <int NT>
-__device__ double wg_sum_t(double v, double* red)
-{
-    red[threadIdx.x] = v;
-    __syncthreads();
-    for (int w = NT / 2; w > 0; w >>= 1) {
-        if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-        __syncthreads();
-    }
-    const double s = red[0];
-    __syncthreads();
-    return s;
-}
-
-// bcell with b and the boundary values read from the level instead of evaluated / loaded
-__device__ __forceinline__ OpVal rcell64(const BGrid& g, const double* u, const double* b, const double* fc, int i,
-                                         int j, int k, double f)
-{
-    const int m = g.n - 1;
-    const int q = (((i << g.lg) + j) << g.lg) + k;
-    const double ui = u[q], bi = b[q];
-    double su = 0.0, sb = 0.0, sbu = 0.0, lg_ = 0.0, dlg = 0.0;
-    int nreg = 0;
-    const int di[6] = {-1, 1, 0, 0, 0, 0}, dj[6] = {0, 0, -1, 1, 0, 0}, dk[6] = {0, 0, 0, 0, -1, 1};
-#pragma unroll
-    for (int x = 0; x < 6; ++x) {
-        const int ii = i + di[x], jj = j + dj[x], kk = k + dk[x];
-        const bool out = ii < 0 || ii > m || jj < 0 || jj > m || kk < 0 || kk > m;
-        if (out && !g.periodic) {
-            const double ug = (1.0 - kR) * fc[face_index(g.lg, x, i, j, k)] + kR * ui;
-            const double bg = dev::exp_(ug);
-            lg_ += (bg + bi) * (ug - ui);
-            dlg += (kR * bg + bi) * (ug - ui) + (bg + bi) * (kR - 1.0);
-        } else {
-            const int qn = ((((ii & m) << g.lg) + (jj & m)) << g.lg) + (kk & m);
-            const double bn = b[qn], du = u[qn] - ui;
-            su += du;
-            sb += bn;
-            sbu = fma(bn, du, sbu);
-            ++nreg;
-        }
-    }
-    const double S = g.A * dev::exp_(-ui * g.inv_np1);
-    OpVal r;
-    r.L = g.C * (fma(bi, su, sbu) + lg_) + S - f;
-    r.dL = g.C * (fma(bi, su, -sb) - nreg * bi + dlg) - S * g.inv_np1;
-    return r;
-}
-
-template <int NT>
-__device__ void rsweep64(const BGrid& g, double* u, double* b, const double* f, const double* fc, int colour)
-{
-    const int half = 1 << (3 * g.lg - 1);
-    for (int t = threadIdx.x; t < half; t += NT) {
-        int i, j, k;
-        const int q = (int)colour_cell(g, t, colour, i, j, k);
-        const OpVal r = rcell64(g, u, b, fc, i, j, k, f[q]);
-        const double v = u[q] + dev::bounded(-r.L / r.dL, g.max_step);
-        u[q] = v;
-        b[q] = dev::exp_(v);
-    }
-    __syncthreads();
-}
-
-
-// coarse u = uh = R u, b = exp(u), f = R d; then f = L^H(uh) - f.  Rounds of NT fine cells
-// (whole slabs of coarse cells: NT is a multiple of 2 n^2, or the level fits one round):
-// every thread evaluates one fine residual into red (NT entries), then each coarse cell of
-// the round sums its eight children in (i, j, k) order.
-template <int NT>
-__device__ void rcoarsen64(const BGrid& g, const BGrid& c, double* lds, const Off64& a, const Off64& z, double* red)
-{
-    const int ncc = 1 << (3 * c.lg);
-    const int nf = 1 << (3 * g.lg);
-    for (int r0 = 0; r0 < nf; r0 += NT) {
-        const int q = r0 + (int)threadIdx.x;
-        if (q < nf) {
-            int i, j, k;
-            cell_of(g, q, i, j, k);
-            red[threadIdx.x] = rcell64(g, lds + a.u, lds + a.b, lds + a.fc, i, j, k, lds[a.f + q]).L;
-        }
-        __syncthreads();
-        const int nct = min(NT, nf - r0) / 8;
-        for (int t = threadIdx.x; t < nct; t += NT) {
-            const int qc = r0 / 8 + t;
-            int I, J, K;
-            cell_of(c, qc, I, J, K);
-            double su = 0.0, sd = 0.0;
-            for (int x = 0; x < 2; ++x)
-                for (int y = 0; y < 2; ++y)
-                    for (int w = 0; w < 2; ++w) {
-                        const int qf = (int)idx3(g.lg, 2 * I + x, 2 * J + y, 2 * K + w);
-                        su += lds[a.u + qf];
-                        sd += red[qf - r0];
-                    }
-            lds[z.u + qc] = 0.125 * su;
-            lds[z.uh + qc] = 0.125 * su;
-            lds[z.b + qc] = dev::exp_(0.125 * su);
-            lds[z.f + qc] = 0.125 * sd;
-        }
-        __syncthreads();
-    }
-    for (int q = threadIdx.x; q < ncc; q += NT) {
-        int i, j, k;
-        cell_of(c, q, i, j, k);
-        lds[z.f + q] = rcell64(c, lds + z.uh, lds + z.b, lds + z.fc, i, j, k, 0.0).L - lds[z.f + q];
-    }
-    __syncthreads();
-}
-
-// uh = u - uh on the coarse level, then u += P(uh) on the fine one (with its b)
-template <int NT>
-__device__ void rcorrect64(const BGrid& g, const BGrid& c, double* lds, const Off64& a, const Off64& z)
-{
-    const int nc = 1 << (3 * c.lg);
-    for (int q = threadIdx.x; q < nc; q += NT) lds[z.uh + q] = lds[z.u + q] - lds[z.uh + q];
-    __syncthreads();
-    const int nf = 1 << (3 * g.lg);
-    const int mc = c.n - 1;
-    const double* eh = lds + z.uh;
-    for (int q = threadIdx.x; q < nf; q += NT) {
-        int i, j, k;
-        cell_of(g, q, i, j, k);
-        const int I = i >> 1, J = j >> 1, K = k >> 1;
-        const int si = (i & 1) ? 1 : -1, sj = (j & 1) ? 1 : -1, sk = (k & 1) ? 1 : -1;
-        auto E = [&](int x, int y, int w) -> double {
-            if (c.periodic) return eh[idx3(c.lg, x & mc, y & mc, w & mc)];
-            if (x < 0 || x > mc || y < 0 || y > mc || w < 0 || w > mc) return 0.0;
-            return eh[idx3(c.lg, x, y, w)];
-        };
-        const double p = (27.0 / 64.0) * E(I, J, K) +
-                         (9.0 / 64.0) * (E(I + si, J, K) + E(I, J + sj, K) + E(I, J, K + sk)) +
-                         (3.0 / 64.0) * (E(I + si, J + sj, K) + E(I + si, J, K + sk) + E(I, J + sj, K + sk)) +
-                         (1.0 / 64.0) * E(I + si, J + sj, K + sk);
-        const double v = lds[a.u + q] + p;
-        lds[a.u + q] = v;
-        lds[a.b + q] = dev::exp_(v);
-    }
-    __syncthreads();
-}
-
-template <int NT>
-__device__ double rrms64(const BGrid& g, double* lds, const Off64& a, double* red)
-{
-    const int nf = 1 << (3 * g.lg);
-    double s = 0.0;
-    for (int q = threadIdx.x; q < nf; q += NT) {
-        int i, j, k;
-        cell_of(g, q, i, j, k);
-        const double d = rcell64(g, lds + a.u, lds + a.b, lds + a.fc, i, j, k, lds[a.f + q]).L;
-        s += d * d;
-    }
-    return sqrt(wg_sum_t<NT>(s, red) / (double)nf);
-}
-
-// V-cycle of the resident levels 0 .. nl - 1 (G[d] the descriptor of level d)
-template <int W, int NT>
-__device__ void rvcycle64(const BGrid* G, int nl, const UnitCfg& cfg, double* lds, double* cS, double* ra, double* rb)
-{
-    // the restriction rounds: whole slabs of coarse cells per NT fine cells on every level
-    static_assert(NT >= 2 * W * W && NT % (2 * W * W) == 0, "NT threads per resident workgroup");
-    for (int d = 0; d + 1 < nl; ++d) {
-        const Off64 a = off64<W>(d), z = off64<W>(d + 1);
-        for (int s = 0; s < cfg.pre; ++s) {
-            rsweep64<NT>(G[d], lds + a.u, lds + a.b, lds + a.f, lds + a.fc, 0);
-            rsweep64<NT>(G[d], lds + a.u, lds + a.b, lds + a.f, lds + a.fc, 1);
-        }
-        rcoarsen64<NT>(G[d], G[d + 1], lds, a, z, ra);
-    }
-    {
-        const BGrid& g = G[nl - 1];
-        const Off64 a = off64<W>(nl - 1);
-        const int nc = 1 << (3 * g.lg);
-        for (int q = threadIdx.x; q < nc; q += NT) cS[q] = g.A * dev::exp_(-lds[a.u + q] * g.inv_np1);
-        __syncthreads();
-        const double* fc = lds + a.fc;
-        coarsest64_core<NT>(g, cfg.cap, cfg.rtol, C64{lds + a.u, lds + a.b, cS, lds + a.f, ra, rb},
-                            [&](int f, int i, int j, int k) { return fc[face_index(g.lg, f, i, j, k)]; });
-        __syncthreads();
-    }
-    for (int d = nl - 2; d >= 0; --d) {
-        const Off64 a = off64<W>(d), z = off64<W>(d + 1);
-        rcorrect64<NT>(G[d], G[d + 1], lds, a, z);
-        for (int s = 0; s < cfg.post; ++s) {
-            rsweep64<NT>(G[d], lds + a.u, lds + a.b, lds + a.f, lds + a.fc, 0);
-            rsweep64<NT>(G[d], lds + a.u, lds + a.b, lds + a.f, lds + a.fc, 1);
+    if constexpr (!PER) {
+        for (int q = threadIdx.x; q < 6 * S * S; q += NT) l.fc[q] = G[0].ub[q];
+        if constexpr (S > 2) {
+            if (nl > 1) load_faces<S / 2, PER, NT>(G + 1, nl - 1, below.lv, below.below);
         }
     }
 }
 
-// level 0 from device memory: u, b = exp(u), f = the level's right-hand side; and the
-// boundary values of levels 0 .. nl - 1 (patches)
-template <int W, int NT>
-__device__ void rload64(const BGrid* G, int nl, double* lds)
+__device__ __forceinline__ res::Op64 op64(const BGrid& g) { return res::Op64{g.C, g.A, g.inv_np1, g.max_step}; }
+__device__ __forceinline__ res::Cfg cycle_cfg(const UnitCfg& c) { return res::Cfg{c.pre, c.post, c.cap, c.rtol}; }
+
+// Level 0 from device memory (u, b and the right-hand side) and every level's boundary values.
+template <int W, bool PER, int NT>
+__device__ void load64(const BGrid* G, int nl, res::Lds64<W, PER>& m)
 {
     const BGrid& g = G[0];
-    const Off64 a = off64<W>(0);
     for (int q = threadIdx.x; q < cube(W); q += NT) {
-        const double v = g.u[q];
-        lds[a.u + q] = v;
-        lds[a.b + q] = dev::exp_(v);
-        lds[a.f + q] = brhs(g, q);
+        const int e = element<W>(q);
+        const double u = g.u[e];
+        m.top.v[q] = make_double2(u, dev::exp_(u));
+        m.top.f[q] = brhs(g, e);
     }
-    if (!g.periodic)
-        for (int d = 0; d < nl; ++d) {
-            const int n6 = 6 << (2 * G[d].lg), fc = off64<W>(d).fc;
-            for (int q = threadIdx.x; q < n6; q += NT) lds[fc + q] = G[d].ub[q];
-        }
+    load_faces<W, PER, NT>(G, nl, m.top, m.below);
     __syncthreads();
 }
 
-template <int W, int NT>
-__device__ void rstore64(const BGrid& g, const double* lds)
+template <int W, bool PER, int NT>
+__device__ void store64(const BGrid& g, const res::Lds64<W, PER>& m)
 {
-    const Off64 a = off64<W>(0);
-    for (int q = threadIdx.x; q < cube(W); q += NT) g.u[q] = lds[a.u + q];
+    for (int q = threadIdx.x; q < cube(W); q += NT) g.u[element<W>(q)] = m.top.v[q].x;
 }
 
-template <int W>
-__global__ void __launch_bounds__(res_threads(W)) kr_whole64(UnitSet us, int begin, int end, int* queue, UnitOut out,
-                                                            UnitCfg cfg)
+template <int W, bool PER>
+__global__ void __launch_bounds__(res::threads(W)) kr_whole64(UnitSet us, int begin, int end, int* queue, UnitOut out,
+                                                             UnitCfg cfg)
 {
-    constexpr int NT = res_threads(W);
-    __shared__ double lds[res64_size<W>()];
-    __shared__ double cS[cube(W < 8 ? W : 8)];
-    __shared__ double ra[NT], rb[NT];
+    constexpr int NT = res::threads(W);
+    __shared__ res::Lds64<W, PER> m;
     __shared__ int slot;
     for (;;) {
         const int it = begin + next_unit(queue, &slot);
@@ -751,310 +515,114 @@ __global__ void __launch_bounds__(res_threads(W)) kr_whole64(UnitSet us, int beg
         const int u = __builtin_amdgcn_readfirstlane(us.order[it]);
         const BGrid* G = us.grids + us.first[u];
         const int nl = us.nlev[u];
+        const res::Op64 o = op64(G[0]);
         double* hist = out.hist + (long long)u * out.H;
-        rload64<W, NT>(G, nl, lds);
-        double rms = rrms64<NT>(G[0], lds, off64<W>(0), ra);
+        load64<W, PER, NT>(G, nl, m);
+        double rms = res::rms64<W, PER, NT>(o, m.top, m.red);
         if (threadIdx.x == 0) hist[0] = rms;
         int k = 0;
         while (isfinite(rms) && rms > cfg.tol && k < cfg.max_cycles) {
-            rvcycle64<W, NT>(G, nl, cfg, lds, cS, ra, rb);
-            rms = rrms64<NT>(G[0], lds, off64<W>(0), ra);
+            res::vcycle64<W, PER, NT>(o, cycle_cfg(cfg), nl, m.top, m.below, m.red);
+            rms = res::rms64<W, PER, NT>(o, m.top, m.red);
             ++k;
             if (threadIdx.x == 0) hist[k] = rms;
         }
-        rstore64<W, NT>(G[0], lds);
+        store64<W, PER, NT>(G[0], m);
         finish(out, u, k, rms, cfg.tol);
     }
 }
 
-template <int W>
-__global__ void __launch_bounds__(tail_threads(W)) kr_tail64(UnitSet us, const int2* __restrict__ tails,
+template <int W, bool PER>
+__global__ void __launch_bounds__(res::threads(W)) kr_tail64(UnitSet us, const int2* __restrict__ tails,
                                                             const int* __restrict__ active, UnitCfg cfg)
 {
-    constexpr int NT = tail_threads(W);
-    __shared__ double lds[res64_size<W>()];
-    __shared__ double cS[cube(W < 8 ? W : 8)];
-    __shared__ double ra[NT], rb[NT];
+    constexpr int NT = res::threads(W);
+    __shared__ res::Lds64<W, PER> m;
     const int2 t = tails[blockIdx.x];
     const BGrid* G = us.grids + t.x;
     if (!active[G[0].unit]) return;
-    rload64<W, NT>(G, t.y, lds);
-    rvcycle64<W, NT>(G, t.y, cfg, lds, cS, ra, rb);
-    rstore64<W, NT>(G[0], lds);
+    load64<W, PER, NT>(G, t.y, m);
+    res::vcycle64<W, PER, NT>(op64(G[0]), cycle_cfg(cfg), t.y, m.top, m.below, m.red);
+    store64<W, PER, NT>(G[0], m);
 }
 
 // ---- single precision, resident ---------------------------------------------------------
-// bcell32 with b, S and the boundary values read from the level instead of evaluated / loaded
-__device__ __forceinline__ Res32 rcell32(const BGrid& g, const Op32& o, const float* ub, const float* e,
-                                         const float* b, const float* S, const float* fc, int i, int j, int k,
-                                         float f)
+template <int S, bool PER, int NT, class L, class Below>
+__device__ void load_faces32(const BGrid* G, int nl, L& l, Below& below)
 {
-    const int m = g.n - 1;
-    const int q = (((i << g.lg) + j) << g.lg) + k;
-    V32 c;
-    c.ub = ub[q];
-    c.e = e[q];
-    c.M = b[q] * em1f(c.e);
-    c.B = b[q] + c.M;
-    float t1 = 0.0f, t2 = 0.0f, su = 0.0f, se = 0.0f, sB = 0.0f, nreg = 0.0f, lgh = 0.0f, dgh = 0.0f;
-    const int di[6] = {-1, 1, 0, 0, 0, 0}, dj[6] = {0, 0, -1, 1, 0, 0}, dk[6] = {0, 0, 0, 0, -1, 1};
+    if constexpr (!PER) {
+        for (int q = threadIdx.x; q < 6 * S * S; q += NT) l.fc[q] = (float)G[0].ub[q];
+        if constexpr (S > 2) {
+            if (nl > 1) load_faces32<S / 2, PER, NT>(G + 1, nl - 1, below.lv, below.below);
+        }
+    }
+}
+
+// The finest level's residual in double precision, with (u, b) staged in the words of the
+// correction level: d = L(u) - f; then r = -d and the base ub = u with its b and S, and e = 0.
+// update: u += e first, also in device memory.  Returns rms(d).
+template <int W, bool PER, int NT>
+__device__ double resid_cast_resident(const BGrid& g, bool update, res::Lds32<W, PER>& m)
+{
+    constexpr int PT = (cube(W) + NT - 1) / NT;
+    const int tid = res::thread_index();
+    const Op32 o = op32(g);
+    const res::Op64 o64 = op64(g);
+    double2* v2 = reinterpret_cast<double2*>(m.top.v);
+    static_assert(sizeof(double2) == sizeof(float4), "one word per cell in either precision");
+    double d[PT], u[PT], s = 0.0;
 #pragma unroll
-    for (int x = 0; x < 6; ++x) {
-        const int ii = i + di[x], jj = j + dj[x], kk = k + dk[x];
-        const bool out = ii < 0 || ii > m || jj < 0 || jj > m || kk < 0 || kk > m;
-        if (out && !g.periodic) {
-            const float ubg = (1.0f - kR32) * fc[face_index(g.lg, x, i, j, k)] + kR32 * c.ub;
-            const float eg = kR32 * c.e;
-            const float bg = __expf(ubg);
-            const float Mg = bg * em1f(eg), Bg = bg + Mg;
-            const float du = ubg - c.ub, de = eg - c.e;
-            lgh += (Mg + c.M) * du + (Bg + c.B) * de;
-            dgh += (kR32 * Bg + c.B) * (du + de) + (Bg + c.B) * (kR32 - 1.0f);
-        } else {
-            const int qn = ((((ii & m) << g.lg) + (jj & m)) << g.lg) + (kk & m);
-            const float nM = b[qn] * em1f(e[qn]);
-            const float nB = b[qn] + nM;
-            const float du = ub[qn] - c.ub, de = e[qn] - c.e;
-            t1 = fmaf(nM, du, t1);
-            t2 = fmaf(nB, de, t2);
-            su += du;
-            se += de;
-            sB += nB;
-            nreg += 1.0f;
+    for (int p = 0; p < PT; ++p) {
+        const int q = tid + p * NT;
+        d[p] = u[p] = 0.0;
+        if (q < cube(W)) {
+            const int e = element<W>(q);
+            u[p] = g.u[e];
+            if (update) {
+                u[p] += (double)m.top.v[q].y;
+                g.u[e] = u[p];
+            }
         }
     }
-    const float Si = S[q];
-    const float x = em1f(-c.e * o.inv_np1);
-    Res32 r;
-    r.N = o.C * (fmaf(c.M, su, t1) + fmaf(c.B, se, t2) + lgh) + Si * x - f;
-    r.dN = o.C * (c.B * (su + se) - sB - nreg * c.B + dgh) - Si * o.inv_np1 * (1.0f + x);
-    return r;
-}
-
-template <int NT>
-__device__ void rsweep32(const BGrid& g, float* lds, const Off32& a, int colour)
-{
-    const Op32 o = op32(g);
-    const int half = 1 << (3 * g.lg - 1);
-    for (int t = threadIdx.x; t < half; t += NT) {
-        int i, j, k;
-        const int q = (int)colour_cell(g, t, colour, i, j, k);
-        const Res32 r = rcell32(g, o, lds + a.ub, lds + a.e, lds + a.b, lds + a.S, lds + a.fc, i, j, k, lds[a.f + q]);
-        lds[a.e + q] = lds[a.e + q] + newton32(r, o.max_step);
+    __syncthreads();  // the words change their type
+#pragma unroll
+    for (int p = 0; p < PT; ++p) {
+        const int q = tid + p * NT;
+        if (q < cube(W)) v2[q] = make_double2(u[p], dev::exp_(u[p]));
     }
     __syncthreads();
-}
-
-
-// coarse e = eh = R e, f = R N; then f = N^H(eh) - f (red: NT entries, as in rcoarsen64)
-template <int NT>
-__device__ void rcoarsen32(const BGrid& g, const BGrid& c, float* lds, const Off32& a, const Off32& z, float* red)
-{
-    const Op32 o = op32(g), oc = op32(c);
-    const int ncc = 1 << (3 * c.lg);
-    const int nf = 1 << (3 * g.lg);
-    // as rcoarsen64: the fine residuals of a round of whole coarse slabs, one per thread
-    for (int r0 = 0; r0 < nf; r0 += NT) {
-        const int q = r0 + (int)threadIdx.x;
-        if (q < nf) {
+#pragma unroll
+    for (int p = 0; p < PT; ++p) {
+        const int q = tid + p * NT;
+        if (q < cube(W)) {
             int i, j, k;
-            cell_of(g, q, i, j, k);
-            red[threadIdx.x] =
-                rcell32(g, o, lds + a.ub, lds + a.e, lds + a.b, lds + a.S, lds + a.fc, i, j, k, lds[a.f + q]).N;
+            res::cell_at<W>(q, i, j, k);
+            d[p] = res::cell64<W, PER>(o64, v2, g.ub, q, i, j, k, brhs(g, (i * W + j) * W + k)).L;
+            s += d[p] * d[p];
         }
-        __syncthreads();
-        const int nct = min(NT, nf - r0) / 8;
-        for (int t = threadIdx.x; t < nct; t += NT) {
-            const int qc = r0 / 8 + t;
-            int I, J, K;
-            cell_of(c, qc, I, J, K);
-            float se = 0.0f, sd = 0.0f;
-            for (int x = 0; x < 2; ++x)
-                for (int y = 0; y < 2; ++y)
-                    for (int w = 0; w < 2; ++w) {
-                        const int qf = (int)idx3(g.lg, 2 * I + x, 2 * J + y, 2 * K + w);
-                        se += lds[a.e + qf];
-                        sd += red[qf - r0];
-                    }
-            lds[z.e + qc] = 0.125f * se;
-            lds[z.eh + qc] = 0.125f * se;
-            lds[z.f + qc] = 0.125f * sd;
-        }
-        __syncthreads();
-    }
-    for (int q = threadIdx.x; q < ncc; q += NT) {
-        int i, j, k;
-        cell_of(c, q, i, j, k);
-        lds[z.f + q] =
-            rcell32(c, oc, lds + z.ub, lds + z.eh, lds + z.b, lds + z.S, lds + z.fc, i, j, k, 0.0f).N - lds[z.f + q];
     }
     __syncthreads();
-}
-
-template <int NT>
-__device__ void rcorrect32(const BGrid& g, const BGrid& c, float* lds, const Off32& a, const Off32& z)
-{
-    const int nc = 1 << (3 * c.lg);
-    for (int q = threadIdx.x; q < nc; q += NT) lds[z.eh + q] = lds[z.e + q] - lds[z.eh + q];
-    __syncthreads();
-    const int nf = 1 << (3 * g.lg);
-    const int mc = c.n - 1;
-    const float* eh = lds + z.eh;
-    for (int q = threadIdx.x; q < nf; q += NT) {
-        int i, j, k;
-        cell_of(g, q, i, j, k);
-        const int I = i >> 1, J = j >> 1, K = k >> 1;
-        const int si = (i & 1) ? 1 : -1, sj = (j & 1) ? 1 : -1, sk = (k & 1) ? 1 : -1;
-        auto E = [&](int x, int y, int w) -> float {
-            if (c.periodic) return eh[idx3(c.lg, x & mc, y & mc, w & mc)];
-            if (x < 0 || x > mc || y < 0 || y > mc || w < 0 || w > mc) return 0.0f;
-            return eh[idx3(c.lg, x, y, w)];
-        };
-        const float p = (27.0f / 64.0f) * E(I, J, K) +
-                        (9.0f / 64.0f) * (E(I + si, J, K) + E(I, J + sj, K) + E(I, J, K + sk)) +
-                        (3.0f / 64.0f) * (E(I + si, J + sj, K) + E(I + si, J, K + sk) + E(I, J + sj, K + sk)) +
-                        (1.0f / 64.0f) * E(I + si, J + sj, K + sk);
-        lds[a.e + q] += p;
-    }
-    __syncthreads();
-}
-
-// b = exp(ub) and S of level d, from its base
-template <int NT>
-__device__ void rbase_terms32(const BGrid& g, float* lds, const Off32& a)
-{
-    const Op32 o = op32(g);
-    const int n3 = 1 << (3 * g.lg);
-    for (int q = threadIdx.x; q < n3; q += NT) {
-        const float ub = lds[a.ub + q];
-        lds[a.b + q] = __expf(ub);
-        lds[a.S + q] = o.A * __expf(-ub * o.inv_np1);
-    }
-}
-
-// coarse bases R ub of levels 1 .. nl - 1 with their b and S
-template <int W, int NT>
-__device__ void rbases32(const BGrid* G, int nl, float* lds)
-{
-    for (int d = 1; d < nl; ++d) {
-        const BGrid& g = G[d - 1];
-        const BGrid& c = G[d];
-        const Off32 a = off32<W>(d - 1), z = off32<W>(d);
-        const int ncc = 1 << (3 * c.lg);
-        for (int qc = threadIdx.x; qc < ncc; qc += NT) {
-            int I, J, K;
-            cell_of(c, qc, I, J, K);
-            float s = 0.0f;
-            for (int x = 0; x < 2; ++x)
-                for (int y = 0; y < 2; ++y)
-                    for (int w = 0; w < 2; ++w) s += lds[a.ub + idx3(g.lg, 2 * I + x, 2 * J + y, 2 * K + w)];
-            lds[z.ub + qc] = 0.125f * s;
-        }
-        __syncthreads();
-        rbase_terms32<NT>(c, lds, z);
-    }
-    __syncthreads();
-}
-
-// the coarsest solve's own LDS: (B, M) per cell and the ghost-face terms
-struct R32Co {
-    float* cB;
-    float* cM;
-    float* gdu;
-    float* gbb;
-    float* ra;
-    float* rb;
-};
-
-template <int W, int NT>
-__device__ void rvcycle32(const BGrid* G, int nl, const UnitCfg& cfg, float* lds, const R32Co& co)
-{
-    // the restriction rounds: whole slabs of coarse cells per NT fine cells on every level
-    static_assert(NT >= 2 * W * W && NT % (2 * W * W) == 0, "NT threads per resident workgroup");
-    for (int d = 0; d + 1 < nl; ++d) {
-        const Off32 a = off32<W>(d), z = off32<W>(d + 1);
-        for (int s = 0; s < cfg.pre; ++s) {
-            rsweep32<NT>(G[d], lds, a, 0);
-            rsweep32<NT>(G[d], lds, a, 1);
-        }
-        rcoarsen32<NT>(G[d], G[d + 1], lds, a, z, co.ra);
-    }
-    {
-        const BGrid& g = G[nl - 1];
-        const Off32 a = off32<W>(nl - 1);
-        const int nc = 1 << (3 * g.lg);
-        for (int q = threadIdx.x; q < nc; q += NT) {
-            const float bq = lds[a.b + q];
-            const float M = bq * em1f(lds[a.e + q]);
-            co.cM[q] = M;
-            co.cB[q] = bq + M;
-            const float* fc = lds + a.fc;
-            coarse_ghosts32(g, q, lds[a.ub + q], co.gdu, co.gbb,
-                            [&](int f, int i, int j, int k) { return fc[face_index(g.lg, f, i, j, k)]; });
-        }
-        __syncthreads();
-        coarsest32_core<NT>(g, cfg.cap, (float)cfg.rtol,
-                            C32{lds + a.ub, lds + a.b, lds + a.e, co.cB, co.cM, lds + a.S, lds + a.f, co.gdu, co.gbb,
-                                co.ra, co.rb});
-        __syncthreads();
-    }
-    for (int d = nl - 2; d >= 0; --d) {
-        const Off32 a = off32<W>(d), z = off32<W>(d + 1);
-        rcorrect32<NT>(G[d], G[d + 1], lds, a, z);
-        for (int s = 0; s < cfg.post; ++s) {
-            rsweep32<NT>(G[d], lds, a, 0);
-            rsweep32<NT>(G[d], lds, a, 1);
+#pragma unroll
+    for (int p = 0; p < PT; ++p) {
+        const int q = tid + p * NT;
+        if (q < cube(W)) {
+            const float ub = (float)u[p];
+            m.top.v[q] = make_float4(ub, 0.0f, __expf(ub), 0.0f);
+            m.top.f[q] = (float)(-d[p]);
+            m.top.S_[q] = o.A * __expf(-ub * o.inv_np1);
         }
     }
-}
-
-// boundary values of levels 0 .. nl - 1 (patches), in single precision
-template <int W, int NT>
-__device__ void rfaces32(const BGrid* G, int nl, float* lds)
-{
-    if (G[0].periodic) return;
-    for (int d = 0; d < nl; ++d) {
-        const int n6 = 6 << (2 * G[d].lg), fc = off32<W>(d).fc;
-        for (int q = threadIdx.x; q < n6; q += NT) lds[fc + q] = (float)G[d].ub[q];
-    }
-}
-
-// Finest level in double precision from device memory: d = L(u) - f; r = -d, ub = u (with its
-// b and S) and e = 0 into level 0; returns rms(d).
-template <int W, int NT>
-__device__ double rresid_cast(const BGrid& g, float* lds, double* red)
-{
-    const Off32 a = off32<W>(0);
-    const long long nf = 1LL << (3 * g.lg);
-    double s = 0.0;
-    for (long long q = threadIdx.x; q < nf; q += NT) {
-        int i, j, k;
-        cell_of(g, q, i, j, k);
-        const double d = bcell(g, g.u, i, j, k, brhs(g, q)).L;
-        lds[a.f + q] = (float)(-d);
-        lds[a.ub + q] = (float)g.u[q];
-        lds[a.e + q] = 0.0f;
-        s += d * d;
-    }
+    s = res::group_sum<NT>(s, m.sum);
     __syncthreads();
-    rbase_terms32<NT>(g, lds, a);
-    return sqrt(wg_sum_t<NT>(s, red) / (double)nf);
+    return sqrt(s / (double)cube(W));
 }
 
-#define MGFR_R32_LDS(W, NTV)                           \
-    constexpr int NT = NTV;                            \
-    __shared__ float lds[res32_size<W>()];             \
-    constexpr int NC = cube(W < 8 ? W : 8);            \
-    __shared__ float cB[NC], cM[NC], gdu[6 * 512], gbb[6 * 512]; \
-    __shared__ float ra[NT], rb[NT];                   \
-    const R32Co co{cB, cM, gdu, gbb, ra, rb};
-
-template <int W>
-__global__ void __launch_bounds__(res_threads(W)) kr_whole_mixed(UnitSet us, int begin, int end, int* queue,
-                                                                UnitOut out, UnitCfg cfg)
+template <int W, bool PER>
+__global__ void __launch_bounds__(res::threads(W)) kr_whole_mixed(UnitSet us, int begin, int end, int* queue,
+                                                                 UnitOut out, UnitCfg cfg)
 {
-    MGFR_R32_LDS(W, res_threads(W))
-    __shared__ double red[NT];
+    constexpr int NT = res::threads(W);
+    __shared__ res::Lds32<W, PER> m;
     __shared__ int slot;
     for (;;) {
         const int it = begin + next_unit(queue, &slot);
@@ -1062,20 +630,17 @@ __global__ void __launch_bounds__(res_threads(W)) kr_whole_mixed(UnitSet us, int
         const int u = __builtin_amdgcn_readfirstlane(us.order[it]);
         const BGrid* G = us.grids + us.first[u];
         const int nl = us.nlev[u];
+        const Op32 o = op32(G[0]);
         double* hist = out.hist + (long long)u * out.H;
-        rfaces32<W, NT>(G, nl, lds);
-        double rms = rresid_cast<W, NT>(G[0], lds, red);
+        load_faces32<W, PER, NT>(G, nl, m.top, m.below);
+        double rms = resid_cast_resident<W, PER, NT>(G[0], false, m);
         if (threadIdx.x == 0) hist[0] = rms;
         int k = 0;
         while (isfinite(rms) && rms > cfg.tol && k < cfg.max_cycles) {
-            rbases32<W, NT>(G, nl, lds);
-            for (int ic = 0; ic < cfg.inner; ++ic) rvcycle32<W, NT>(G, nl, cfg, lds, co);
-            {
-                const Off32 a = off32<W>(0);
-                for (int q = threadIdx.x; q < cube(W); q += NT) G[0].u[q] += (double)lds[a.e + q];
-                __syncthreads();
-            }
-            rms = rresid_cast<W, NT>(G[0], lds, red);
+            res::bases32<W, PER, NT>(o, nl, m.top, m.below);
+            for (int ic = 0; ic < cfg.inner; ++ic)
+                res::vcycle32<W, PER, NT>(o, cycle_cfg(cfg), nl, m.top, m.below, m.red);
+            rms = resid_cast_resident<W, PER, NT>(G[0], true, m);
             ++k;
             if (threadIdx.x == 0) hist[k] = rms;
         }
@@ -1083,30 +648,30 @@ __global__ void __launch_bounds__(res_threads(W)) kr_whole_mixed(UnitSet us, int
     }
 }
 
-template <int W>
-__global__ void __launch_bounds__(tail_threads(W)) kr_tail32(UnitSet us, const int2* __restrict__ tails,
+template <int W, bool PER>
+__global__ void __launch_bounds__(res::threads(W)) kr_tail32(UnitSet us, const int2* __restrict__ tails,
                                                             const int* __restrict__ active, UnitCfg cfg)
 {
-    MGFR_R32_LDS(W, tail_threads(W))
+    constexpr int NT = res::threads(W);
+    __shared__ res::Lds32<W, PER> m;
     const int2 t = tails[blockIdx.x];
     const BGrid* G = us.grids + t.x;
     if (!active[G[0].unit]) return;
     const BGrid& g = G[0];
-    const Off32 a = off32<W>(0);
+    const Op32 o = op32(g);
     for (int q = threadIdx.x; q < cube(W); q += NT) {
-        lds[a.ub + q] = g.ub32[q];
-        lds[a.e + q] = g.e32[q];
-        lds[a.f + q] = g.f32[q];
+        const int e = element<W>(q);
+        const float ub = g.ub32[e];
+        m.top.v[q] = res::make_v4(ub, __expf(ub), g.e32[e]);
+        m.top.f[q] = g.f32[e];
+        m.top.S_[q] = o.A * __expf(-ub * o.inv_np1);
     }
-    rfaces32<W, NT>(G, t.y, lds);
+    load_faces32<W, PER, NT>(G, t.y, m.top, m.below);
     __syncthreads();
-    rbase_terms32<NT>(g, lds, a);
-    __syncthreads();
-    rbases32<W, NT>(G, t.y, lds);
-    rvcycle32<W, NT>(G, t.y, cfg, lds, co);
-    for (int q = threadIdx.x; q < cube(W); q += NT) g.e32[q] = lds[a.e + q];
+    res::bases32<W, PER, NT>(o, t.y, m.top, m.below);
+    res::vcycle32<W, PER, NT>(o, cycle_cfg(cfg), t.y, m.top, m.below, m.red);
+    for (int q = threadIdx.x; q < cube(W); q += NT) g.e32[element<W>(q)] = m.top.v[q].y;
 }
-#undef MGFR_R32_LDS
 
 __global__ void __launch_bounds__(kU) ku_fill_int(int* __restrict__ p, int v, int n)
 {
@@ -1117,39 +682,43 @@ __global__ void __launch_bounds__(kU) ku_fill_int(int* __restrict__ p, int v, in
 
 int unit_block() { return kU; }
 
-template <int W>
+template <int W, bool PER>
 hipError_t whole_resident(const UnitSet& us, int begin, int end, int* queue, const UnitOut& out, const UnitCfg& cfg,
                           bool mixed, int nwg, hipStream_t s)
 {
     if (mixed)
-        hipLaunchKernelGGL(kr_whole_mixed<W>, dim3(nwg), dim3(res_threads(W)), 0, s, us, begin, end, queue, out, cfg);
+        hipLaunchKernelGGL((kr_whole_mixed<W, PER>), dim3(nwg), dim3(res::threads(W)), 0, s, us, begin, end, queue, out, cfg);
     else
-        hipLaunchKernelGGL(kr_whole64<W>, dim3(nwg), dim3(res_threads(W)), 0, s, us, begin, end, queue, out, cfg);
+        hipLaunchKernelGGL((kr_whole64<W, PER>), dim3(nwg), dim3(res::threads(W)), 0, s, us, begin, end, queue, out, cfg);
     return hipGetLastError();
 }
 
-template <int W>
+template <int W, bool PER>
 hipError_t tail_resident(const UnitSet& us, const int2* tails, int ntail, const int* active, const UnitCfg& cfg,
                          bool mixed, hipStream_t s)
 {
     if (mixed)
-        hipLaunchKernelGGL(kr_tail32<W>, dim3(ntail), dim3(tail_threads(W)), 0, s, us, tails, active, cfg);
+        hipLaunchKernelGGL((kr_tail32<W, PER>), dim3(ntail), dim3(res::threads(W)), 0, s, us, tails, active, cfg);
     else
-        hipLaunchKernelGGL(kr_tail64<W>, dim3(ntail), dim3(tail_threads(W)), 0, s, us, tails, active, cfg);
+        hipLaunchKernelGGL((kr_tail64<W, PER>), dim3(ntail), dim3(res::threads(W)), 0, s, us, tails, active, cfg);
     return hipGetLastError();
 }
 
 hipError_t unit_whole(const UnitSet& us, int begin, int end, int side, int* queue, const UnitOut& out,
-                      const UnitCfg& cfg, bool mixed, int max_wg, hipStream_t s)
+                      const UnitCfg& cfg, bool mixed, bool periodic, int max_wg, hipStream_t s)
 {
     if (end <= begin) return hipSuccess;
     const int nwg = std::max(1, std::min({end - begin, 1024, max_wg}));
     hipLaunchKernelGGL(ku_fill_int, dim3(1), dim3(kU), 0, s, queue, 0, 1);
+    auto go = [&](auto whole_box, auto whole_patch) {
+        return periodic ? whole_box(us, begin, end, queue, out, cfg, mixed, nwg, s)
+                        : whole_patch(us, begin, end, queue, out, cfg, mixed, nwg, s);
+    };
     switch (side) {
-    case 2: return whole_resident<2>(us, begin, end, queue, out, cfg, mixed, nwg, s);
-    case 4: return whole_resident<4>(us, begin, end, queue, out, cfg, mixed, nwg, s);
-    case 8: return whole_resident<8>(us, begin, end, queue, out, cfg, mixed, nwg, s);
-    case 16: return whole_resident<16>(us, begin, end, queue, out, cfg, mixed, nwg, s);
+    case 2: return go(whole_resident<2, true>, whole_resident<2, false>);
+    case 4: return go(whole_resident<4, true>, whole_resident<4, false>);
+    case 8: return go(whole_resident<8, true>, whole_resident<8, false>);
+    case 16: return go(whole_resident<16, true>, whole_resident<16, false>);
     default: break;
     }
     if (mixed)
@@ -1160,14 +729,18 @@ hipError_t unit_whole(const UnitSet& us, int begin, int end, int side, int* queu
 }
 
 hipError_t unit_tail(const UnitSet& us, const int2* tails, int ntail, int side, const int* active, const UnitCfg& cfg,
-                     bool mixed, hipStream_t s)
+                     bool mixed, bool periodic, hipStream_t s)
 {
     if (ntail <= 0) return hipSuccess;
+    auto go = [&](auto tail_box, auto tail_patch) {
+        return periodic ? tail_box(us, tails, ntail, active, cfg, mixed, s)
+                        : tail_patch(us, tails, ntail, active, cfg, mixed, s);
+    };
     switch (side) {
-    case 2: return tail_resident<2>(us, tails, ntail, active, cfg, mixed, s);
-    case 4: return tail_resident<4>(us, tails, ntail, active, cfg, mixed, s);
-    case 8: return tail_resident<8>(us, tails, ntail, active, cfg, mixed, s);
-    case 16: return tail_resident<16>(us, tails, ntail, active, cfg, mixed, s);
+    case 2: return go(tail_resident<2, true>, tail_resident<2, false>);
+    case 4: return go(tail_resident<4, true>, tail_resident<4, false>);
+    case 8: return go(tail_resident<8, true>, tail_resident<8, false>);
+    case 16: return go(tail_resident<16, true>, tail_resident<16, false>);
     default: break;
     }
     if (mixed)
