@@ -417,79 +417,6 @@ __global__ void __launch_bounds__(kBlock) k32_fill(float* __restrict__ x, float 
 {
     for (long long q = (long long)blockIdx.x * kBlock + threadIdx.x; q < n; q += (long long)gridDim.x * kBlock) x[q] = v;
 }
-
-// ---- coarsest level in one workgroup (n <= 8) ------------------------------------------
-__global__ void __launch_bounds__(kBlock) k32_coarsest(Grid g, const float* __restrict__ ub, float* __restrict__ e,
-                                                       const float* __restrict__ f, int cap, float rtol)
-{
-    if (g.halt && *g.halt) return;
-    __shared__ float sub[512], se[512], sf[512];
-    __shared__ float rs[kBlock], rf[kBlock];
-    const Op32 o = op32(g);
-    const int nc = 1 << (3 * g.lg);
-    for (int q = threadIdx.x; q < nc; q += kBlock) {
-        sub[q] = ub[q];
-        se[q] = e[q];
-        sf[q] = f[q];
-    }
-    __syncthreads();
-    auto cell = [&](int q, V32& c, V32 (&nb)[6]) {
-        const int i = q >> (2 * g.lg), j = (q >> g.lg) & (g.n - 1), k = q & (g.n - 1);
-        long long qn[6];
-        nbr_index(g.lg, i, j, k, qn);
-#pragma unroll
-        for (int v = 0; v < 6; ++v) nb[v] = make_v(sub[qn[v]], se[qn[v]]);
-        c = make_v(sub[q], se[q]);
-        return (i + j + k) & 1;
-    };
-    // rms of N - f and its rounding floor (single precision: one unit in the last place of
-    // |dN||e| plus the summed magnitudes)
-    auto rms = [&](float& floor) {
-        float s = 0.0f, fl = 0.0f;
-        for (int q = threadIdx.x; q < nc; q += kBlock) {
-            V32 c, nb[6];
-            cell(q, c, nb);
-            const Res32 r = dev32::corr_op(o, c, nb, sf[q]);
-            s += r.N * r.N;
-            const float f1 = 1.1920929e-7f * (fabsf(r.dN) * fabsf(c.e) + fabsf(sf[q]));
-            fl += f1 * f1;
-        }
-        rs[threadIdx.x] = s;
-        rf[threadIdx.x] = fl;
-        __syncthreads();
-        for (int w = kBlock / 2; w > 0; w >>= 1) {
-            if (threadIdx.x < w) {
-                rs[threadIdx.x] += rs[threadIdx.x + w];
-                rf[threadIdx.x] += rf[threadIdx.x + w];
-            }
-            __syncthreads();
-        }
-        const float tot = rs[0], tf = rf[0];
-        __syncthreads();
-        floor = sqrtf(tf / nc);
-        return sqrtf(tot / nc);
-    };
-    float fl0;
-    const float r0 = rtol > 0.0f ? rms(fl0) : 0.0f;
-    for (int sweep = 0; sweep < cap; ++sweep) {
-        if (rtol > 0.0f) {
-            float fl;
-            const float r = rms(fl);
-            if (r <= rtol * r0 || r <= fl) break;
-        }
-        for (int colour = 0; colour < 2; ++colour) {
-            for (int q = threadIdx.x; q < nc; q += kBlock) {
-                V32 c, nb[6];
-                if (cell(q, c, nb) != colour) continue;
-                const Res32 r = dev32::corr_op(o, c, nb, sf[q]);
-                se[q] = c.e + newton32(r, o.max_step);
-            }
-            __syncthreads();
-        }
-    }
-    for (int q = threadIdx.x; q < nc; q += kBlock) e[q] = se[q];
-}
-
 inline unsigned blocks_for(long long work) { return (unsigned)((work + kBlock - 1) / kBlock); }
 
 }  // namespace
@@ -565,14 +492,6 @@ hipError_t fas_rhs32(const Grid& gc, const float* ubc, const float* ehat, float*
 hipError_t restrict_mean32(const Grid& gc, const float* fine, float* coarse, hipStream_t s)
 {
     hipLaunchKernelGGL(k32_restrict_mean, dim3(blocks_for(cells(gc))), dim3(kBlock), 0, s, gc.lg, fine, coarse);
-    return hipGetLastError();
-}
-
-hipError_t coarsest_solve32(const Grid& g, const float* ub, float* e, const float* f, int cap, double rtol,
-                            hipStream_t s)
-{
-    if (g.n > 8) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k32_coarsest, dim3(1), dim3(kBlock), 0, s, g, ub, e, f, cap, (float)rtol);
     return hipGetLastError();
 }
 

@@ -165,79 +165,6 @@ __device__ void block_reduce2(double& a, double& b, double* sh_a, double* sh_b)
     __syncthreads();
 }
 
-__global__ void __launch_bounds__(kBlock) k_coarsest(Grid g, double* __restrict__ u,
-                                                     const double* __restrict__ src, int cap,
-                                                     double rtol, long long* __restrict__ sweeps_done)
-{
-    if (g.halt && *g.halt) return;
-    __shared__ double su[512];
-    __shared__ double sf[512];
-    __shared__ double rs[kBlock], rm[kBlock];
-    const int nc = 1 << (3 * g.lg);
-    for (int q = threadIdx.x; q < nc; q += kBlock) {
-        su[q] = u[q];
-        sf[q] = rhs(g, src, q);
-    }
-    __syncthreads();
-    const int m = g.n - 1;
-    auto nbrs = [&](int q, double (&un)[6]) {
-        const int i = q >> (2 * g.lg), j = (q >> g.lg) & m, k = q & m;
-        un[0] = su[(((i - 1) & m) << (2 * g.lg)) + (j << g.lg) + k];
-        un[1] = su[(((i + 1) & m) << (2 * g.lg)) + (j << g.lg) + k];
-        un[2] = su[(i << (2 * g.lg)) + (((j - 1) & m) << g.lg) + k];
-        un[3] = su[(i << (2 * g.lg)) + (((j + 1) & m) << g.lg) + k];
-        un[4] = su[(i << (2 * g.lg)) + (j << g.lg) + ((k - 1) & m)];
-        un[5] = su[(i << (2 * g.lg)) + (j << g.lg) + ((k + 1) & m)];
-        return (i + j + k) & 1;
-    };
-    // rms of L - f, and the rounding floor of that rms: per cell one unit in the last place
-    // of u times |dL/du| plus one of the summed magnitudes (C (b_nb + b_i)|u_nb - u_i| per
-    // face, the curvature term and |f|)
-    auto rms = [&](double& floor) {
-        double s = 0.0, fl = 0.0;
-        for (int q = threadIdx.x; q < nc; q += kBlock) {
-            double un[6];
-            nbrs(q, un);
-            const double ui = su[q];
-            const OpVal r = cell_op(g, ui, un, sf[q]);
-            s += r.L * r.L;
-            const double bi = dev::exp_(ui);
-            double t = 0.0;
-#pragma unroll
-            for (int v = 0; v < 6; ++v) t += g.C * (dev::exp_(un[v]) + bi) * fabs(un[v] - ui);
-            t += g.A * dev::exp_(-ui * g.inv_np1) + fabs(sf[q]);
-            const double f1 = 2.220446049250313e-16 * (fabs(r.dL) * fabs(ui) + t);
-            fl += f1 * f1;
-        }
-        block_reduce2<false>(s, fl, rs, rm);
-        floor = sqrt(fl / nc);
-        return sqrt(s / nc);
-    };
-    double floor0 = 0.0;
-    const double r0 = rtol > 0.0 ? rms(floor0) : 0.0;
-    int sweep = 0;
-    for (; sweep < cap; ++sweep) {
-        if (rtol > 0.0) {
-            // stop once reduced by rtol or down to the rounding floor
-            double floor;
-            const double r = rms(floor);
-            if (r <= rtol * r0 || r <= floor) break;
-        }
-        for (int colour = 0; colour < 2; ++colour) {
-            for (int q = threadIdx.x; q < nc; q += kBlock) {
-                double un[6];
-                if (nbrs(q, un) != colour) continue;
-                const double ui = su[q];
-                const OpVal r = cell_op(g, ui, un, sf[q]);
-                su[q] = ui + bounded(-r.L / r.dL, g.max_step);
-            }
-            __syncthreads();
-        }
-    }
-    for (int q = threadIdx.x; q < nc; q += kBlock) u[q] = su[q];
-    if (threadIdx.x == 0 && sweeps_done) sweeps_done[0] += sweep;
-}
-
 __global__ void __launch_bounds__(kBlock) k_residual_field(Grid g, const double* __restrict__ u,
                                                            const double* __restrict__ src,
                                                            double* __restrict__ d)
@@ -408,14 +335,6 @@ hipError_t resid_restrict(const Grid& g, const double* u, const double* src, dou
 hipError_t fas_rhs(const Grid& gc, const double* uhat, double* f, hipStream_t s)
 {
     hipLaunchKernelGGL(k_fas_rhs, dim3(blocks_for(cells(gc))), dim3(kBlock), 0, s, gc, uhat, f);
-    return hipGetLastError();
-}
-
-hipError_t coarsest_solve(const Grid& g, double* u, const double* src, int cap, double rtol,
-                          long long* sweeps_done, hipStream_t s)
-{
-    if (g.n > 8) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_coarsest, dim3(1), dim3(kBlock), 0, s, g, u, src, cap, rtol, sweeps_done);
     return hipGetLastError();
 }
 

@@ -262,11 +262,16 @@ hipError_t prolong_add_direct(const Grid& gc, double* uf, const double* ec, hipS
 // uf += P ec at the fine cells whose mask is positive (the others unchanged).
 hipError_t prolong_add_masked(const Grid& gc, double* uf, const double* ec, const float* maskf, hipStream_t s);
 
-// Coarsest level in one workgroup: sweeps until rms(L - f) <= rtol x initial or `cap`
-// sweeps (rtol = 0: exactly cap sweeps).  n <= 8.  Adds the sweeps done to *sweeps_done
-// (may be null).
-hipError_t coarsest_solve(const Grid& g, double* u, const double* src, int cap, double rtol,
-                          long long* sweeps_done, hipStream_t s);
+// ---- the V-cycle's levels of side <= domain_tail_n(), one launch (tail.hip) -------------
+// One V-cycle of the nl levels from the level g (periodic, side 2 - 16) down, the coarsest of
+// side <= 8 swept until rms(L - f) <= rtol x initial, or its rounding floor, or cap sweeps (rtol =
+// 0: exactly cap).  u is relaxed in place; *sweeps is increased by the coarsest level's sweeps.
+int domain_tail_n();
+hipError_t domain_tail(const Grid& g, double* u, const double* src, int nl, int pre, int post, int cap, double rtol,
+                       long long* sweeps, hipStream_t s);
+// The same for the correction equation, e in place; the bases of the levels below come from ub.
+hipError_t domain_tail32(const Grid& g, const float* ub, float* e, const float* f, int nl, int pre, int post, int cap,
+                         double rtol, hipStream_t s);
 
 // d = L(u) - f at every cell.
 hipError_t residual_field(const Grid& g, const double* u, const double* src, double* d,
@@ -333,8 +338,6 @@ hipError_t resid_restrict32(const Grid& g, const float* ub, const float* e, cons
                             float* ehat, float* fc, hipStream_t s);
 hipError_t fas_rhs32(const Grid& gc, const float* ubc, const float* ehat, float* f, hipStream_t s);
 hipError_t restrict_mean32(const Grid& gc, const float* fine, float* coarse, hipStream_t s);
-hipError_t coarsest_solve32(const Grid& g, const float* ub, float* e, const float* f, int cap, double rtol,
-                            hipStream_t s);
 hipError_t fill32(float* x, float v, long long n, hipStream_t s);
 
 // Number of doubles the partial-sum scratch of the reductions needs.

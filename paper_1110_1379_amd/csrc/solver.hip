@@ -90,6 +90,14 @@ bool fused32(const mgfr_opts* o, size_t m, int n)
     return n > least || (n == least && m == 0 && (o->planes > 0 || o->tile > 0));
 }
 
+// Whether the V-cycle runs from level m (side n) down in one launch: the levels of side <= 16, and
+// the coarsest one in any case.  A finest level whose launches are timed keeps them.
+bool tail_from(const mgfr_opts* o, size_t m, int n, size_t nlev)
+{
+    if (m + 1 == nlev) return true;
+    return n <= mgfr::domain_tail_n() && !(m == 0 && (o->flags & MGFR_PROFILE));
+}
+
 struct Cycle {
     mgfr_ctx* c;
     const Hier& h;
@@ -155,10 +163,15 @@ struct Cycle {
     {
         Level& L = h.lv[m];
         const double* src = m == 0 ? finest_src : L.f;
-        if (m + 1 == h.nlev) {
-            return hip_check(c, mgfr::coarsest_solve(L.g, L.u, src, o->coarsest_sweeps, o->coarsest_rtol,
-                                                     h.counter, s),
-                             "coarsest_solve");
+        if (tail_from(o, m, L.g.n, h.nlev)) {
+            for (size_t k = m; k + 1 < h.nlev; ++k) {
+                const long long n = (long long)(o->pre + o->post) * mgfr::cells(h.lv[k].g);
+                c->stats.cell_updates += n;
+                if (k == 0) c->stats.finest_updates += n;
+            }
+            return hip_check(c, mgfr::domain_tail(L.g, L.u, src, (int)(h.nlev - m), o->pre, o->post, o->coarsest_sweeps,
+                                                  o->coarsest_rtol, h.counter, s),
+                             "domain_tail");
         }
         double* cur = L.u;
         for (int k = 0; k < o->pre; ++k) MGFR_TRY(sweep(m, src, cur));
@@ -232,9 +245,16 @@ struct Cycle32 {
     int vcycle(size_t m)
     {
         Level32& L = h.lv32[m];
-        if (m + 1 == h.nlev32)
-            return hip_check(c, mgfr::coarsest_solve32(L.g, L.ub, L.e, L.f, o->coarsest_sweeps, o->coarsest_rtol, s),
-                             "coarsest_solve32");
+        if (tail_from(o, m, L.g.n, h.nlev32)) {
+            for (size_t k = m; k + 1 < h.nlev32; ++k) {
+                const long long n = (long long)(o->pre + o->post) * mgfr::cells(h.lv32[k].g);
+                c->stats.cell_updates += n;
+                if (k == 0) c->stats.finest_updates += n;
+            }
+            return hip_check(c, mgfr::domain_tail32(L.g, L.ub, L.e, L.f, (int)(h.nlev32 - m), o->pre, o->post,
+                                                    o->coarsest_sweeps, o->coarsest_rtol, s),
+                             "domain_tail32");
+        }
         float* cur = L.e;
         for (int k = 0; k < o->pre; ++k) MGFR_TRY(sweep(m, cur));
         Level32& H = h.lv32[m + 1];
@@ -868,6 +888,9 @@ int solve_body(mgfr_ctx* c, const Hier& h, const Model& md, const double* rho, i
         Level32& I0 = h.lv32[0];
         Cycle32 cyc32{c, h, o, s};
         const bool stream = N >= mgfr::fused_sweep_min_n();
+        // levels whose base is restricted by a launch (the tail forms those below its own)
+        size_t nbase = 1;
+        while (nbase < h.nlev32 && !tail_from(o, nbase - 1, h.lv32[nbase - 1].g.n, h.nlev32)) ++nbase;
         double* ucur = u;
         // residual of ucur (+ e when `update`), cast to the single-precision right-hand side
         auto outer_residual = [&](bool update) -> int {
@@ -905,7 +928,7 @@ int solve_body(mgfr_ctx* c, const Hier& h, const Model& md, const double* rho, i
             // the double-precision residual; u and the second finest buffer alternate, so
             // the graph holds two iterations and the solve starts from u
             auto iteration = [&]() -> int {
-                for (size_t m = 1; m < h.nlev32; ++m)
+                for (size_t m = 1; m < nbase; ++m)
                     MGFR_TRY(hip_check(c, mgfr::restrict_mean32(h.lv32[m].g, h.lv32[m - 1].ub, h.lv32[m].ub, s),
                                        "restrict_mean32"));
                 MGFR_TRY(hip_check(c, mgfr::fill32(I0.e, 0.0f, ncell, s), "fill32"));
@@ -951,7 +974,7 @@ int solve_body(mgfr_ctx* c, const Hier& h, const Model& md, const double* rho, i
             if (stream && (k & 1)) ucur = L0.alt;  // an odd count ends in the second buffer
         }
         while (std::isfinite(rms) && !stop && k < o->max_cycles) {
-            for (size_t m = 1; m < h.nlev32; ++m)
+            for (size_t m = 1; m < nbase; ++m)
                 MGFR_TRY(hip_check(c, mgfr::restrict_mean32(h.lv32[m].g, h.lv32[m - 1].ub, h.lv32[m].ub, s),
                                    "restrict_mean32"));
             MGFR_TRY(hip_check(c, mgfr::fill32(I0.e, 0.0f, ncell, s), "fill32"));
