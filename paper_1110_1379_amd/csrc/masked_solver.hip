@@ -211,6 +211,7 @@ int mg_fr_solve_masked(mgfr_ctx* c, const double* rho, const float* mask, int N,
         MGFR_TRY(hip_check(c, mgfr::fold_partials(c->partial, nparts, c->red, s), "fold_partials"));
         MGFR_TRY(read_reduction(c, s, r));
         L0.flags = r[0] == 0.0 ? c->mflags : nullptr;
+        if (L0.flags) MGFR_TRY(hip_check(c, mgfr::masked_boundary(L0.g, c->mflags, s), "masked_boundary"));
     }
     // fixed values: u on entry; coarse masks and fixed values by 8-child means
     MGFR_TRY(hip_check(c, hipMemcpyAsync(L0.w, u, sizeof(double) * ncell, hipMemcpyDeviceToDevice, s),

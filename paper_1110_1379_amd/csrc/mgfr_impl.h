@@ -50,8 +50,10 @@ hipError_t masked_restrict_setup(const Grid& gc, const float* maskf, const doubl
 // of cells whose mask is neither +1 nor -1; their number in *nparts.
 hipError_t masked_flags(const float* mask, long long n, unsigned char* flags, double* partial, int* nparts,
                         hipStream_t s);
+// Bit 1 of the flags of active cells with a masked neighbour.
+hipError_t masked_boundary(const Grid& g, unsigned char* flags, hipStream_t s);
 // One red-black Newton-Gauss-Seidel sweep of the active cells (one launch per colour).  The
-// byte-flag forms take a +1 / -1 mask as flags (1: active).
+// byte-flag forms take a +1 / -1 mask as flags (bit 0: active, bit 1: masked neighbour).
 hipError_t masked_ngs(const Grid& g, const float* mask, const double* w, double* u, const double* src, hipStream_t s);
 hipError_t masked_ngs(const Grid& g, const unsigned char* flags, const double* w, double* u, const double* src,
                       hipStream_t s);
