@@ -112,6 +112,7 @@ struct mgfr_ctx {
         float* mbuf = nullptr;
         double* w = nullptr;          // fixed values (level 0: u on entry)
         double* u = nullptr;          // coarse levels
+        double* alt = nullptr;        // coarse levels above 64^3: second buffer of the fused sweeps
         double* uhat = nullptr;       // coarse: R u of the finer level
         double* f = nullptr;          // coarse: FAS right-hand side
         long long active = 0;         // number of active cells
@@ -135,6 +136,7 @@ struct mgfr_ctx {
             (void)hipFree(mlv[m].w);
             if (m > 0) {
                 (void)hipFree(mlv[m].u);
+                (void)hipFree(mlv[m].alt);
                 (void)hipFree(mlv[m].uhat);
                 (void)hipFree(mlv[m].f);
             }

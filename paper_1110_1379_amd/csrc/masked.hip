@@ -32,16 +32,13 @@ using u8 = unsigned char;
 __device__ __forceinline__ double mval(const float* __restrict__ m, long long q) { return m[q]; }
 __device__ __forceinline__ double mval(const u8* __restrict__ m, long long q) { return (m[q] & 1) ? 1.0 : -1.0; }
 
-// The term of a masked neighbour (mask mn <= 0, fixed value wn) in L_i and dL_i/du_i of an
-// active cell of mask mi, value ui, b_i = bi and fixed value wi: the boundary value
-// u_b = (mi wn - mn wi) / (mi - mn), the ghost u_g = (1 - r) u_b + r ui with r = mn / mi, and
+// The term of a masked neighbour (mask ratio r = m_nb / m_i <= 0, fixed value wn) in L_i and
+// dL_i/du_i of an active cell of value ui, b_i = bi and fixed value wi: with the boundary value
+// u_b = (m_i wn - m_nb wi) / (m_i - m_nb) the ghost u_g = (1 - r) u_b + r ui is wn + r (ui - wi), and
 // b_g = exp(u_g) (eq. phi_b, eq. u_i-1jk, eq. bc_modified_fR_op, eq. bc_modified_fR_dop).
-__device__ __forceinline__ void masked_face(double mi, double mn, double wn, double wi, double ui, double bi,
-                                            double& L, double& dL)
+__device__ __forceinline__ void masked_face(double r, double wn, double wi, double ui, double bi, double& L, double& dL)
 {
-    const double r = mn / mi;
-    const double ubv = (mi * wn - mn * wi) / (mi - mn);
-    const double ug = (1.0 - r) * ubv + r * ui;
+    const double ug = fma(r, ui - wi, wn);
     const double bg = dev::exp_(ug), du = ug - ui;
     L = fma(bg + bi, du, L);
     // chain rule: du_g/du_i = r, db_g/du_i = r b_g
@@ -142,8 +139,36 @@ __device__ __forceinline__ OpVal masked_op(const Grid& g, const M* __restrict__ 
                 wi = w[at(g, i, j, k)];
                 have_wi = true;
             }
-            masked_face(mi, mn, w[qn[v]], wi, ui, bi, L, dL);
+            masked_face(mn / mi, w[qn[v]], wi, ui, bi, L, dL);
         }
+    }
+    const double S = dev::curvature(g, ui, bi);
+    OpVal o;
+    o.L = fma(g.C, L, S) - f;
+    o.dL = fma(g.C, dL, -S * g.inv_np1);
+    return o;
+}
+
+// The same from values at hand: the neighbours' u (a masked one's fixed value), signed b and mask.
+// A wavefront without a masked neighbour runs no ghost terms.
+__device__ __forceinline__ OpVal masked_op_at(const Grid& g, double ui, double bi, const double (&un)[6],
+                                              const double (&bn)[6], const float (&mn)[6], float mi, double f, double wi)
+{
+    double L = 0.0, dL = 0.0;
+    bool any = false;
+#pragma unroll
+    for (int v = 0; v < 6; ++v) {
+        const bool gh = masked_b(bn[v]);
+        any = any || gh;
+        const double b = gh ? 0.0 : bn[v], du = gh ? 0.0 : un[v] - ui, bb = gh ? 0.0 : bi;
+        L = fma(b + bb, du, L);
+        dL += fma(bb, du, -b) - bb;
+    }
+    if (__any(any)) {
+        const double im = 1.0 / (double)mi;
+#pragma unroll
+        for (int v = 0; v < 6; ++v)
+            if (masked_b(bn[v])) masked_face((double)mn[v] * im, un[v], wi, ui, bi, L, dL);
     }
     const double S = dev::curvature(g, ui, bi);
     OpVal o;
@@ -243,30 +268,45 @@ __global__ void __launch_bounds__(kB) km_ngs_colour(Grid g, const M* __restrict_
     u[q] = ui + bounded(-r.L / r.dL, g.max_step);
 }
 
-// ---- fused red-black sweep of a level read as byte flags (n >= 64) ------------------------
+// ---- fused red-black sweep of a level (n >= 64), of byte flags or of a float mask -----------
 // The domain's fused sweep (sweep_fp64.hip: red cells of plane p, then black cells of plane p-1,
 // in one pass over HBM, out of place from uin to uout, (u, b) of the planes in LDS, one tile
 // column pair per thread with the ring and the halo as extra columns) with the mask scheme: a
 // masked cell carries -b, is never updated and is copied to uout unchanged.  The density is
-// loaded for active cells and w for those with a masked neighbour.  Every update sees the operands
-// of the two-colour sweep in the same order.
+// loaded for active cells and w for those with a masked neighbour.  On byte flags every update sees
+// the operands of the two-colour sweep in the same order.  A float mask (the coarse levels') is
+// staged beside (u, b).
 // Bound by its double-precision arithmetic, the ghosts' on top of the domain sweep's.  Measured at
 // 512^3 with 61% of the cells active: 1.32 ms per sweep; with the column pairs laid over tile and
-// halo (704 threads) and an exponential and a branch per masked neighbour 2.19 ms.
+// halo (704 threads) and an exponential and a branch per masked neighbour 2.19 ms.  Float mask at
+// 256^3: 264 us, the two colour launches 443 us.
 constexpr int kMK = 64;  // tile width along k
 
+// A flag byte or a mask value: whether the cell is active, and whether its update needs w.
+__device__ __forceinline__ bool is_active(int fl) { return fl & 1; }
+__device__ __forceinline__ bool is_active(float m) { return m > 0.0f; }
+__device__ __forceinline__ bool needs_w(int fl) { return fl & 2; }
+__device__ __forceinline__ bool needs_w(float m) { return m > 0.0f; }
+template <class M>
+using MaskVal = typename std::conditional<std::is_same<M, float>::value, float, int>::type;
+
+template <class V>
 struct ColM {
     double u1, b1, vr, br, ru[2], fr, fb, wr, wb;
-    int m1, rm[2];  // flags of plane p+1 and, raw, of planes p+2 and p+3
+    V m1, rm[2];    // flag or mask of plane p+1 and, raw, of planes p+2 and p+3
+    V mr;           // mask of the cell (vr, br)
     unsigned col;   // (j,k) offset within a plane
     int c, cl;      // LDS cell and its k-neighbour below (the one above follows it)
 };
 
-template <int TJ, int TK>
+template <int TJ, int TK, class M>
 __global__ void __launch_bounds__(TJ * TK / 2) __attribute__((amdgpu_waves_per_eu(4)))
-km_ngs_fused(Grid g, const u8* __restrict__ flags, const double* __restrict__ w, const double* __restrict__ uin,
+km_ngs_fused(Grid g, const M* __restrict__ flags, const double* __restrict__ w, const double* __restrict__ uin,
              double* __restrict__ uout, const double* __restrict__ src, FusedSweep a)
 {
+    using V = MaskVal<M>;
+    using Col = ColM<V>;
+    constexpr bool FM = std::is_same<M, float>::value;
     constexpr int NT = TJ * TK / 2;
     constexpr int LJ = TJ + 4, LK = TK + 4, HK = LK / 2, NL = LJ * LK;
     constexpr int NR = 2 * (TK + 2) + 2 * TJ;
@@ -274,6 +314,7 @@ km_ngs_fused(Grid g, const u8* __restrict__ flags, const double* __restrict__ w,
     constexpr int NR2 = NR / 2, R1 = (NR2 + 63) / 64 * 64;
     static_assert(R1 + NR2 <= NT && NR + NH <= NT, "one extra column per thread");
     __shared__ double2 lv[3][NL];
+    __shared__ float lm[FM ? 3 : 1][FM ? NL : 1];
     const int nb = gridDim.x;
     int lid = blockIdx.x;
     if ((nb & 7) == 0) lid = (lid & 7) * (nb >> 3) + (lid >> 3);
@@ -287,12 +328,12 @@ km_ngs_fused(Grid g, const u8* __restrict__ flags, const double* __restrict__ w,
     const int t = threadIdx.x;
 
     // a row's even columns before its odd ones
-    auto place = [](ColM& q, int jj, int kk) {
+    auto place = [](Col& q, int jj, int kk) {
         q.c = jj * LK + (kk & 1) * HK + (kk >> 1);
         q.cl = jj * LK + ((kk & 1) ? kk >> 1 : HK + (kk >> 1) - 1);
     };
     // X is the column of the pair with the red cell on plane i0-1, Y the other
-    ColM X{}, Y{}, E{};
+    Col X{}, Y{}, E{};
     {
         const int jj = 2 + t / (TK / 2), kk = 2 + 2 * (t - (jj - 2) * (TK / 2));
         const int gj = (j0 - 2 + jj) & m, gk = (k0 - 2 + kk) & m;
@@ -327,32 +368,36 @@ km_ngs_fused(Grid g, const u8* __restrict__ flags, const double* __restrict__ w,
         epar = (gj + gk) & 1;
     }
 
-    auto offset = [&](int p, const ColM& q) -> unsigned { return ((unsigned)(p & m) << (2 * lg)) + q.col; };
+    auto offset = [&](int p, const Col& q) -> unsigned { return ((unsigned)(p & m) << (2 * lg)) + q.col; };
     auto buf = [&](int p) { return (p - i0 + 3) % 3; };
     // the density and w of a cell of flag byte fl on plane p, where an update needs them
-    auto fetch = [&](int p, const ColM& q, int fl, double& fv, double& wv) {
-        if (fl & 1) fv = src[offset(p, q)];
-        if (fl & 2) wv = w[offset(p, q)];
+    auto fetch = [&](int p, const Col& q, V fl, double& fv, double& wv) {
+        if (is_active(fl)) fv = src[offset(p, q)];
+        if (needs_w(fl)) wv = w[offset(p, q)];
     };
-    auto prologue = [&](ColM& q) {
+    auto prologue = [&](Col& q) {
         const double um2 = uin[offset(i0 - 2, q)], um1 = uin[offset(i0 - 1, q)];
-        const int fm2 = flags[offset(i0 - 2, q)], fm1 = flags[offset(i0 - 1, q)];
+        const V fm2 = flags[offset(i0 - 2, q)], fm1 = flags[offset(i0 - 1, q)];
         q.u1 = uin[offset(i0, q)];
         q.m1 = flags[offset(i0, q)];
         q.ru[1] = uin[offset(i0 + 1, q)];
         q.rm[1] = flags[offset(i0 + 1, q)];
-        q.b1 = signed_b(q.u1, q.m1 & 1);
-        lv[buf(i0 - 2)][q.c] = make_double2(um2, signed_b(um2, fm2 & 1));
-        lv[buf(i0 - 1)][q.c] = make_double2(um1, signed_b(um1, fm1 & 1));
+        q.b1 = signed_b(q.u1, is_active(q.m1));
+        lv[buf(i0 - 2)][q.c] = make_double2(um2, signed_b(um2, is_active(fm2)));
+        lv[buf(i0 - 1)][q.c] = make_double2(um1, signed_b(um1, is_active(fm1)));
+        if constexpr (FM) {
+            lm[buf(i0 - 2)][q.c] = fm2;
+            lm[buf(i0 - 1)][q.c] = fm1;
+        }
         return fm1;
     };
     {
-        const int fx = prologue(X);
+        const V fx = prologue(X);
         fetch(i0 - 1, X, fx, X.fr, X.wr);
         prologue(Y);
         fetch(i0, Y, Y.m1, Y.fr, Y.wr);
         if (eon) {
-            const int fe = prologue(E);
+            const V fe = prologue(E);
             if (ering) {
                 if ((i0 - 1 + epar) & 1) fetch(i0, E, E.m1, E.fr, E.wr);
                 else fetch(i0 - 1, E, fe, E.fr, E.wr);
@@ -362,12 +407,13 @@ km_ngs_fused(Grid g, const u8* __restrict__ flags, const double* __restrict__ w,
     __syncthreads();
 
     const double ms = g.max_step;
-    auto step = [&](auto N2c, int p, ColM& A, ColM& B) {
+    auto step = [&](auto N2c, int p, Col& A, Col& B) {
         constexpr int N2 = decltype(N2c)::value, N3 = N2 ^ 1;
         double2* L0 = lv[buf(p)];
         const double2* Lm = lv[buf(p - 1)];
         double2* L1 = lv[buf(p + 1)];
-        auto load = [&](ColM& q) {
+        auto Lf = [&](int pp) -> float* { return lm[FM ? buf(pp) : 0]; };
+        auto load = [&](Col& q) {
             q.ru[N3] = uin[offset(p + 3, q)];
             q.rm[N3] = flags[offset(p + 3, q)];
         };
@@ -376,13 +422,25 @@ km_ngs_fused(Grid g, const u8* __restrict__ flags, const double* __restrict__ w,
             load(B);
             if (eon) load(E);
         }
+        // the operator at the cell of column q on plane pp (its mask from LDS; below and above: the
+        // masks of its i-neighbours)
+        auto op = [&](const Col& q, int pp, const double (&un)[6], const double (&bn)[6], float below, V above,
+                      const double2& own, double fv, double wv) -> OpVal {
+            if constexpr (FM) {
+                const float* l = Lf(pp);
+                const float mn[6] = {below, above, l[q.c - LK], l[q.c + LK], l[q.cl], l[q.cl + 1]};
+                return masked_op_at(g, own.x, own.y, un, bn, mn, l[q.c], dev::rhs_value(g, fv), wv);
+            } else {
+                return masked_op_pm1(g, own.x, own.y, un, bn, dev::rhs_value(g, fv), wv);
+            }
+        };
         // red cell of plane p, if active
-        auto red = [&](const ColM& q, const double2& m1, const double2& p0) -> double2 {
+        auto red = [&](const Col& q, const double2& m1, const double2& p0) -> double2 {
             const int c = q.c;
             const double2 jm = L0[c - LK], jp = L0[c + LK], km = L0[q.cl], kp = L0[q.cl + 1];
             const double un[6] = {m1.x, q.u1, jm.x, jp.x, km.x, kp.x};
             const double bn[6] = {m1.y, q.b1, jm.y, jp.y, km.y, kp.y};
-            const OpVal r = masked_op_pm1(g, p0.x, p0.y, un, bn, dev::rhs_value(g, q.fr), q.wr);
+            const OpVal r = op(q, p, un, bn, Lf(p - 1)[FM ? c : 0], q.m1, p0, q.fr, q.wr);
             const double v = p0.x + bounded(-r.L / r.dL, ms);
             return make_double2(v, dev::exp_(v));
         };
@@ -401,7 +459,7 @@ km_ngs_fused(Grid g, const u8* __restrict__ flags, const double* __restrict__ w,
                     const double2 jm = Lm[c - LK], jp = Lm[c + LK], km = Lm[A.cl], kp = Lm[A.cl + 1];
                     const double un[6] = {A.vr, v.x, jm.x, jp.x, km.x, kp.x};
                     const double bn[6] = {A.br, v.y, jm.y, jp.y, km.y, kp.y};
-                    const OpVal r = masked_op_pm1(g, m1.x, m1.y, un, bn, dev::rhs_value(g, A.fb), A.wb);
+                    const OpVal r = op(A, p - 1, un, bn, (float)A.mr, FM ? (V)Lf(p)[FM ? c : 0] : V(0), m1, A.fb, A.wb);
                     un1 = m1.x + bounded(-r.L / r.dL, ms);
                 }
                 uout[offset(p - 1, A)] = un1;
@@ -409,6 +467,7 @@ km_ngs_fused(Grid g, const u8* __restrict__ flags, const double* __restrict__ w,
             }
             A.vr = v.x;
             A.br = v.y;
+            if constexpr (FM) A.mr = Lf(p)[c];
         }
         const bool ered = ering && ((p + epar) & 1) == 0;
         if (ered) {
@@ -418,13 +477,14 @@ km_ngs_fused(Grid g, const u8* __restrict__ flags, const double* __restrict__ w,
         // stage plane p+1; plane p+2 follows in the registers, and with its flags known the
         // right-hand sides and fixed values of A's next active step (p+2) are loaded
         const bool more2 = p + 2 <= last;
-        const int mA = A.m1;
-        auto advance = [&](ColM& q) {
+        const V mA = A.m1;
+        auto advance = [&](Col& q) {
             L1[q.c] = make_double2(q.u1, q.b1);
+            if constexpr (FM) Lf(p + 1)[q.c] = q.m1;
             if (more2) {
                 q.u1 = q.ru[N2];
                 q.m1 = q.rm[N2];
-                q.b1 = signed_b(q.u1, q.m1 & 1);
+                q.b1 = signed_b(q.u1, is_active(q.m1));
             }
         };
         advance(A);
@@ -550,22 +610,29 @@ __global__ void __launch_bounds__(kB) km_norm(Grid g, const M* __restrict__ mask
 // LDS, keeps the i-neighbours in registers and has the next two planes in flight, so each value
 // and exponential is fetched and formed once.  One column per thread.  RESTRICT: R u of all 8
 // children and R d of the active ones into active coarse cells; masked coarse cells take their
-// fixed value and a zero right-hand side.  Otherwise the norm's partial (sum d^2, max |d|) of the
-// workgroup, summed in a fixed order.
+// fixed value and a zero right-hand side.  FAS: f = L(u) - f at active cells (fc holds f).  NORM: the
+// partial (sum d^2, max |d|) of the workgroup, summed in a fixed order.
 // Bound by its arithmetic and the barrier of each plane: the small tile puts three workgroups on
 // a compute unit.  Measured at 512^3, 61% active: norm 1.25 ms (8 x 64 tiles, 704 threads, two
-// barriers a plane: 1.69), restriction 1.67 ms (one thread per coarse cell: 2.2).
-template <int TJ, int TK, int NT, bool RESTRICT>
-__global__ void __launch_bounds__(NT) km_stream(Grid g, const u8* __restrict__ flags, const double* __restrict__ w,
+// barriers a plane: 1.69), restriction 1.67 ms (one thread per coarse cell: 2.2);
+// float masks at 256^3: restriction 286 us (360 - 565), FAS right-hand side of 256^3 243 us (310 - 380).
+// What km_stream does with d = L(u) - f.
+enum { kNorm, kRestrict, kFas };
+
+template <int TJ, int TK, int NT, int MODE, class M>
+__global__ void __launch_bounds__(NT) km_stream(Grid g, const M* __restrict__ flags, const double* __restrict__ w,
                                                 const double* __restrict__ u, const double* __restrict__ src,
                                                 double* __restrict__ partial, const float* __restrict__ maskc,
                                                 const double* __restrict__ wc, double* __restrict__ uc,
                                                 double* __restrict__ uhat, double* __restrict__ fc, int ti)
 {
+    using V = MaskVal<M>;
+    constexpr bool FM = std::is_same<M, float>::value, RESTRICT = MODE == kRestrict;
     constexpr int LJ = TJ + 2, LK = TK + 2, NL = LJ * LK;
     static_assert(NL <= NT && TJ * TK / 4 <= NT, "one column per thread");
     __shared__ double2 lv[2][NL];
-    __shared__ double ra[RESTRICT ? TJ * TK : NT], rb[RESTRICT ? TJ * TK : NT];
+    __shared__ float lm[FM ? 2 : 1][FM ? NL : 1];
+    __shared__ double ra[MODE == kRestrict ? TJ * TK : NT], rb[MODE == kRestrict ? TJ * TK : NT];
     const int ntk = g.n / TK, ntj = g.n / TJ;
     const int nb = gridDim.x;
     int lid = blockIdx.x;
@@ -583,35 +650,42 @@ __global__ void __launch_bounds__(NT) km_stream(Grid g, const u8* __restrict__ f
     auto off = [&](int p) -> unsigned { return ((unsigned)(p & m) << (2 * lg)) + col; };
     double um = 0.0, uv = 0.0, up = 0.0, bm = 0.0, bv = 0.0, bp = 0.0, f0 = 0.0, w0 = 0.0, ru = 0.0;
     double usum = 0.0, dsum = 0.0;
-    int fp = 0, rm = 0;
+    V mm = 0, mv = 0, fp = 0, rm = 0;
     if (on) {
         um = u[off(i0 - 1)];
         uv = u[off(i0)];
         up = u[off(i0 + 1)];
         ru = u[off(i0 + 2)];
-        const int fm = flags[off(i0 - 1)], fv = flags[off(i0)];
+        mm = flags[off(i0 - 1)];
+        mv = flags[off(i0)];
         fp = flags[off(i0 + 1)];
         rm = flags[off(i0 + 2)];
-        if (in && (fv & 1)) f0 = src[off(i0)];
-        if (in && (fv & 2)) w0 = w[off(i0)];
-        bm = signed_b(um, fm & 1);
-        bv = signed_b(uv, fv & 1);
-        bp = signed_b(up, fp & 1);
+        if (in && MODE != kFas && is_active(mv)) f0 = src[off(i0)];
+        if (in && MODE == kFas && is_active(mv)) f0 = fc[off(i0)];
+        if (in && needs_w(mv)) w0 = w[off(i0)];
+        bm = signed_b(um, is_active(mm));
+        bv = signed_b(uv, is_active(mv));
+        bp = signed_b(up, is_active(fp));
         lv[0][t] = make_double2(uv, bv);
+        if constexpr (FM) lm[0][t] = mv;
     }
     __syncthreads();
     double s = 0.0, mx = 0.0;
     for (int p = i0; p < i0 + ti; ++p) {
         // loads: u and flag of plane p+3, density and w of plane p+1
         double ru3 = 0.0, f1 = 0.0, w1 = 0.0;
-        int rm3 = 0;
+        V rm3 = 0;
         if (on && p + 3 <= i0 + ti) {
             ru3 = u[off(p + 3)];
             rm3 = flags[off(p + 3)];
         }
         if (in && p + 1 < i0 + ti) {
-            if (fp & 1) f1 = src[off(p + 1)];
-            if (fp & 2) w1 = w[off(p + 1)];
+            if (MODE == kFas) {
+                if (is_active(fp)) f1 = fc[off(p + 1)];
+            } else if (is_active(fp)) {
+                f1 = src[off(p + 1)];
+            }
+            if (needs_w(fp)) w1 = w[off(p + 1)];
         }
         const double2* L = lv[(p - i0) & 1];
         const bool second = RESTRICT && ((p - i0) & 1);
@@ -621,9 +695,17 @@ __global__ void __launch_bounds__(NT) km_stream(Grid g, const u8* __restrict__ f
                 const double2 jm = L[t - LK], jp = L[t + LK], km = L[t - 1], kp = L[t + 1];
                 const double un[6] = {um, up, jm.x, jp.x, km.x, kp.x};
                 const double bn[6] = {bm, bp, jm.y, jp.y, km.y, kp.y};
-                d = masked_op_pm1(g, uv, bv, un, bn, dev::rhs_value(g, f0), w0).L;
+                if constexpr (FM) {
+                    const float* l = lm[(p - i0) & 1];
+                    const float mn[6] = {mm, fp, l[t - LK], l[t + LK], l[t - 1], l[t + 1]};
+                    d = masked_op_at(g, uv, bv, un, bn, mn, mv, MODE == kFas ? 0.0 : dev::rhs_value(g, f0), w0).L;
+                } else {
+                    d = masked_op_pm1(g, uv, bv, un, bn, MODE == kFas ? 0.0 : dev::rhs_value(g, f0), w0).L;
+                }
             }
-            if (RESTRICT) {
+            if (MODE == kFas) {
+                if (!masked_b(bv)) fc[off(p)] = d - f0;
+            } else if (RESTRICT) {
                 usum = second ? usum + uv : uv;
                 dsum = second ? dsum + d : d;
                 if (second) {
@@ -658,13 +740,16 @@ __global__ void __launch_bounds__(NT) km_stream(Grid g, const u8* __restrict__ f
         }
         if (on) {
             lv[(p + 1 - i0) & 1][t] = make_double2(up, bp);
+            if constexpr (FM) lm[(p + 1 - i0) & 1][t] = fp;
+            mm = mv;
+            mv = fp;
             um = uv;
             bm = bv;
             uv = up;
             bv = bp;
             up = ru;
             fp = rm;
-            bp = signed_b(ru, rm & 1);
+            bp = signed_b(ru, is_active(rm));
             ru = ru3;
             rm = rm3;
             f0 = f1;
@@ -672,7 +757,7 @@ __global__ void __launch_bounds__(NT) km_stream(Grid g, const u8* __restrict__ f
         }
         __syncthreads();
     }
-    if constexpr (!RESTRICT) {
+    if constexpr (MODE == kNorm) {
         ra[t] = s;
         rb[t] = mx;
         __syncthreads();
@@ -693,12 +778,12 @@ __global__ void __launch_bounds__(NT) km_stream(Grid g, const u8* __restrict__ f
 
 constexpr int kSJ = 8, kSK = 32, kST = 384;  // km_stream: 340 columns of 10 x 34
 
-template <bool RESTRICT>
-hipError_t stream(const Grid& g, const u8* flags, const double* w, const double* u, const double* src, double* partial,
+template <int MODE, class M>
+hipError_t stream(const Grid& g, const M* flags, const double* w, const double* u, const double* src, double* partial,
                   const float* maskc, const double* wc, double* uc, double* uhat, double* fc, int ti, hipStream_t s)
 {
     const unsigned nb = (unsigned)((g.n / ti) * (g.n / kSJ) * (g.n / kSK));
-    hipLaunchKernelGGL((km_stream<kSJ, kSK, kST, RESTRICT>), dim3(nb), dim3(kST), 0, s, g, flags, w, u, src, partial, maskc,
+    hipLaunchKernelGGL((km_stream<kSJ, kSK, kST, MODE, M>), dim3(nb), dim3(kST), 0, s, g, flags, w, u, src, partial, maskc,
                        wc, uc, uhat, fc, ti);
     return hipGetLastError();
 }
@@ -920,8 +1005,9 @@ hipError_t masked_ngs(const Grid& g, const unsigned char* flags, const double* w
     return ngs_t(g, flags, w, u, src, s);
 }
 
-hipError_t masked_ngs_fused(const Grid& g, const unsigned char* flags, const double* w, const double* uin,
-                            double* uout, const double* src, int ti, hipStream_t s)
+template <class M>
+hipError_t ngs_fused_t(const Grid& g, const M* mask, const double* w, const double* uin, double* uout, const double* src,
+                       int ti, hipStream_t s)
 {
     if (g.n < kMK || g.n > 1024 || uin == uout || ti < 4 || (ti & 3) || ti > g.n || (g.n % ti) != 0)
         return hipErrorInvalidValue;
@@ -931,8 +1017,20 @@ hipError_t masked_ngs_fused(const Grid& g, const unsigned char* flags, const dou
     a.ntj = g.n / TJ;
     a.ntk = g.n / kMK;
     const unsigned nb = (unsigned)((g.n / ti) * a.ntj * a.ntk);
-    hipLaunchKernelGGL((km_ngs_fused<TJ, kMK>), dim3(nb), dim3(TJ * kMK / 2), 0, s, g, flags, w, uin, uout, src, a);
+    hipLaunchKernelGGL((km_ngs_fused<TJ, kMK, M>), dim3(nb), dim3(TJ * kMK / 2), 0, s, g, mask, w, uin, uout, src, a);
     return hipGetLastError();
+}
+
+hipError_t masked_ngs_fused(const Grid& g, const unsigned char* flags, const double* w, const double* uin, double* uout,
+                            const double* src, int ti, hipStream_t s)
+{
+    return ngs_fused_t(g, flags, w, uin, uout, src, ti, s);
+}
+
+hipError_t masked_ngs_fused(const Grid& g, const float* mask, const double* w, const double* uin, double* uout,
+                            const double* src, int ti, hipStream_t s)
+{
+    return ngs_fused_t(g, mask, w, uin, uout, src, ti, s);
 }
 
 template <class M>
@@ -949,7 +1047,8 @@ hipError_t masked_resid_restrict(const Grid& g, const float* mask, const double*
                                  const double* src, const float* maskc, const double* wc, double* uc, double* uhat,
                                  double* fc, hipStream_t s)
 {
-    return resid_restrict_t(g, mask, w, u, src, maskc, wc, uc, uhat, fc, s);
+    if (g.n < kMK) return resid_restrict_t(g, mask, w, u, src, maskc, wc, uc, uhat, fc, s);
+    return stream<kRestrict>(g, mask, w, u, src, nullptr, maskc, wc, uc, uhat, fc, stream_planes(g.n), s);
 }
 
 hipError_t masked_resid_restrict(const Grid& g, const unsigned char* flags, const double* w, const double* u,
@@ -957,12 +1056,15 @@ hipError_t masked_resid_restrict(const Grid& g, const unsigned char* flags, cons
                                  double* fc, hipStream_t s)
 {
     if (g.n < kMK) return resid_restrict_t(g, flags, w, u, src, maskc, wc, uc, uhat, fc, s);
-    return stream<true>(g, flags, w, u, src, nullptr, maskc, wc, uc, uhat, fc, stream_planes(g.n), s);
+    return stream<kRestrict>(g, flags, w, u, src, nullptr, maskc, wc, uc, uhat, fc, stream_planes(g.n), s);
 }
 
 hipError_t masked_fas_rhs(const Grid& gc, const float* maskc, const double* wc, const double* uhat, double* f,
                           hipStream_t s)
 {
+    if (gc.n >= kMK)
+        return stream<kFas>(gc, maskc, wc, uhat, (const double*)nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, f,
+                            stream_planes(gc.n), s);
     hipLaunchKernelGGL(km_fas_rhs, dim3(blocks(cells(gc))), dim3(kB), 0, s, gc, maskc, wc, uhat, f);
     return hipGetLastError();
 }
@@ -1004,7 +1106,7 @@ hipError_t masked_norm(const Grid& g, const unsigned char* flags, const double* 
     const long long nb = (long long)(g.n / ti) * (g.n / kSJ) * (g.n / kSK);
     if (nb > masked_norm_partials(g)) return hipErrorInvalidValue;
     *nparts = (int)nb;
-    return stream<false>(g, flags, w, u, src, partial, nullptr, nullptr, nullptr, nullptr, nullptr, ti, s);
+    return stream<kNorm>(g, flags, w, u, src, partial, nullptr, nullptr, nullptr, nullptr, nullptr, ti, s);
 }
 
 hipError_t masked_coarsest(const Grid& g, const float* mask, const double* w, double* u, const double* f, int cap,

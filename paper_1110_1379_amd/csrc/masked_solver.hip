@@ -3,6 +3,8 @@
 // fixed at the values the caller interpolated from the coarser level.  FAS V-cycles (Sec.
 // V.B.2) over coarse levels whose masks and fixed values are 8-child means, until the rms
 // residual over the active cells is <= opts->tol.
+#include <utility>
+
 #include "host_internal.h"
 
 using namespace mgfr_host;
@@ -21,7 +23,8 @@ int ensure_masked(mgfr_ctx* c, int N, int coarsest)
         if (ok && n < N)
             ok = hipMalloc(&L.mbuf, sizeof(float) * nc) == hipSuccess && hipMalloc(&L.u, sizeof(double) * nc) == hipSuccess &&
                  hipMalloc(&L.uhat, sizeof(double) * nc) == hipSuccess &&
-                 hipMalloc(&L.f, sizeof(double) * nc) == hipSuccess;
+                 hipMalloc(&L.f, sizeof(double) * nc) == hipSuccess &&
+                 (n <= mgfr::fused_sweep_min_n() || hipMalloc(&L.alt, sizeof(double) * nc) == hipSuccess);
         L.mask = L.mbuf;
         c->mlv.push_back(L);
         if (!ok) {
@@ -66,15 +69,26 @@ struct MCycle {
             }
             MGFR_TRY(hip_check(c, hipEventRecord(c->ev[c->ev_used], s), "hipEventRecord"));
         }
-        // a finest level of byte flags (n >= 64): both colours in one pass, out of place
-        // between the caller's u and the context's second buffer (opts->tile = 1: per colour)
-        const bool fused = m == 0 && L.flags && c->malt && o->tile != 1;
+        // the finest level: both colours in one pass, out of place between the caller's u and the
+        // context's second buffer (opts->tile = 1: per colour), from 64^3 up on byte flags and, like
+        // the coarse levels of fractional masks, from 128^3 on a float mask (256^3: 264 us against
+        // 443 for the two colour launches)
+        const bool fused = m == 0 && c->malt && o->tile != 1 && (L.flags || L.g.n > mgfr::fused_sweep_min_n());
         if (fused) {
             double* out = L.u == c->malt ? user_u : c->malt;
             const int ti = o->planes > 0 && o->planes <= L.g.n ? o->planes : mgfr::fused_sweep_planes(L.g.n);
-            MGFR_TRY(hip_check(c, mgfr::masked_ngs_fused(L.g, L.flags, L.w, L.u, out, src(m), ti, s),
-                               "masked_ngs_fused"));
+            if (L.flags)
+                MGFR_TRY(hip_check(c, mgfr::masked_ngs_fused(L.g, L.flags, L.w, L.u, out, src(m), ti, s),
+                                   "masked_ngs_fused"));
+            else
+                MGFR_TRY(hip_check(c, mgfr::masked_ngs_fused(L.g, L.mask, L.w, L.u, out, src(m), ti, s),
+                                   "masked_ngs_fused"));
             L.u = out;
+        } else if (L.alt) {
+            MGFR_TRY(hip_check(c, mgfr::masked_ngs_fused(L.g, L.mask, L.w, L.u, L.alt, src(m),
+                                                         mgfr::fused_sweep_planes(L.g.n), s),
+                               "masked_ngs_fused"));
+            std::swap(L.u, L.alt);
         } else if (L.flags) {
             MGFR_TRY(hip_check(c, mgfr::masked_ngs(L.g, L.flags, L.w, L.u, src(m), s), "masked_ngs"));
         } else {

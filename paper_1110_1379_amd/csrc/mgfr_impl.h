@@ -63,6 +63,9 @@ hipError_t masked_ngs(const Grid& g, const unsigned char* flags, const double* w
 // values, bit for bit, as masked_ngs on the flags.
 hipError_t masked_ngs_fused(const Grid& g, const unsigned char* flags, const double* w, const double* uin,
                             double* uout, const double* src, int ti, hipStream_t s);
+// The same on a float mask (not the bits of masked_ngs, which divides by the mask per neighbour).
+hipError_t masked_ngs_fused(const Grid& g, const float* mask, const double* w, const double* uin, double* uout,
+                            const double* src, int ti, hipStream_t s);
 // Into the level below: uc = uhat = R u and fc = R d at active coarse cells (w, w and 0 at
 // masked ones).
 hipError_t masked_resid_restrict(const Grid& g, const float* mask, const double* w, const double* u,

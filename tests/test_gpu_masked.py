@@ -131,6 +131,31 @@ def test_fractional_mask_matches_oracle(mg, ctx):
     say(f"  cycles {len(hg) - 1}, max err {err:.2e}")
 
 
+@pytest.mark.parametrize("pre,post,planes", [(2, 2, 0), (2, 1, 4), (1, 2, 128)])
+def test_fused_sweep_of_fractional_masks(mg, ctx, pre, post, planes):
+    """From 128^3 up a level of fractional masks is swept both colours in one pass as well (the
+    finest one here, at several plane chunks, and with an odd count of sweeps the field ends in the
+    second buffer): the oracle's field and history, and the per-colour launches' (tile = 1) to
+    the rounding of the last sweeps."""
+    import torch
+    say(f"[masked] fractional fused pre={pre} post={post} planes={planes}")
+    N = 128
+    rho, _, u0, box, fr0 = oct_case(N, 3)
+    rng = np.random.default_rng(4)
+    coarse = rng.integers(-4, 5, size=(N // 4,) * 3) / 4.0
+    mask = np.repeat(np.repeat(np.repeat(coarse, 4, 0), 4, 1), 4, 2)
+    m = O.Model(box_mpc_h=box, fr0_abs=fr0)
+    p = mg.Params(box_mpc_h=box, fr0_abs=fr0)
+    ur, hr, sr = O.solve_masked(rho, mask, m, u0, O.Opts(tol=1e-11, pre=pre, post=post))
+    assert sr == 0, hr
+    for tile in (0, 1):
+        o = mg.mgfr_default_opts(tol=1e-11, pre=pre, post=post, planes=planes, tile=tile)
+        ud, hg, sg = mg.mg_fr_solve_masked(ctx, dev(rho), dev(mask.astype(np.float32), torch.float32), dev(u0), p, o)
+        assert sg == mg.MGFR_OK, ctx.last_error()
+        err = check(ur, hr, ud.cpu().numpy(), hg, mask, u0)
+        say(f"  tile {tile}: cycles {len(hg) - 1}, max err {err:.2e}")
+
+
 def test_all_active_is_the_domain_solve(mg, ctx):
     say("[masked] all active")
     import torch
