@@ -25,7 +25,9 @@ int poisson_fused_min_n();
 hipError_t poisson_ngs_fused(const PGrid& g, const double* xin, double* xout, const double* b, double bmean, int ti,
                              hipStream_t s);
 // Two red-black sweeps from xin into xout in one pass (the same bits as two one-sweep calls),
-// and its planes per workgroup when the options leave them automatic.
+// n >= 64; the smallest level that gains by it, and its planes per workgroup when the options leave
+// them automatic.
+int poisson_fused2_min_n();
 int poisson_fused2_planes(int n);
 hipError_t poisson_ngs_fused2(const PGrid& g, const double* xin, double* xout, const double* b, double bmean, int ti,
                               hipStream_t s);

@@ -33,7 +33,7 @@ int ensure_poisson(mgfr_ctx* c, int N, int coarsest)
     if (c->PN == N && c->Pcoarsest == coarsest) return MGFR_OK;
     (void)hipDeviceSynchronize();
     c->free_poisson();
-    const int fused = mgfr::poisson_fused_min_n();
+    const int fused = mgfr::poisson_fused2_min_n();
     for (int n = N; n >= coarsest; n /= 2) {
         mgfr_ctx::PLevel L;
         L.g = pgrid(n);
@@ -58,8 +58,8 @@ struct PCycle {
     hipStream_t s;
     double mean0;  // mean of the finest source
 
-    // `count` sweeps: one launch, or on levels with the fused kernels as many two-sweep
-    // passes as fit and one single sweep for an odd remainder
+    // `count` sweeps: on levels with a second buffer as many two-sweep passes as fit, and single
+    // sweeps (fused from poisson_fused_min_n() up, one launch per colour below) for the rest
     int sweeps(size_t m, double*& cur, double bm, int count)
     {
         int k = 0;
@@ -84,7 +84,8 @@ struct PCycle {
             }
             MGFR_TRY(hip_check(c, hipEventRecord(c->ev[c->ev_used], s), "hipEventRecord"));
         }
-        if (L.alt) {
+        const bool fused = L.alt && (passes == 2 || L.g.n >= mgfr::poisson_fused_min_n());
+        if (fused) {
             double* out = cur == L.alt ? (m == 0 ? finest_x : L.x) : L.alt;
             const bool opt = m == 0 && o->planes > 0 && o->planes <= L.g.n;
             if (passes == 2) {
@@ -101,7 +102,7 @@ struct PCycle {
         if (timed) {
             MGFR_TRY(hip_check(c, hipEventRecord(c->ev[c->ev_used + 1], s), "hipEventRecord"));
             c->ev_used += 2;
-            c->stats.sweep_launches += L.alt ? 1 : 2;
+            c->stats.sweep_launches += fused ? 1 : 2;
             // read x, b; write x: once per launch, also for a two-sweep pass
             c->stats.sweep_bytes += 24.0 * (double)(1LL << (3 * L.g.lg));
         }

@@ -7,6 +7,8 @@
 // Linear multigrid (Sec. V.A.3, correction scheme): red-black Gauss-Seidel, x_i =
 // (sum_nb x_nb - h^2 b_i) / 6, the residual restricted by 8-child means, the coarse
 // correction prolongated 27/9/3/1 (prolong.hip).  Every level is periodic.
+#include <type_traits>
+
 #include "device_fp64.h"
 
 namespace mgfr {
@@ -229,7 +231,7 @@ __global__ void __launch_bounds__(NT) kp_fused(PGrid g, const double* __restrict
     }
 }
 
-// ---- two fused red-black sweeps per pass (n >= 256), out of place --------------------------
+// ---- two fused red-black sweeps per pass, out of place -------------------------------------
 // Temporal blocking of the sweep above: one pass over the planes applies two complete
 // red-black sweeps, A then B, so x and b come from HBM once for both.  At plane step p:
 //   A red on plane p (tile + 3-cell ring), A black on plane p-1 (tile + 2-cell ring),
@@ -240,13 +242,41 @@ __global__ void __launch_bounds__(NT) kp_fused(PGrid g, const double* __restrict
 // 4-cell in-plane halo; a plane's LDS buffer serves, in turn, as the staged plane, A's red
 // and black planes, then B's red and black planes (five buffers, one barrier per plane).
 // The planes i0-4 .. i0+ti+3 are read and i0 .. i0+ti-1 written.
-template <int TJ, int NT>
-__global__ void __launch_bounds__(NT) kp_fused2(PGrid g, const double* __restrict__ xin, double* __restrict__ xout,
-                                                const double* __restrict__ b, double bmean, int ti, int ntj, int ntk)
+//
+// A thread owns two k-adjacent columns of the tile and its halo.  At step p the one whose cell on
+// plane p is red makes all four updates of the step, the other none, and the roles alternate:
+// every lane updates.  No update of a step reads a cell that the step writes for another column,
+// so the LDS reads run ahead of the updates and the writes come last.  The planes below p+1 are in
+// LDS (a row's even columns before its odd ones, so the lanes' active columns are neighbours); a
+// column keeps its planes p+1 and p+2, the last value of its second sweep and its right-hand
+// sides, each used by A and two steps later by B.  A ring too far out for an update gets a value
+// that nothing valid reads: a cell's validity shrinks by one ring per update, and the tile is
+// written after four.
+// Bound by latency: a step of 14 wavefronts is one barrier, four dependent updates and the wait for
+// the loads of two steps before (VALU busy 20 %, LDS conflicts 7 % of the cycles).  97 VGPRs let one
+// workgroup run on a compute unit; at 64 for a second one it spills (1.06 ms), 8 x 64 and 16 x 32
+// tiles at two or three a unit re-read more halo (1.07 ms), and 32 x 64 with two pairs per thread
+// spills (1.02 ms).  Measured at 512^3: 0.853 ms per pass, 3.8 TB/s of the 3.2 GB it cannot do
+// without; with a slot for every cell of tile and halo, half of them idle in each phase, and
+// six planes of x in registers (157 VGPRs) 1.18 ms.  256^3: 0.112 against 0.154 ms.
+struct Col2 {
+    double xr[2], vr;     // plane q of x in xr[(q - p0) & 1]; the last value of sweep B
+    double bR[2], bK[2];  // right-hand sides of this active step's red and black cell and of the last one's
+    unsigned col;         // byte offset of (j,k) within a plane
+    int c, cu, cl;        // LDS cell staged and cell updated; the latter's k-neighbour below, the one above follows it
+    bool own;             // in the tile
+};
+
+template <int TJ, int TK, int NT>
+__global__ void __launch_bounds__(NT)
+kp_fused2(PGrid g, const double* __restrict__ xin, double* __restrict__ xout, const double* __restrict__ b, double bmean,
+          int ti, int ntj, int ntk)
 {
-    constexpr int H = 4, LJ = TJ + 2 * H, LK = kTK + 2 * H, NL = LJ * LK;
-    constexpr int NS = (NL + NT - 1) / NT;
-    __shared__ double lx[5][NL];
+    constexpr int H = 4, LJ = TJ + 2 * H, LK = TK + 2 * H, HK = LK / 2, NL = LJ * LK, NP = NL / 2;
+    static_assert(NP <= NT, "one column pair per thread");
+    // the cell past a plane's tile is the one of the columns that stage or update none
+    constexpr int NB = NL + 2;
+    __shared__ double lx[5 * NB + LK];
     const int nb = gridDim.x;
     int lid = blockIdx.x;
     if ((nb & 7) == 0) lid = (lid & 7) * (nb >> 3) + (lid >> 3);
@@ -254,146 +284,118 @@ __global__ void __launch_bounds__(NT) kp_fused2(PGrid g, const double* __restric
     lid /= ntk;
     const int tj = lid % ntj;
     const int ci = lid / ntj;
-    const int i0 = ci * ti, j0 = tj * TJ, k0 = tk * kTK;
+    const int i0 = ci * ti, j0 = tj * TJ, k0 = tk * TK;
     const int lg = g.lg, m = g.n - 1;
-    const int last = i0 + ti + H - 1;  // last plane read
+    const int p0 = i0 - H + 1;  // first step
     const double hh = g.hh;
 
-    // per slot: column offset, parity of (j + k), and the rings it is updated on:
-    // 1 loaded, 2 A red (ring <= 3), 4 A black (ring <= 2), 8 B red (ring <= 1), 16 tile
-    unsigned col[NS];
-    int par[NS], fl[NS];
-#pragma unroll
-    for (int s = 0; s < NS; ++s) {
-        const int c = threadIdx.x + s * NT;
-        col[s] = 0;
-        par[s] = 0;
-        fl[s] = 0;
-        if (c < NL) {
-            const int jj = c / LK, kk = c - jj * LK;
-            const int gj = (j0 - H + jj) & m, gk = (k0 - H + kk) & m;
-            col[s] = (unsigned)((gj << lg) | gk);
-            par[s] = (gj + gk) & 1;
-            fl[s] = 1;
-#pragma unroll
-            for (int r = 1; r <= 4; ++r)
-                if (jj >= r && jj <= LJ - 1 - r && kk >= r && kk <= LK - 1 - r) fl[s] |= 1 << r;
-        }
-    }
-    // element offsets fit in 32 bits (n <= 1024)
-    auto offset = [&](int p, int s) -> unsigned { return ((unsigned)(p & m) << (2 * lg)) + col[s]; };
-    auto buf = [&](int p) { return (p - i0 + 2 * H) % 5; };
-
-    // x of planes p-4 .. p+1 in xr[0..5] (plane p+d in xr[d+4]) and the raw load of plane
-    // p+2; the right-hand side (minus its mean, times h^2) of planes p-3 .. p+1 in br[0..4]
-    // (plane p+d in br[d+3]) and the raw load of plane p+2
-    double xr[NS][6], br[NS][5], xn2[NS], bn2[NS];
-    const int p0 = i0 - H + 1;  // first step
-#pragma unroll
-    for (int s = 0; s < NS; ++s) {
-#pragma unroll
-        for (int d = 0; d < 6; ++d) xr[s][d] = 0.0;
-#pragma unroll
-        for (int d = 0; d < 5; ++d) br[s][d] = 0.0;
-        xn2[s] = bn2[s] = 0.0;
-        if (fl[s]) {
-            // step p0 needs planes p0-1 (= i0-4) .. p0+1 and loads p0+2 raw
-            xr[s][3] = xin[offset(p0 - 1, s)];
-            xr[s][4] = xin[offset(p0, s)];
-            xr[s][5] = xin[offset(p0 + 1, s)];
-            br[s][3] = hh * (b[offset(p0, s)] - bmean);
-            br[s][4] = hh * (b[offset(p0 + 1, s)] - bmean);
-            xn2[s] = xin[offset(p0 + 2, s)];
-            bn2[s] = b[offset(p0 + 2, s)];
-            lx[buf(p0)][threadIdx.x + s * NT] = xr[s][4];
-        }
+    // X is the column of a pair with the red cell on plane p0, Y the other
+    Col2 X{}, Y{};
+    // a plane's base is scalar, a column's byte offset fits in 32 bits; planes past the last one read
+    // are loaded, wrapped, and not used
+    // (both opaque: the compiler would keep a 64-bit pointer per column and add to it)
+    using gptr = __attribute__((address_space(1))) char*;
+    auto plane = [&](const double* f, int p) -> gptr {
+        gptr q = (gptr)(f + ((size_t)(p & m) << (2 * lg)));
+        asm("" : "+s"(q));
+        return q;
+    };
+    using gval = __attribute__((address_space(1))) double*;
+    auto place = [&](unsigned o) -> unsigned {
+        asm("" : "+v"(o));
+        return o;
+    };
+    auto at = [&](const double* f, int p, const Col2& q) -> double { return *(gval)(plane(f, p) + place(q.col)); };
+    auto put = [&](int p, const Col2& q, double v) { *(gval)(plane(xout, p) + place(q.col)) = v; };
+    // LDS bases of the planes p+1 .. p-3
+    int u1 = NB, u0 = 0, d1 = 4 * NB, d2 = 3 * NB, d3 = 2 * NB;
+    {
+        const int t = threadIdx.x;
+        const bool on = t < NP;
+        const int jj = on ? t / HK : 0, kk = on ? 2 * (t - jj * HK) : 0;
+        const int gj = (j0 - H + jj) & m, gk = (k0 - H + kk) & m;
+        const int sx = (p0 + gj + gk) & 1;
+        auto setup = [&](Col2& q, int d) {
+            const int k = kk + d;
+            q.col = (unsigned)((gj << lg) | (gk + d)) * sizeof(double);
+            q.c = on ? jj * LK + (k & 1) * HK + (k >> 1) : NL;
+            const int rj = jj < LJ - 1 - jj ? jj : LJ - 1 - jj, rk = k < LK - 1 - k ? k : LK - 1 - k;
+            const int r = on ? (rj < rk ? rj : rk) : 0;
+            q.cu = r >= 1 ? q.c : NL;
+            q.cl = r >= 1 ? jj * LK + ((k & 1) ? k >> 1 : HK + (k >> 1) - 1) : NL;
+            q.own = r >= H;
+            lx[d1 + q.c] = at(xin, p0 - 1, q);
+            lx[u0 + q.c] = at(xin, p0, q);
+            q.xr[1] = at(xin, p0 + 1, q);
+            q.xr[0] = at(xin, p0 + 2, q);
+        };
+        setup(X, sx);
+        setup(Y, 1 - sx);
+        // the first steps need only the red cells' sides: X's on p0, Y's on p0+1
+        X.bR[0] = at(b, p0, X);
+        Y.bR[0] = at(b, p0 + 1, Y);
     }
     __syncthreads();
-    for (int p = p0; p <= i0 + ti + H - 2; ++p) {
-        const bool more3 = p + 3 <= last;
-        double xn3[NS], bn3[NS];
-#pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            xn3[s] = bn3[s] = 0.0;
-            if (more3 && fl[s]) {
-                xn3[s] = xin[offset(p + 3, s)];
-                bn3[s] = b[offset(p + 3, s)];
-            }
+
+    // The slots are compile-time constants (N1: of plane p+1, and of p+3; S: of this active step's
+    // right-hand sides, the other one of the last one's and of the next one's): a copy of a register
+    // whose load is in flight would wait for it.
+    auto step = [&](auto N1c, auto Sc, int p, Col2& A, Col2& B) {
+        constexpr int N1 = decltype(N1c)::value, S = decltype(Sc)::value, T = S ^ 1;
+        struct Nb {
+            double m, jm, jp, km, kp;
+        };
+        // the cell below (plane dm) and the in-plane neighbours (plane d)
+        auto gather = [&](const Col2& q, int dm, int d) -> Nb {
+            return {lx[dm + q.cu], lx[d + q.cu - LK], lx[d + q.cu + LK], lx[d + q.cl], lx[d + q.cl + 1]};
+        };
+        auto relax = [&](const Nb& q, double xm, double xp, double bv) -> double {
+            // hh is a power of two, so the fma rounds as the product and difference do; the
+            // result is rounded before the next update adds it
+#pragma clang fp contract(off)
+            return __builtin_fma(-hh, bv - bmean, xm + xp + q.jm + q.jp + q.km + q.kp) * (1.0 / 6.0);
+        };
+        const Nb q0 = gather(A, d1, u0), q1 = gather(A, d2, d1);
+        const double a0 = relax(q0, q0.m, A.xr[N1], A.bR[S]);  // A red, plane p
+        const Nb q2 = gather(A, d3, d2);
+        const double a1 = relax(q1, q1.m, a0, A.bK[S]);  // A black, plane p-1
+        const Nb q3 = gather(A, d3, d3);
+        const double a2 = relax(q2, q2.m, a1, A.bR[T]);  // B red, plane p-2
+        const double a3 = relax(q3, A.vr, a2, A.bK[T]);  // B black, plane p-3
+        lx[u0 + A.cu] = a0;
+        lx[d1 + A.cu] = a1;
+        lx[d2 + A.cu] = a2;
+        A.vr = a2;
+        // A is active again at step p+2
+        A.bR[T] = at(b, p + 2, A);
+        A.bK[T] = at(b, p + 1, A);
+        // stage plane p+1 and request p+3
+        lx[u1 + A.c] = A.xr[N1];
+        lx[u1 + B.c] = B.xr[N1];
+        A.xr[N1] = at(xin, p + 3, A);
+        B.xr[N1] = at(xin, p + 3, B);
+        if (A.own && (unsigned)(p - 3 - i0) < (unsigned)ti) {  // the tile of plane p-3 is final
+            put(p - 3, A, a3);
+            put(p - 3, B, B.vr);
         }
-        // A red, plane p
-        {
-            double* L = lx[buf(p)];
-#pragma unroll
-            for (int s = 0; s < NS; ++s) {
-                const int c = threadIdx.x + s * NT;
-                if ((fl[s] & 2) && ((p + par[s]) & 1) == 0) {
-                    const double v =
-                        (xr[s][3] + xr[s][5] + L[c - LK] + L[c + LK] + L[c - 1] + L[c + 1] - br[s][3]) * (1.0 / 6.0);
-                    xr[s][4] = v;
-                    L[c] = v;
-                }
-            }
-        }
-        // A black, plane p-1
-        if (p - 1 >= i0 - H + 2) {
-            double* L = lx[buf(p - 1)];
-#pragma unroll
-            for (int s = 0; s < NS; ++s) {
-                const int c = threadIdx.x + s * NT;
-                if ((fl[s] & 4) && ((p - 1 + par[s]) & 1) == 1) {
-                    const double v =
-                        (xr[s][2] + xr[s][4] + L[c - LK] + L[c + LK] + L[c - 1] + L[c + 1] - br[s][2]) * (1.0 / 6.0);
-                    xr[s][3] = v;
-                    L[c] = v;
-                }
-            }
-        }
-        // B red, plane p-2
-        if (p - 2 >= i0 - 1) {
-            double* L = lx[buf(p - 2)];
-#pragma unroll
-            for (int s = 0; s < NS; ++s) {
-                const int c = threadIdx.x + s * NT;
-                if ((fl[s] & 8) && ((p - 2 + par[s]) & 1) == 0) {
-                    const double v =
-                        (xr[s][1] + xr[s][3] + L[c - LK] + L[c + LK] + L[c - 1] + L[c + 1] - br[s][1]) * (1.0 / 6.0);
-                    xr[s][2] = v;
-                    L[c] = v;
-                }
-            }
-        }
-        // B black, plane p-3, and the tile of that plane is final
-        if (p - 3 >= i0) {
-            const double* L = lx[buf(p - 3)];
-#pragma unroll
-            for (int s = 0; s < NS; ++s) {
-                const int c = threadIdx.x + s * NT;
-                if (fl[s] & 16) {
-                    if (((p - 3 + par[s]) & 1) == 1)
-                        xr[s][1] =
-                            (xr[s][0] + xr[s][2] + L[c - LK] + L[c + LK] + L[c - 1] + L[c + 1] - br[s][0]) * (1.0 / 6.0);
-                    xout[offset(p - 3, s)] = xr[s][1];
-                }
-            }
-        }
-        // stage plane p+1; shift the register planes
-        double* LC = lx[buf(p + 1)];
-        const bool more2 = p + 2 <= last;
-#pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            if (fl[s]) LC[threadIdx.x + s * NT] = xr[s][5];
-#pragma unroll
-            for (int d = 0; d < 5; ++d) xr[s][d] = xr[s][d + 1];
-#pragma unroll
-            for (int d = 0; d < 4; ++d) br[s][d] = br[s][d + 1];
-            if (more2 && fl[s]) {
-                xr[s][5] = xn2[s];
-                br[s][4] = hh * (bn2[s] - bmean);
-            }
-            xn2[s] = xn3[s];
-            bn2[s] = bn3[s];
-        }
+        const int f = d3;
+        d3 = d2;
+        d2 = d1;
+        d1 = u0;
+        u0 = u1;
+        u1 = f;
         __syncthreads();
+    };
+    using I0 = std::integral_constant<int, 0>;
+    using I1 = std::integral_constant<int, 1>;
+    const int steps = ti + 2 * H - 2;  // one more for an odd ti
+    for (int p = p0;; p += 4) {
+        step(I1{}, I0{}, p, X, Y);
+        step(I0{}, I0{}, p + 1, Y, X);
+        if (p + 2 >= p0 + steps) break;
+        step(I1{}, I1{}, p + 2, X, Y);
+        step(I0{}, I1{}, p + 3, Y, X);
+        if (p + 4 >= p0 + steps) break;
     }
 }
 
@@ -677,8 +679,11 @@ hipError_t poisson_ngs(const PGrid& g, double* x, const double* b, double bmean,
     return hipGetLastError();
 }
 
-// below 256 a level has too few tiles to fill the chip; the per-colour sweep is used there
+// below 256 a level has too few tiles to fill the chip for a single sweep; the two-sweep pass, whose
+// alternative is four launches, is the faster one wherever its tile fits: 128^3 19 against 42 us,
+// 64^3 10.5 against 16.3 us
 int poisson_fused_min_n() { return 4 * kTK; }
+int poisson_fused2_min_n() { return kTK; }
 
 hipError_t poisson_ngs_fused(const PGrid& g, const double* xin, double* xout, const double* b, double bmean, int ti,
                              hipStream_t s)
@@ -691,18 +696,23 @@ hipError_t poisson_ngs_fused(const PGrid& g, const double* xin, double* xout, co
     return hipGetLastError();
 }
 
-int poisson_fused2_planes(int n) { return n / 4 < 128 ? n / 4 : 128; }
+// One workgroup per compute unit and pass where the level has the tiles for it (n <= 512), and as
+// few of the 6 planes that a chunk computes again as that allows: 512^3 with 512 planes 0.853 ms,
+// with 128 0.916; 256^3 with 64 0.112, with 32 0.120 and with 128 0.176.
+int poisson_fused2_planes(int n)
+{
+    const int ti = (n / 16) * (n / 64) * n / 256;
+    return ti < 2 ? 2 : ti < n ? ti : n;
+}
 
 hipError_t poisson_ngs_fused2(const PGrid& g, const double* xin, double* xout, const double* b, double bmean, int ti,
                               hipStream_t s)
 {
-    // 24 x 72 cells with the halo, 4 slots per thread; 8 x 64 tiles (3 slots of 384 threads)
-    // re-read more halo per pass and ran slower (1.39 against 1.21 ms at 512^3)
-    constexpr int TJ = 16, NT = 512;
-    if (g.n < kTK || g.n > 1024 || xin == xout || ti < 1 || ti > g.n || (g.n % ti) != 0) return hipErrorInvalidValue;
-    const int ntj = g.n / TJ, ntk = g.n / kTK;
+    constexpr int TJ = 16, TK = 64, NT = 896;  // 24 x 72 cells with the halo: 864 column pairs
+    if (g.n < TK || g.n > 1024 || xin == xout || ti < 1 || ti > g.n || (g.n % ti) != 0) return hipErrorInvalidValue;
+    const int ntj = g.n / TJ, ntk = g.n / TK;
     const unsigned nb = (unsigned)((g.n / ti) * ntj * ntk);
-    hipLaunchKernelGGL((kp_fused2<TJ, NT>), dim3(nb), dim3(NT), 0, s, g, xin, xout, b, bmean, ti, ntj, ntk);
+    hipLaunchKernelGGL((kp_fused2<TJ, TK, NT>), dim3(nb), dim3(NT), 0, s, g, xin, xout, b, bmean, ti, ntj, ntk);
     return hipGetLastError();
 }
 

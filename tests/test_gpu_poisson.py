@@ -197,3 +197,21 @@ def test_two_sweep_pass_is_bitwise_two_sweeps(mg, ctx):
         assert not torch.equal(out[1], phi0)
     with pytest.raises(mg.MgfrError):
         mg.mg_poisson_smooth(ctx, rho, u, phi0, params, 3, 2)
+
+
+@pytest.mark.parametrize("N", [128, 256])
+def test_two_sweep_pass_does_not_depend_on_its_plane_chunks(mg, ctx, N):
+    """A chunk of planes recomputes its halo from the same values: the potential has the same bits
+    for every number of planes per workgroup, from the smallest to all."""
+    import torch
+    params = mg.Params(box_mpc_h=float(N), fr0_abs=1e-5)
+    rho = dev(inputs.lognormal(N, 1.5, -1.5, seed=N))
+    u = dev(synthetic_u(O.Model(box_mpc_h=float(N), fr0_abs=1e-5), N, seed=N + 1))
+    ref = None
+    for planes in (0, 4, 8, N // 2, N):
+        opts = mg.mgfr_default_opts(tol=1e-8, max_cycles=100, planes=planes)
+        phi, _, status = mg.mg_poisson_solve(ctx, rho, u, params, opts)
+        assert status == mg.MGFR_OK
+        say(f"[poisson] N={N} planes={planes}")
+        ref = phi if ref is None else ref
+        assert torch.equal(phi, ref)
