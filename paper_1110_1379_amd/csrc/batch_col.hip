@@ -22,6 +22,12 @@ using namespace bdev;
 
 constexpr int kTJ = 16, kTK = 32, kTI = 16;     // tile and plane chunk
 constexpr int kPatchTI = 8;                     // plane chunk of the fused sweep of a patch
+// From this many tiles up a workgroup of the fused sweep takes two plane chunks of a box in a row and
+// that of the second ends at once: half as many of the 4 planes read and 2 computed again per
+// chunk.  4096 tiles are four rounds of the four workgroups to a compute unit, two when halved;
+// below that the last round would be the emptier one.  64 boxes of 64^3 and 16 of 128^3 (6144 tiles):
+// 240 us per sweep, 254 one by one.
+constexpr int kTwiceFrom = 4096;
 constexpr int kAhead = 4;                       // planes whose loads are in flight
 constexpr int kNT = kTJ * kTK / 2;              // one cell of the colour per thread per plane
 constexpr int kLK = kTK + 2, kNL = (kTJ + 2) * kLK;
@@ -524,8 +530,12 @@ __global__ void __launch_bounds__(kNT, 4) kf32_ngs(BTable t, int dir)
     const int k0 = (tile % ntk) * kTK;
     tile /= ntk;
     const int j0 = (tile % ntj) * kTJ;
-    const int ti = PER ? kTI : kPatchTI;
+    int ti = PER ? kTI : kPatchTI;
     const int i0 = (tile / ntj) * ti;
+    if (PER && nb >= kTwiceFrom && g.n >= 2 * kTI) {
+        if (i0 & kTI) return;
+        ti = 2 * kTI;
+    }
     const float* ein = dir ? g.e32b : g.e32;
     float* eout = dir ? g.e32 : g.e32b;
     if (PER)

@@ -77,9 +77,11 @@ struct Res32 {
 // the neighbour parts and M_i sum(du) + B_i sum(de).
 __device__ __forceinline__ Res32 corr_op(const Op32& o, const V32& c, const V32 (&nb)[6], float f)
 {
-    float t1 = 0.0f, t2 = 0.0f, su = 0.0f, se = 0.0f, sB = 0.0f;
+    // the sums start from the first neighbour: an addition of zero is not folded away
+    float su = nb[0].ub - c.ub, se = nb[0].e - c.e, sB = nb[0].B;
+    float t1 = nb[0].M * su, t2 = nb[0].B * se;
 #pragma unroll
-    for (int q = 0; q < 6; ++q) {
+    for (int q = 1; q < 6; ++q) {
         const float du = nb[q].ub - c.ub, de = nb[q].e - c.e;
         t1 = fmaf(nb[q].M, du, t1);
         t2 = fmaf(nb[q].B, de, t2);

@@ -8,11 +8,17 @@
 // pair of k-adjacent tile columns t (TJ x TK tile, TJ TK / 2 threads): at every step it
 // updates one red cell on plane p and one black cell on plane p-1, every one of them part of
 // the result.  The ring of red cells around the tile (recomputed from the same old values by
-// every tile that sees them) and the outer halo (only read) are extra columns E of the first
-// threads: thread t < NR holds ring cell t, which it updates on the planes where that cell is
-// red; the next NH threads hold one halo cell each, which they only stage.  Every updated
+// every tile that sees them) and the outer halo (only read) are extra columns E, one
+// to a thread: a ring cell, which it updates on the planes where that cell is red, or a halo
+// cell, which it only stages.  Every updated
 // cell's (B, M) are formed again from (ub, e) as the per-colour kernel forms them, so both
 // sweeps give the same bits.
+//
+// Bound by its arithmetic (VALU busy 72 % of the cycles, about 235 instructions per wavefront and
+// plane), then by its barriers.  Measured on the domain grid in 16 x 64 tiles, us per sweep: 512^3 653
+// (3.3 TB/s at the 16 B per cell it cannot do without), 256^3 73.5, 128^3 18.4; with the loads of the next
+// planes behind their branch, which waited for them at every plane, a 64-bit address each, and the
+// ring's two parities in the same wavefronts 692, 76.8 and 18.9.
 //
 // On a patch, a position outside the patch next to a cell inside it (across one face) holds
 // that face's boundary value u_b in the ub field of its V32, for the ghost term of the
@@ -44,7 +50,7 @@ struct Col32 {
     float f[4];               // right-hand side, same slots (planes p-1 .. p+1 used)
     float rub[2], re[2], rf[2];  // raw loads of planes p+2 and p+3, plane q in [(q - i0) & 1]
     unsigned col;             // (j,k) offset within a plane
-    int c, cl, fl;            // LDS cell, its k-neighbour below (the one above follows it); 1 loaded, 2 red range
+    int c, cl, fl;            // LDS cell, its k-neighbour below (the one above follows it); 1 staged, 2 red range
 };
 
 // A column of a patch tile: also its position, whether it lies inside the patch, and for a
@@ -107,7 +113,8 @@ __device__ __forceinline__ void sweep_tile(const Op32& o, int n, int lg, int i0,
     constexpr int LK = TK + 4, HK = LK / 2;
     constexpr int NR = 2 * (TK + 2) + 2 * TJ;        // ring around the tile
     constexpr int NH = 2 * (TK + 4) + 2 * (TJ + 2);  // outer halo
-    static_assert(NR + NH <= NT, "one extra column per thread");
+    constexpr int NR2 = NR / 2, R1 = (NR2 + 63) / 64 * 64;  // ring cells of one parity; first thread of the second
+    static_assert(R1 + NR2 <= NT && NR + NH <= NT, "one extra column per thread");
     using Col = typename std::conditional<PATCH, ColP, Col32>::type;
     const int m = n - 1;
     const int last = i0 + ti + 1;  // last plane read
@@ -140,24 +147,37 @@ __device__ __forceinline__ void sweep_tile(const Op32& o, int n, int lg, int i0,
         setup(X, sx);
         setup(Y, 1 - sx);
     }
-    // E: ring cell t or halo cell t - NR, walked around its rectangle (rows first, then the
-    // two side columns)
+    // E: the ring cells in the order of a walk around it, whose parity alternates: even ones to
+    // threads 0 .., odd ones to threads R1 .., so that the wavefronts that update them are full (a
+    // third of them updates nothing otherwise); the halo cells to the threads left over
     int epar = 0;  // parity of (j + k) of E's column
-    if (t < NR + NH) {
-        const bool ring = t < NR;
-        const int r = ring ? t : t - NR;
+    E.col = X.col;  // a thread without one loads its own column again, in vain
+    unsigned efcol = X.col;  // and so does a halo cell, which needs none, for the right-hand side
+    if constexpr (PATCH) {
+        E.j = X.j;
+        E.k = X.k;
+        E.fq = -1;
+        E.in = true;
+    }
+    int w = -1;
+    if (t < NR2) w = 2 * t;
+    else if (t >= R1 && t < R1 + NR2) w = 2 * (t - R1) + 1;
+    const bool ring = w >= 0;
+    if (!ring) w = t < R1 ? t - NR2 : t - 2 * NR2;
+    if (ring || w < NH) {
         const int ra = ring ? TJ + 2 : TJ + 4, rb = ring ? TK + 2 : TK + 4, off = ring ? 1 : 0;
         int ej, ek;
-        if (r < rb) { ej = 0; ek = r; }
-        else if (r < 2 * rb) { ej = ra - 1; ek = r - rb; }
-        else if (r < 2 * rb + ra - 2) { ej = 1 + (r - 2 * rb); ek = 0; }
-        else { ej = 1 + (r - 2 * rb - (ra - 2)); ek = rb - 1; }
+        if (w < rb) { ej = 0; ek = w; }
+        else if (w < rb + ra - 1) { ej = w - rb + 1; ek = rb - 1; }
+        else if (w < 2 * rb + ra - 2) { ej = ra - 1; ek = rb - 2 - (w - (rb + ra - 1)); }
+        else { ej = ra - 2 - (w - (2 * rb + ra - 2)); ek = 0; }
         ej += off;
         ek += off;
         const int gj = (j0 - 2 + ej) & m, gk = (k0 - 2 + ek) & m;
         E.col = (unsigned)((gj << lg) | gk);
         place(E, ej, ek);
         E.fl = ring ? 3 : 1;
+        if (ring) efcol = E.col;
         epar = (gj + gk) & 1;
         if constexpr (PATCH) {
             E.j = j0 - 2 + ej;
@@ -169,6 +189,17 @@ __device__ __forceinline__ void sweep_tile(const Op32& o, int n, int lg, int i0,
             E.fq = (jo != ko) ? (fc << (2 * lg)) + (jo ? E.k : E.j) : -1;
         }
     }
+    // The columns' loads and stores on a plane: a scalar plane pointer and the column's byte offset.
+    // Both are opaque, or the compiler keeps a 64-bit pointer per column and array and adds to it.
+    using gptr = __attribute__((address_space(1))) char*;
+    auto ref = [&](const void* a, int p, unsigned col, auto one) -> auto& {
+        using T = decltype(one);
+        gptr b = (gptr)((const char*)a + ((size_t)(p & m) << (2 * lg)) * sizeof(T));
+        unsigned d = col * (unsigned)sizeof(T);
+        asm("" : "+s"(b));
+        asm("" : "+v"(d));
+        return *(__attribute__((address_space(1))) T*)(b + d);
+    };
     // element offsets fit in 32 bits (n <= 1024)
     auto offset = [&](int p, const Col& q) -> unsigned { return ((unsigned)(p & m) << (2 * lg)) + q.col; };
     auto buf = [&](int p) { return (p - i0 + 3) % 3; };
@@ -190,8 +221,8 @@ __device__ __forceinline__ void sweep_tile(const Op32& o, int n, int lg, int i0,
             rub = *px;
             re = *py;
         } else {
-            rub = ub[offset(p, q)];
-            re = ein[offset(p, q)];
+            rub = ref(ub, p, q.col, 0.0f);
+            re = ref(ein, p, q.col, 0.0f);
         }
     };
     auto make = [&](int p, const Col& q, float rub, float re) -> V32 {
@@ -204,7 +235,6 @@ __device__ __forceinline__ void sweep_tile(const Op32& o, int n, int lg, int i0,
         return make_v(rub, re);
     };
     auto prologue = [&](Col& q) {
-        if (!q.fl) return;
         // planes i0-2, i0-1, i0 in slots 1, 2, 3; plane i0+1 raw in slot 1
         float a, b;
         load_raw(i0 - 2, q, a, b);
@@ -214,13 +244,11 @@ __device__ __forceinline__ void sweep_tile(const Op32& o, int n, int lg, int i0,
         load_raw(i0, q, a, b);
         q.v[3] = make(i0, q, a, b);
         load_raw(i0 + 1, q, q.rub[1], q.re[1]);
-        if (q.fl & 2) {
-            q.f[1] = f[offset(i0 - 2, q)];
-            q.f[2] = f[offset(i0 - 1, q)];
-            q.f[3] = f[offset(i0, q)];
-            q.rf[1] = f[offset(i0 + 1, q)];
-        }
-        lv[buf(i0 - 1)][q.c] = q.v[2];
+        q.f[1] = ref(f, i0 - 2, q.col, 0.0f);
+        q.f[2] = ref(f, i0 - 1, q.col, 0.0f);
+        q.f[3] = ref(f, i0, q.col, 0.0f);
+        q.rf[1] = ref(f, i0 + 1, q.col, 0.0f);
+        if (q.fl) lv[buf(i0 - 1)][q.c] = q.v[2];
     };
     prologue(X);
     prologue(Y);
@@ -249,28 +277,29 @@ __device__ __forceinline__ void sweep_tile(const Op32& o, int n, int lg, int i0,
     };
 
     // One plane step, R = (p - i0 + 1) mod 4 fixed at compile time so that the register planes
-    // rotate by renaming.  A holds the red cell of plane p and the black cell of plane p-1.
-    auto step = [&](auto Rc, int p, Col& A, Col& B) {
+    // rotate by renaming.  A holds the red cell of plane p and the black cell of plane p-1; the
+    // first two steps have none of these in the chunk (BLACK false).  Every thread requests plane
+    // p+3 of every column at every step, the last plane again past it: behind a branch the compiler
+    // cannot count the loads in flight and waits for these, too, where it needs those of the step
+    // before.
+    auto step = [&](auto Rc, auto Bc, int p, Col& A, Col& B) {
         constexpr int R = decltype(Rc)::value;
+        constexpr bool BLACK = decltype(Bc)::value;
         constexpr int M2 = R, M1 = (R + 1) & 3, P0 = (R + 2) & 3, P1 = (R + 3) & 3;
         constexpr int N2 = (R + 1) & 1, N3 = R & 1;  // raw slots of planes p+2, p+3
+        const int p3 = p + 3 < last ? p + 3 : last;
         auto fetch = [&](Col& q) {
-            if (!q.fl) return;
-            load_raw(p + 3, q, q.rub[N3], q.re[N3]);
-            if (q.fl & 2) q.rf[N3] = f[offset(p + 3, q)];
+            load_raw(p3, q, q.rub[N3], q.re[N3]);
+            q.rf[N3] = ref(f, p3, &q == &E ? efcol : q.col, 0.0f);
         };
-        if (p + 3 <= last) {
-            fetch(A);
-            fetch(B);
-            fetch(E);
-        }
+        fetch(A);
+        fetch(B);
+        fetch(E);
         // ADDU: the field of this step's two output cells, loaded before the updates
         double ua = 0.0, ubv = 0.0;
-        if constexpr (ADDU) {
-            if (p - 1 >= i0) {
-                ua = uadd[offset(p - 1, A)];
-                ubv = uadd[offset(p - 1, B)];
-            }
+        if constexpr (ADDU && BLACK) {
+            ua = ref(uadd, p - 1, A.col, 0.0);
+            ubv = ref(uadd, p - 1, B.col, 0.0);
         }
         V32* LA = lv[buf(p)];
         const bool pin = !PATCH || (p >= 0 && p <= m);  // a patch's planes -1 and n are not relaxed
@@ -285,29 +314,27 @@ __device__ __forceinline__ void sweep_tile(const Op32& o, int n, int lg, int i0,
         bool ered = (E.fl & 2) && ((p + epar) & 1) == 0;
         if constexpr (PATCH) ered = ered && pin && E.in;
         if (ered) red(E);
-        if (p - 1 >= i0) {
+        if constexpr (BLACK) {
             const V32* LB = lv[buf(p - 1)];
             const int c = A.c;
             const V32 nbv[6] = {A.v[M2], A.v[P0], LB[c - LK], LB[c + LK], LB[A.cl], LB[A.cl + 1]};
             const Res32 r = op(p - 1, A, A.v[M1], nbv, A.f[M1]);
             A.v[M1].e = A.v[M1].e + newton32(r, o.max_step);
             if constexpr (ADDU) {
-                uadd[offset(p - 1, A)] = ua + (double)A.v[M1].e;
-                uadd[offset(p - 1, B)] = ubv + (double)B.v[M1].e;
+                ref(uadd, p - 1, A.col, 0.0) = ua + (double)A.v[M1].e;
+                ref(uadd, p - 1, B.col, 0.0) = ubv + (double)B.v[M1].e;
             } else {
-                eout[offset(p - 1, A)] = A.v[M1].e;
-                eout[offset(p - 1, B)] = B.v[M1].e;
+                ref(eout, p - 1, A.col, 0.0f) = A.v[M1].e;
+                ref(eout, p - 1, B.col, 0.0f) = B.v[M1].e;
             }
         }
         V32* LC = lv[buf(p + 1)];
-        const bool more2 = p + 2 <= last;
         auto advance = [&](Col& q) {
             if (!q.fl) return;
             LC[q.c] = q.v[P1];
-            if (more2) {  // plane p+2 takes the slot of plane p-2
-                q.v[M2] = make(p + 2, q, q.rub[N2], q.re[N2]);
-                q.f[M2] = q.rf[N2];
-            }
+            // plane p+2 takes the slot of plane p-2
+            q.v[M2] = make(p + 2, q, q.rub[N2], q.re[N2]);
+            q.f[M2] = q.rf[N2];
         };
         advance(A);
         advance(B);
@@ -321,13 +348,13 @@ __device__ __forceinline__ void sweep_tile(const Op32& o, int n, int lg, int i0,
     // ti + 2 steps (ti a multiple of 4): two, then groups of four so that the register
     // planes and the column roles are back in place at the end of every iteration.  X holds
     // the red cells of planes i0-1, i0+1, ...
-    step(I0{}, i0 - 1, X, Y);
-    step(I1{}, i0, Y, X);
+    step(I0{}, std::false_type{}, i0 - 1, X, Y);
+    step(I1{}, std::false_type{}, i0, Y, X);
     for (int p = i0 + 1; p <= i0 + ti; p += 4) {
-        step(I2{}, p, X, Y);
-        step(I3{}, p + 1, Y, X);
-        step(I0{}, p + 2, X, Y);
-        step(I1{}, p + 3, Y, X);
+        step(I2{}, std::true_type{}, p, X, Y);
+        step(I3{}, std::true_type{}, p + 1, Y, X);
+        step(I0{}, std::true_type{}, p + 2, X, Y);
+        step(I1{}, std::true_type{}, p + 3, Y, X);
     }
 }
 

@@ -26,13 +26,14 @@ int planes_for(const mgfr_opts* o, size_t m, int n)
     return mgfr::fused_sweep_planes(n);
 }
 
-// The same for the single-precision sweep.  Measured on 16 x 64 tiles, us per sweep at 8 / 16 /
-// 32 / 64 planes: 128^3 18.4 / 27.3 / 47.5, 256^3 95.6 / 82.4 / 76.8 / 90.3, 512^3 871 / 758 /
-// 697 / 690.
+// The same for the single-precision sweep.  Measured on 16 x 64 tiles, us per sweep: 128^3 with 8
+// planes 18.4 (27 with 16), 256^3 with 16 / 32 / 64 79.7 / 73.5 / 84.2, 512^3 with 64 / 128 / 256 / 512
+// 682 / 661 / 653 / 742: two workgroups of 512 threads to each of 256 compute units, and as few of
+// the 4 planes that a chunk reads beyond its own as that allows.
 int planes_for32(const mgfr_opts* o, size_t m, int n)
 {
     if (m == 0 && o->planes > 0 && o->planes <= n) return o->planes;
-    return n <= 128 ? 8 : n == 256 ? 32 : 64;
+    return n <= 128 ? 8 : n == 256 ? 32 : 256;
 }
 
 // The storage one domain solve works on: the multigrid levels (double precision, and single

@@ -369,3 +369,27 @@ def test_column_sweep_matches_per_cell_sweep(mg, ctx, precision, engine):
         assert np.array_equal(r[0], res[2][0])
         for a, b in zip(r[1], res[2][1]):
             assert np.array_equal(a, b)
+
+
+def test_two_chunk_sweep_of_a_large_batch_matches_per_cell_sweep(mg, ctx):
+    """From 4096 tiles up a workgroup of the fused sweep takes two plane chunks in a row: the same
+    bits as one thread per cell, for boxes of 32 (two chunks), 64 and 128 in one table."""
+    import torch
+    seeds = {32: 1, 64: 4, 128: 2}
+    fields = {N: [dev(inputs.lognormal(N, 1.5, -1.5, seed=70 + N + b)) for b in range(k)] for N, k in seeds.items()}
+    sides = [64] * 64 + [128] * 8 + [32] * 3
+    assert sum((N // 16) * (N // 16) * (N // 32) for N in sides) >= 4096
+    rhos = [fields[N][b % seeds[N]] for b, N in enumerate(sides)]
+    params = [mg.Params(box_mpc_h=float(N), fr0_abs=10.0 ** (-6 + 2 * (b % 7) / 6)) for b, N in enumerate(sides)]
+    ref = None
+    for tile in (1, 0):
+        opts = mg.mgfr_default_opts(tol=1e-8, precision=mg.MGFR_MIXED, tile=tile)
+        us, hists, st = mg.mg_fr_solve_batch(ctx, rhos, params, opts)
+        assert st == mg.MGFR_OK, ctx.last_error()
+        say(f"[large batch] tile={tile}")
+        if ref is None:
+            ref = (us, hists)
+    for a, b in zip(us, ref[0]):
+        assert torch.equal(a, b)
+    for a, b in zip(hists, ref[1]):
+        assert np.array_equal(np.asarray(a), np.asarray(b))
