@@ -54,9 +54,9 @@ struct Edge64 {
 // At 16 x 64: 512 threads, 65 KB of LDS and at most 128 VGPRs, so that two workgroups share a
 // compute unit and one computes while the other waits at its barrier; with the pairs laid over
 // the tile and its halo (704 threads) and four planes of (u, b, f) in registers it was one.
-// Bound by its double-precision arithmetic (about 190 instructions per thread and step, 24 B of
-// traffic per cell).  Measured at 512^3, 128 planes: 0.834 ms per sweep (3.86 TB/s at 24 B per
-// cell), 1.045 ms before; at 256^3 111 against 153 us.
+// Bound by its double-precision arithmetic (24 B of traffic per cell).  Measured at 512^3, 128
+// planes: 0.794 ms per sweep (4.06 TB/s at 24 B per cell); with the loads behind branches and a 64-bit
+// address each 0.835, in the layout before 1.045 ms; at 256^3 106, 111 and 153 us.
 template <int TJ, int TK, int NT>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4)))
 k_ngs_fused(Grid g, const double* __restrict__ uin, double* __restrict__ uout, const double* __restrict__ src,
@@ -67,7 +67,7 @@ k_ngs_fused(Grid g, const double* __restrict__ uin, double* __restrict__ uout, c
     constexpr int NR = 2 * (TK + 2) + 2 * TJ;             // ring around the tile
     constexpr int NH = 2 * (TK + 4) + 2 * (TJ + 2);       // halo around the ring
     constexpr int NR2 = NR / 2, R1 = (NR2 + 63) / 64 * 64;  // ring cells of one parity; first thread of the second
-    static_assert(NP <= NT && R1 + NR2 <= NT && NR + NH <= NT, "one pair and one extra column per thread");
+    static_assert(NP == NT && R1 + NR2 <= NT && NR + NH <= NT, "one pair and one extra column per thread");
     // three plane buffers: plane p-1 (black update), plane p (red update), plane p+1 (staged)
     __shared__ double2 lv[3][NL];
 
@@ -84,7 +84,6 @@ k_ngs_fused(Grid g, const double* __restrict__ uin, double* __restrict__ uout, c
     const int lg = g.lg, m = g.n - 1;
     const int last = i0 + a.ti + 1;  // last plane read
     const int t = threadIdx.x;
-    const bool own = NP == NT || t < NP;
 
     // LDS cell of tile cell (jj, kk), 0 <= jj < LJ, 0 <= kk < LK
     auto cell = [&](int jj, int kk) { return jj * LK + (kk & 1) * HK + (kk >> 1); };
@@ -133,49 +132,57 @@ k_ngs_fused(Grid g, const double* __restrict__ uin, double* __restrict__ uout, c
         epar = (gj + gk) & 1;
     }
 
-    // element offsets fit in 32 bits (n <= 1024)
-    auto offset = [&](int p, unsigned col) -> unsigned { return ((unsigned)(p & m) << (2 * lg)) + col; };
+    // A plane's pointer is scalar and a column's byte offset fits in 32 bits (n <= 1024); both are
+    // opaque, or the compiler keeps a 64-bit pointer per column and array and adds to it.
+    auto ref = [&](const double* f, int p, unsigned col) -> auto& {
+        using gptr = __attribute__((address_space(1))) char*;
+        gptr b = (gptr)(f + ((size_t)(p & m) << (2 * lg)));
+        unsigned d = col * (unsigned)sizeof(double);
+        asm("" : "+s"(b));
+        asm("" : "+v"(d));
+        return *(__attribute__((address_space(1))) double*)(b + d);
+    };
     auto buf = [&](int p) { return (p - i0 + 3) % 3; };
     auto prologue = [&](auto& q) {
         // planes i0-2 and i0-1 to LDS, plane i0 in (u1, b1), plane i0+1 raw
-        const double um2 = uin[offset(i0 - 2, q.col)], um1 = uin[offset(i0 - 1, q.col)];
-        q.u1 = uin[offset(i0, q.col)];
-        q.ru[1] = uin[offset(i0 + 1, q.col)];
+        const double um2 = ref(uin, i0 - 2, q.col), um1 = ref(uin, i0 - 1, q.col);
+        q.u1 = ref(uin, i0, q.col);
+        q.ru[1] = ref(uin, i0 + 1, q.col);
         q.b1 = dev::exp_(q.u1);
         lv[buf(i0 - 2)][q.c] = make_double2(um2, dev::exp_(um2));
         lv[buf(i0 - 1)][q.c] = make_double2(um1, dev::exp_(um1));
     };
-    if (own) {
-        X.fr = src[offset(i0 - 1, X.col)];
-        Y.fr = src[offset(i0, Y.col)];
-        prologue(X);
-        prologue(Y);
-    }
+    X.fr = ref(src, i0 - 1, X.col);
+    Y.fr = ref(src, i0, Y.col);
+    prologue(X);
+    prologue(Y);
     if (E.on) {
-        if (E.ring) E.fr = src[offset(((i0 - 1 + epar) & 1) ? i0 : i0 - 1, E.col)];
+        // the right-hand side of the plane on which the cell is red first
+        const double f0 = ref(src, i0 - 1, E.col), f1 = ref(src, i0, E.col);
+        E.fr = ((i0 - 1 + epar) & 1) ? f1 : f0;
         prologue(E);
     }
     __syncthreads();
 
     const double ms = g.max_step;
     // One plane step.  N2 = (p - i0) & 1 is fixed at compile time (the raw slots rotate by
-    // renaming).  A holds the red cell of plane p and the black cell of plane p-1; l = p - i0
-    // mod 3 selects the buffers.
-    auto step = [&](auto N2c, int p, Col64& A, Col64& B, int am, int ap) {
+    // renaming).  A holds the red cell of plane p and the black cell of plane p-1, which the first
+    // two steps do not have in the chunk (BLACK false).  The loads stand behind no branch, those
+    // past the chunk's last plane read that one again: where the compiler cannot count the loads in
+    // flight it waits for all of them.
+    auto step = [&](auto N2c, auto Bc, int p, Col64& A, Col64& B, int am, int ap) {
         constexpr int N2 = decltype(N2c)::value, N3 = N2 ^ 1;  // raw slots of planes p+2, p+3
+        constexpr bool BLACK = decltype(Bc)::value;
         double2* L0 = lv[buf(p)];
         const double2* Lm = lv[buf(p - 1)];
         double2* L1 = lv[buf(p + 1)];
         // the loads of plane p+3, two steps ahead of their use
-        if (p + 3 <= last) {
-            if (own) {
-                A.ru[N3] = uin[offset(p + 3, A.col)];
-                B.ru[N3] = uin[offset(p + 3, B.col)];
-            }
-            if (E.on) E.ru[N3] = uin[offset(p + 3, E.col)];
-        }
-        const bool moref = p + 2 <= i0 + a.ti;
-        if (own) {
+        const int p3 = p + 3 < last ? p + 3 : last;
+        A.ru[N3] = ref(uin, p3, A.col);
+        B.ru[N3] = ref(uin, p3, B.col);
+        E.ru[N3] = ref(uin, p3, E.col);
+        const int pf = p + 2 < last ? p + 2 : last - 1;
+        {
             const int c = A.c;
             // red cell of plane p; its black neighbours are all old
             const double2 m1 = Lm[c], p0 = L0[c];
@@ -191,21 +198,19 @@ k_ngs_fused(Grid g, const double* __restrict__ uin, double* __restrict__ uout, c
             }
             // black cell of plane p-1; its red neighbours are all new.  Plane p-1 is then final
             // in both columns.
-            if (p - 1 >= i0) {
+            if constexpr (BLACK) {
                 const double2 jm = Lm[c - LK], jp = Lm[c + LK], km = Lm[am], kp = Lm[ap];
                 const double un[6] = {A.vr, v, jm.x, jp.x, km.x, kp.x};
                 const double bn[6] = {A.br, bv, jm.y, jp.y, km.y, kp.y};
                 const OpVal r = dev::cell_op_b(g, m1.x, m1.y, un, bn, dev::rhs_value(g, A.fb));
-                uout[offset(p - 1, A.col)] = m1.x + dev::bounded(-r.L / r.dL, ms);
-                uout[offset(p - 1, B.col)] = B.vr;
+                ref(uout, p - 1, A.col) = m1.x + dev::bounded(-r.L / r.dL, ms);
+                ref(uout, p - 1, B.col) = B.vr;
             }
             A.vr = v;
             A.br = bv;
             // A is active again at step p+2
-            if (moref) {
-                A.fr = src[offset(p + 2, A.col)];
-                A.fb = src[offset(p + 1, A.col)];
-            }
+            A.fr = ref(src, pf, A.col);
+            A.fb = ref(src, p + 1, A.col);
         }
         if (E.ring && ((p + epar) & 1) == 0) {
             const int c = E.c;
@@ -215,21 +220,16 @@ k_ngs_fused(Grid g, const double* __restrict__ uin, double* __restrict__ uout, c
             const OpVal r = dev::cell_op_b(g, p0.x, p0.y, un, bn, dev::rhs_value(g, E.fr));
             const double v = p0.x + dev::bounded(-r.L / r.dL, ms);
             L0[c] = make_double2(v, dev::exp_(v));
-            if (moref) E.fr = src[offset(p + 2, E.col)];
+            E.fr = ref(src, pf, E.col);
         }
         // stage plane p+1 for the next step; plane p+2 follows in the registers
-        const bool more2 = p + 2 <= last;
         auto advance = [&](auto& q) {
             L1[q.c] = make_double2(q.u1, q.b1);
-            if (more2) {
-                q.u1 = q.ru[N2];
-                q.b1 = dev::exp_(q.u1);
-            }
+            q.u1 = q.ru[N2];
+            q.b1 = dev::exp_(q.u1);
         };
-        if (own) {
-            advance(A);
-            advance(B);
-        }
+        advance(A);
+        advance(B);
         if (E.on) advance(E);
         __syncthreads();
     };
@@ -237,9 +237,11 @@ k_ngs_fused(Grid g, const double* __restrict__ uin, double* __restrict__ uout, c
     using I1 = std::integral_constant<int, 1>;
     // a.ti + 2 steps (a.ti even), two by two so that the column roles and the raw slots are
     // back in place at the end of every iteration
-    for (int p = i0 - 1; p <= i0 + a.ti; p += 2) {
-        step(I1{}, p, X, Y, xm, xp);
-        step(I0{}, p + 1, Y, X, ym, yp);
+    step(I1{}, std::false_type{}, i0 - 1, X, Y, xm, xp);
+    step(I0{}, std::false_type{}, i0, Y, X, ym, yp);
+    for (int p = i0 + 1; p <= i0 + a.ti; p += 2) {
+        step(I1{}, std::true_type{}, p, X, Y, xm, xp);
+        step(I0{}, std::true_type{}, p + 1, Y, X, ym, yp);
     }
 }
 
@@ -263,8 +265,8 @@ int fused_sweep_planes(int n)
 {
     // Planes per workgroup: long enough to amortise the 4 planes a chunk reads beyond its own,
     // short enough to fill the chip (two workgroups of 512 threads to each of 256 compute
-    // units).  Measured, us per sweep at 8 / 16 / 32 / 64 / 128 planes: 128^3 20.5 / 30.9 / 55.5,
-    // 256^3 132.8 / 121.2 / 111.4 / 129.1, 512^3 1047 / 925 / 866 / 839 / 834.
+    // units).  Measured, us per sweep: 128^3 with 4 / 8 / 16 planes 23.0 / 21.4 / 30.3, 256^3 with 16 /
+    // 32 / 64 115 / 106 / 110, 512^3 with 64 / 128 / 256 / 512 801 / 792 / 801 / 827.
     return n <= 128 ? 8 : n == 256 ? 32 : 128;
 }
 
