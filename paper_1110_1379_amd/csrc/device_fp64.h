@@ -65,9 +65,10 @@ __device__ __forceinline__ double curvature(const Grid& g, double ui, double bi)
 __device__ __forceinline__ OpVal cell_op_b(const Grid& g, double ui, double bi, const double (&un)[6],
                                            const double (&bn)[6], double f)
 {
-    double su = 0.0, sb = 0.0, sbu = 0.0;
+    // the sums start from the first neighbour: an addition of zero is not folded away
+    double su = un[0] - ui, sb = bn[0], sbu = bn[0] * su;
 #pragma unroll
-    for (int q = 0; q < 6; ++q) {
+    for (int q = 1; q < 6; ++q) {
         const double du = un[q] - ui;
         su += du;
         sb += bn[q];

@@ -227,9 +227,10 @@ __device__ __forceinline__ OpVal cell64(const Op64& o, const double2* v, const d
     const double S_ = curvature(o, c.x, c.y);
     OpVal r;
     if constexpr (PER) {
-        double su = 0.0, sb = 0.0, sbu = 0.0;
+        const double2 n0 = v[n[0]];
+        double su = n0.x - c.x, sb = n0.y, sbu = n0.y * su;
 #pragma unroll
-        for (int x = 0; x < 6; ++x) {
+        for (int x = 1; x < 6; ++x) {
             const double2 nb = v[n[x]];
             const double du = nb.x - c.x;
             su += du;
