@@ -277,9 +277,9 @@ __global__ void __launch_bounds__(kB) km_ngs_colour(Grid g, const M* __restrict_
 // the operands of the two-colour sweep in the same order.  A float mask (the coarse levels') is
 // staged beside (u, b).
 // Bound by its double-precision arithmetic, the ghosts' on top of the domain sweep's.  Measured at
-// 512^3 with 61% of the cells active: 1.32 ms per sweep; with the column pairs laid over tile and
-// halo (704 threads) and an exponential and a branch per masked neighbour 2.19 ms.  Float mask at
-// 256^3: 264 us, the two colour launches 443 us.
+// 512^3 with 61% of the cells active: 1.26 ms per sweep; with the loads behind branches and a 64-bit
+// address each 1.31, with the column pairs laid over tile and halo (704 threads) and an exponential and
+// a branch per masked neighbour 2.19 ms.  Float mask at 256^3: 272 us, the two colour launches 443 us.
 constexpr int kMK = 64;  // tile width along k
 
 // A flag byte or a mask value: whether the cell is active, and whether its update needs w.
@@ -289,6 +289,21 @@ __device__ __forceinline__ bool needs_w(int fl) { return fl & 2; }
 __device__ __forceinline__ bool needs_w(float m) { return m > 0.0f; }
 template <class M>
 using MaskVal = typename std::conditional<std::is_same<M, float>::value, float, int>::type;
+
+// A column's value on a plane: a scalar plane pointer and the column's byte offset, which fits in 32
+// bits (n <= 1024); both are opaque, or the compiler keeps a 64-bit pointer per column and array and
+// adds to it.
+template <class T>
+__device__ __forceinline__ auto plane_ref(T* f, int lg, int p, unsigned col) -> auto&
+{
+    using U = std::remove_const_t<T>;
+    using gptr = __attribute__((address_space(1))) char*;
+    gptr b = (gptr)(f + ((size_t)p << (2 * lg)));
+    unsigned d = col * (unsigned)sizeof(U);
+    asm("" : "+s"(b));
+    asm("" : "+v"(d));
+    return *(__attribute__((address_space(1))) U*)(b + d);
+}
 
 template <class V>
 struct ColM {
@@ -368,20 +383,30 @@ km_ngs_fused(Grid g, const M* __restrict__ flags, const double* __restrict__ w, 
         epar = (gj + gk) & 1;
     }
 
-    auto offset = [&](int p, const Col& q) -> unsigned { return ((unsigned)(p & m) << (2 * lg)) + q.col; };
+    auto ref = [&](auto* f, int p, unsigned col) -> auto& { return plane_ref(f, lg, p & m, col); };
     auto buf = [&](int p) { return (p - i0 + 3) % 3; };
-    // the density and w of a cell of flag byte fl on plane p, where an update needs them
+    // the density and w of a cell of flag byte fl on plane p, where an update needs them, else the
+    // tile's corner's: no load stands behind a branch (but for a float mask, whose registers
+    // would spill: 287 us instead of 272 at 256^3)
+    const unsigned corner = (unsigned)((j0 << lg) | k0);
     auto fetch = [&](int p, const Col& q, V fl, double& fv, double& wv) {
-        if (is_active(fl)) fv = src[offset(p, q)];
-        if (needs_w(fl)) wv = w[offset(p, q)];
+        if constexpr (FM) {
+            if (is_active(fl)) {
+                fv = ref(src, p, q.col);
+                wv = ref(w, p, q.col);
+            }
+            return;
+        }
+        fv = ref(src, p, is_active(fl) ? q.col : corner);
+        wv = ref(w, p, needs_w(fl) ? q.col : corner);
     };
     auto prologue = [&](Col& q) {
-        const double um2 = uin[offset(i0 - 2, q)], um1 = uin[offset(i0 - 1, q)];
-        const V fm2 = flags[offset(i0 - 2, q)], fm1 = flags[offset(i0 - 1, q)];
-        q.u1 = uin[offset(i0, q)];
-        q.m1 = flags[offset(i0, q)];
-        q.ru[1] = uin[offset(i0 + 1, q)];
-        q.rm[1] = flags[offset(i0 + 1, q)];
+        const double um2 = ref(uin, i0 - 2, q.col), um1 = ref(uin, i0 - 1, q.col);
+        const V fm2 = ref(flags, i0 - 2, q.col), fm1 = ref(flags, i0 - 1, q.col);
+        q.u1 = ref(uin, i0, q.col);
+        q.m1 = ref(flags, i0, q.col);
+        q.ru[1] = ref(uin, i0 + 1, q.col);
+        q.rm[1] = ref(flags, i0 + 1, q.col);
         q.b1 = signed_b(q.u1, is_active(q.m1));
         lv[buf(i0 - 2)][q.c] = make_double2(um2, signed_b(um2, is_active(fm2)));
         lv[buf(i0 - 1)][q.c] = make_double2(um1, signed_b(um1, is_active(fm1)));
@@ -399,29 +424,37 @@ km_ngs_fused(Grid g, const M* __restrict__ flags, const double* __restrict__ w, 
         if (eon) {
             const V fe = prologue(E);
             if (ering) {
-                if ((i0 - 1 + epar) & 1) fetch(i0, E, E.m1, E.fr, E.wr);
-                else fetch(i0 - 1, E, fe, E.fr, E.wr);
+                // of the plane on which the cell is red first
+                double f1, w1;
+                fetch(i0 - 1, E, fe, E.fr, E.wr);
+                fetch(i0, E, E.m1, f1, w1);
+                if ((i0 - 1 + epar) & 1) {
+                    E.fr = f1;
+                    E.wr = w1;
+                }
             }
         }
     }
     __syncthreads();
 
     const double ms = g.max_step;
-    auto step = [&](auto N2c, int p, Col& A, Col& B) {
+    // BLACK: the step has a black cell in the chunk (the first two do not)
+    auto step = [&](auto N2c, auto Bc, int p, Col& A, Col& B) {
         constexpr int N2 = decltype(N2c)::value, N3 = N2 ^ 1;
+        constexpr bool BLACK = decltype(Bc)::value;
         double2* L0 = lv[buf(p)];
         const double2* Lm = lv[buf(p - 1)];
         double2* L1 = lv[buf(p + 1)];
         auto Lf = [&](int pp) -> float* { return lm[FM ? buf(pp) : 0]; };
+        // past the last plane that one again
+        const int p3 = p + 3 < last ? p + 3 : last;
         auto load = [&](Col& q) {
-            q.ru[N3] = uin[offset(p + 3, q)];
-            q.rm[N3] = flags[offset(p + 3, q)];
+            q.ru[N3] = ref(uin, p3, q.col);
+            q.rm[N3] = ref(flags, p3, q.col);
         };
-        if (p + 3 <= last) {
-            load(A);
-            load(B);
-            if (eon) load(E);
-        }
+        load(A);
+        load(B);
+        load(E);
         // the operator at the cell of column q on plane pp (its mask from LDS; below and above: the
         // masks of its i-neighbours)
         auto op = [&](const Col& q, int pp, const double (&un)[6], const double (&bn)[6], float below, V above,
@@ -453,7 +486,7 @@ km_ngs_fused(Grid g, const M* __restrict__ flags, const double* __restrict__ w, 
                 L0[c] = v;
             }
             // black cell of plane p-1, if active; plane p-1 is then final in both columns
-            if (p - 1 >= i0) {
+            if constexpr (BLACK) {
                 double un1 = m1.x;
                 if (!masked_b(m1.y)) {
                     const double2 jm = Lm[c - LK], jp = Lm[c + LK], km = Lm[A.cl], kp = Lm[A.cl + 1];
@@ -462,8 +495,8 @@ km_ngs_fused(Grid g, const M* __restrict__ flags, const double* __restrict__ w, 
                     const OpVal r = op(A, p - 1, un, bn, (float)A.mr, FM ? (V)Lf(p)[FM ? c : 0] : V(0), m1, A.fb, A.wb);
                     un1 = m1.x + bounded(-r.L / r.dL, ms);
                 }
-                uout[offset(p - 1, A)] = un1;
-                uout[offset(p - 1, B)] = B.vr;
+                ref(uout, p - 1, A.col) = un1;
+                ref(uout, p - 1, B.col) = B.vr;
             }
             A.vr = v.x;
             A.br = v.y;
@@ -476,32 +509,30 @@ km_ngs_fused(Grid g, const M* __restrict__ flags, const double* __restrict__ w, 
         }
         // stage plane p+1; plane p+2 follows in the registers, and with its flags known the
         // right-hand sides and fixed values of A's next active step (p+2) are loaded
-        const bool more2 = p + 2 <= last;
         const V mA = A.m1;
         auto advance = [&](Col& q) {
             L1[q.c] = make_double2(q.u1, q.b1);
             if constexpr (FM) Lf(p + 1)[q.c] = q.m1;
-            if (more2) {
-                q.u1 = q.ru[N2];
-                q.m1 = q.rm[N2];
-                q.b1 = signed_b(q.u1, is_active(q.m1));
-            }
+            q.u1 = q.ru[N2];
+            q.m1 = q.rm[N2];
+            q.b1 = signed_b(q.u1, is_active(q.m1));
         };
         advance(A);
         advance(B);
         if (eon) advance(E);
-        if (p + 2 <= i0 + a.ti) {
-            fetch(p + 2, A, A.m1, A.fr, A.wr);
-            fetch(p + 1, A, mA, A.fb, A.wb);
-            if (ered) fetch(p + 2, E, E.m1, E.fr, E.wr);
-        }
+        const int pf = p + 2 < last ? p + 2 : last - 1;
+        fetch(pf, A, A.m1, A.fr, A.wr);
+        fetch(p + 1, A, mA, A.fb, A.wb);
+        if (ered) fetch(pf, E, E.m1, E.fr, E.wr);
         __syncthreads();
     };
     using I0 = std::integral_constant<int, 0>;
     using I1 = std::integral_constant<int, 1>;
-    for (int p = i0 - 1; p <= i0 + a.ti; p += 2) {
-        step(I1{}, p, X, Y);
-        step(I0{}, p + 1, Y, X);
+    step(I1{}, std::false_type{}, i0 - 1, X, Y);
+    step(I0{}, std::false_type{}, i0, Y, X);
+    for (int p = i0 + 1; p <= i0 + a.ti; p += 2) {
+        step(I1{}, std::true_type{}, p, X, Y);
+        step(I0{}, std::true_type{}, p + 1, Y, X);
     }
 }
 
@@ -605,34 +636,56 @@ __global__ void __launch_bounds__(kB) km_norm(Grid g, const M* __restrict__ mask
     }
 }
 
-// A level read as byte flags (n >= 64), streamed: a workgroup owns a tile of TJ x TK columns and
-// a chunk of ti planes (even); per plane it stages (u, signed b) of the tile and a one-cell ring in
-// LDS, keeps the i-neighbours in registers and has the next two planes in flight, so each value
-// and exponential is fetched and formed once.  One column per thread.  RESTRICT: R u of all 8
-// children and R d of the active ones into active coarse cells; masked coarse cells take their
-// fixed value and a zero right-hand side.  FAS: f = L(u) - f at active cells (fc holds f).  NORM: the
-// partial (sum d^2, max |d|) of the workgroup, summed in a fixed order.
-// Bound by its arithmetic and the barrier of each plane: the small tile puts three workgroups on
-// a compute unit.  Measured at 512^3, 61% active: norm 1.25 ms (8 x 64 tiles, 704 threads, two
-// barriers a plane: 1.69), restriction 1.67 ms (one thread per coarse cell: 2.2);
-// float masks at 256^3: restriction 286 us (360 - 565), FAS right-hand side of 256^3 243 us (310 - 380).
+// A level of byte flags or of a float mask (n >= 64), streamed: a workgroup owns a tile of TJ x TK
+// columns and a chunk of ti planes (even); per plane it stages (u, signed b) of the tile and a
+// one-cell ring in LDS (a float mask's values too), keeps the i-neighbours in registers and has the
+// next two planes in flight, so each value and exponential is fetched and formed once.  RESTRICT:
+// R u of all 8 children and R d of the active ones into active coarse cells; masked coarse cells take
+// their fixed value and a zero right-hand side.  FAS: f = L(u) - f at active cells (fc holds f).
+// NORM: the partial (sum d^2, max |d|) of the workgroup, summed in a fixed order.
+// The columns lie as in the domain's residual (resid_fp64.hip: two of a thread, neighbours in j, a
+// coarse cell's eight children in two lanes; the ring is an extra column of the first threads), and
+// no load stands behind a branch: a cell that needs no density or w reads that of the tile's
+// corner instead.
+// Bound by its arithmetic.  Measured at 512^3, 61% active: norm 0.72 ms, restriction 0.80 ms; one
+// column per thread of 8 x 32 tiles (384 threads, loads behind branches, restriction through LDS)
+// 1.25 and 1.67.  Float masks at 256^3: restriction 170 us (286), FAS right-hand side 168 us (243).
 // What km_stream does with d = L(u) - f.
 enum { kNorm, kRestrict, kFas };
 
+template <class V>
+struct ColS {
+    double um, u0, up, bm, b0, bp;  // planes p-1, p, p+1
+    double ru[2];                   // plane q, raw, in [(q - i0) & 1]
+    double f[2], w[2];              // density (FAS: f) and w, same slots
+    double uq, dq;                  // of the plane before, for the restriction
+    V mm, m0, mp, rm[2];
+    unsigned col;                   // (j,k) offset within a plane
+    int c;                          // LDS cell
+};
+
+// the value of the lane whose k differs in its last bit
+__device__ __forceinline__ double k_pair(double v)
+{
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0xb1, 0xf, 0xf, true);  // quad_perm [1,0,3,2]
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0xb1, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+
 template <int TJ, int TK, int NT, int MODE, class M>
-__global__ void __launch_bounds__(NT) km_stream(Grid g, const M* __restrict__ flags, const double* __restrict__ w,
-                                                const double* __restrict__ u, const double* __restrict__ src,
-                                                double* __restrict__ partial, const float* __restrict__ maskc,
-                                                const double* __restrict__ wc, double* __restrict__ uc,
-                                                double* __restrict__ uhat, double* __restrict__ fc, int ti)
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4)))
+km_stream(Grid g, const M* __restrict__ flags, const double* __restrict__ w, const double* __restrict__ u,
+          const double* __restrict__ src, double* __restrict__ partial, const float* __restrict__ maskc,
+          const double* __restrict__ wc, double* __restrict__ uc, double* __restrict__ uhat, double* __restrict__ fc,
+          int ti)
 {
     using V = MaskVal<M>;
-    constexpr bool FM = std::is_same<M, float>::value, RESTRICT = MODE == kRestrict;
-    constexpr int LJ = TJ + 2, LK = TK + 2, NL = LJ * LK;
-    static_assert(NL <= NT && TJ * TK / 4 <= NT, "one column per thread");
+    using Col = ColS<V>;
+    constexpr bool FM = std::is_same<M, float>::value;
+    constexpr int LJ = TJ + 2, LK = TK + 2, NL = LJ * LK, NH = 2 * LK + 2 * TJ;
+    static_assert(NT == TJ * TK / 2 && NH <= NT, "two columns and one ring cell per thread");
     __shared__ double2 lv[2][NL];
     __shared__ float lm[FM ? 2 : 1][FM ? NL : 1];
-    __shared__ double ra[MODE == kRestrict ? TJ * TK : NT], rb[MODE == kRestrict ? TJ * TK : NT];
     const int ntk = g.n / TK, ntj = g.n / TJ;
     const int nb = gridDim.x;
     int lid = blockIdx.x;
@@ -642,127 +695,158 @@ __global__ void __launch_bounds__(NT) km_stream(Grid g, const M* __restrict__ fl
     const int tj = lid % ntj;
     const int i0 = (lid / ntj) * ti, j0 = tj * TJ, k0 = tk * TK;
     const int lg = g.lg, m = g.n - 1;
+    const int last = i0 + ti;  // last plane read
     const int t = threadIdx.x;
-    const bool on = t < NL;
-    const int jj = on ? t / LK : 0, kk = on ? t - jj * LK : 0;
-    const bool in = on && jj >= 1 && jj <= TJ && kk >= 1 && kk <= TK;
-    const unsigned col = (unsigned)((((j0 - 1 + jj) & m) << lg) | ((k0 - 1 + kk) & m));
-    auto off = [&](int p) -> unsigned { return ((unsigned)(p & m) << (2 * lg)) + col; };
-    double um = 0.0, uv = 0.0, up = 0.0, bm = 0.0, bv = 0.0, bp = 0.0, f0 = 0.0, w0 = 0.0, ru = 0.0;
-    double usum = 0.0, dsum = 0.0;
-    V mm = 0, mv = 0, fp = 0, rm = 0;
-    if (on) {
-        um = u[off(i0 - 1)];
-        uv = u[off(i0)];
-        up = u[off(i0 + 1)];
-        ru = u[off(i0 + 2)];
-        mm = flags[off(i0 - 1)];
-        mv = flags[off(i0)];
-        fp = flags[off(i0 + 1)];
-        rm = flags[off(i0 + 2)];
-        if (in && MODE != kFas && is_active(mv)) f0 = src[off(i0)];
-        if (in && MODE == kFas && is_active(mv)) f0 = fc[off(i0)];
-        if (in && needs_w(mv)) w0 = w[off(i0)];
-        bm = signed_b(um, is_active(mm));
-        bv = signed_b(uv, is_active(mv));
-        bp = signed_b(up, is_active(fp));
-        lv[0][t] = make_double2(uv, bv);
-        if constexpr (FM) lm[0][t] = mv;
+
+    auto ref = [&](auto* f, int p, unsigned col) -> auto& { return plane_ref(f, lg, p & m, col); };
+    auto request = [&](Col& q, int N, int p) {
+        q.ru[N] = ref(u, p, q.col);
+        q.rm[N] = ref(flags, p, q.col);
+    };
+    // density (FAS: f) and w of plane p, of mask mp
+    const unsigned corner = (unsigned)((j0 << lg) | k0);
+    auto request_f = [&](Col& q, int N, int p, V mp) {
+        q.f[N] = ref(MODE == kFas ? fc : src, p, is_active(mp) ? q.col : corner);
+        q.w[N] = ref(w, p, needs_w(mp) ? q.col : corner);
+    };
+
+    Col X{}, Y{}, E{};
+    const bool ring = t < NH;
+    {
+        auto setup = [&](Col& q, int j, int k) {
+            q.col = (unsigned)((((j0 - 1 + j) & m) << lg) | ((k0 - 1 + k) & m));
+            q.c = j * LK + k;
+        };
+        const int r = t - 2 * LK;
+        setup(X, 1 + 2 * (t / TK), 1 + t % TK);
+        setup(Y, 2 + 2 * (t / TK), 1 + t % TK);
+        if (t < LK) setup(E, 0, t);
+        else if (t < 2 * LK) setup(E, LJ - 1, t - LK);
+        else if (ring) setup(E, 1 + (r >> 1), (r & 1) * (LK - 1));
+        else E.col = X.col;  // loads its own column again, in vain
     }
+    auto prologue = [&](Col& q) {
+        q.um = ref(u, i0 - 1, q.col);
+        q.u0 = ref(u, i0, q.col);
+        q.up = ref(u, i0 + 1, q.col);
+        q.mm = ref(flags, i0 - 1, q.col);
+        q.m0 = ref(flags, i0, q.col);
+        q.mp = ref(flags, i0 + 1, q.col);
+        request(q, 0, i0 + 2);
+    };
+    auto staged = [&](Col& q) {
+        q.b0 = signed_b(q.u0, is_active(q.m0));
+        q.bp = signed_b(q.up, is_active(q.mp));
+        lv[0][q.c] = make_double2(q.u0, q.b0);
+        if constexpr (FM) lm[0][q.c] = q.m0;
+    };
+    prologue(X);
+    prologue(Y);
+    prologue(E);
+    request_f(X, 0, i0, X.m0);
+    request_f(Y, 0, i0, Y.m0);
+    X.bm = signed_b(X.um, is_active(X.mm));
+    Y.bm = signed_b(Y.um, is_active(Y.mm));
+    staged(X);
+    staged(Y);
+    if (ring) staged(E);
     __syncthreads();
-    double s = 0.0, mx = 0.0;
-    for (int p = i0; p < i0 + ti; ++p) {
-        // loads: u and flag of plane p+3, density and w of plane p+1
-        double ru3 = 0.0, f1 = 0.0, w1 = 0.0;
-        V rm3 = 0;
-        if (on && p + 3 <= i0 + ti) {
-            ru3 = u[off(p + 3)];
-            rm3 = flags[off(p + 3)];
+
+    double s = 0.0, mx = 0.0, cw = 0.0;
+    float cm = 0.0f;
+    // One plane, N = (p - i0) & 1 fixed at compile time: the slots of the loads in flight rotate by
+    // renaming (a copy would wait for them).
+    auto step = [&](auto Nc, int p) {
+        constexpr int N = decltype(Nc)::value, O = N ^ 1;
+        // the coarse cell of this and the next plane, ahead of the planes' loads: waiting for the
+        // youngest load waits for all
+        const long long qc = ((((long long)((p & m) >> 1) << (lg - 1)) + (j0 >> 1) + t / TK) << (lg - 1)) +
+                             ((k0 + t % TK) >> 1);
+        if constexpr (MODE == kRestrict && N == 0) {
+            cm = maskc[qc];
+            cw = wc[qc];
         }
-        if (in && p + 1 < i0 + ti) {
-            if (MODE == kFas) {
-                if (is_active(fp)) f1 = fc[off(p + 1)];
-            } else if (is_active(fp)) {
-                f1 = src[off(p + 1)];
-            }
-            if (needs_w(fp)) w1 = w[off(p + 1)];
-        }
-        const double2* L = lv[(p - i0) & 1];
-        const bool second = RESTRICT && ((p - i0) & 1);
-        if (in) {
+        const int p3 = p + 3 < last ? p + 3 : last, p1 = p + 1 < last ? p + 1 : last - 1;
+        request(X, O, p3);
+        request(Y, O, p3);
+        request(E, O, p3);
+        request_f(X, O, p1, X.mp);
+        request_f(Y, O, p1, Y.mp);
+        const double2* L = lv[N];
+        const float* l = lm[FM ? N : 0];
+        auto residual = [&](Col& q, double2 jm, double2 jp, float mjm, float mjp) -> double {
             double d = 0.0;
-            if (!masked_b(bv)) {
-                const double2 jm = L[t - LK], jp = L[t + LK], km = L[t - 1], kp = L[t + 1];
-                const double un[6] = {um, up, jm.x, jp.x, km.x, kp.x};
-                const double bn[6] = {bm, bp, jm.y, jp.y, km.y, kp.y};
+            if (!masked_b(q.b0)) {
+                const double2 km = L[q.c - 1], kp = L[q.c + 1];
+                const double un[6] = {q.um, q.up, jm.x, jp.x, km.x, kp.x};
+                const double bn[6] = {q.bm, q.bp, jm.y, jp.y, km.y, kp.y};
+                const double f = MODE == kFas ? 0.0 : dev::rhs_value(g, q.f[N]);
                 if constexpr (FM) {
-                    const float* l = lm[(p - i0) & 1];
-                    const float mn[6] = {mm, fp, l[t - LK], l[t + LK], l[t - 1], l[t + 1]};
-                    d = masked_op_at(g, uv, bv, un, bn, mn, mv, MODE == kFas ? 0.0 : dev::rhs_value(g, f0), w0).L;
+                    const float mn[6] = {(float)q.mm, (float)q.mp, mjm, mjp, l[q.c - 1], l[q.c + 1]};
+                    d = masked_op_at(g, q.u0, q.b0, un, bn, mn, q.m0, f, q.w[N]).L;
                 } else {
-                    d = masked_op_pm1(g, uv, bv, un, bn, MODE == kFas ? 0.0 : dev::rhs_value(g, f0), w0).L;
+                    d = masked_op_pm1(g, q.u0, q.b0, un, bn, f, q.w[N]).L;
                 }
             }
-            if (MODE == kFas) {
-                if (!masked_b(bv)) fc[off(p)] = d - f0;
-            } else if (RESTRICT) {
-                usum = second ? usum + uv : uv;
-                dsum = second ? dsum + d : d;
-                if (second) {
-                    ra[(jj - 1) * TK + kk - 1] = usum;
-                    rb[(jj - 1) * TK + kk - 1] = dsum;
-                }
-            } else {
+            asm volatile("" : "+v"(d));  // one column after the other: interleaved, they spill
+            if constexpr (MODE == kFas) {
+                if (!masked_b(q.b0)) ref(fc, p, q.col) = d - q.f[N];
+            } else if constexpr (MODE == kNorm) {
                 s += d * d;
                 const double ad = fabs(d);
                 if (!(mx >= ad)) mx = ad;
             }
-        }
-        if (second) {
-            __syncthreads();
-            if (t < TJ * TK / 4) {
-                const int cj = t / (TK / 2), ck = t - cj * (TK / 2), lgc = lg - 1;
-                const int q = 2 * cj * TK + 2 * ck;
-                const long long qc = ((((long long)((p & m) >> 1) << lgc) + (j0 >> 1) + cj) << lgc) + (k0 >> 1) + ck;
-                if (maskc[qc] > 0.0f) {
-                    const double su = ra[q] + ra[q + 1] + ra[q + TK] + ra[q + TK + 1];
-                    const double sd = rb[q] + rb[q + 1] + rb[q + TK] + rb[q + TK + 1];
-                    uc[qc] = 0.125 * su;
-                    uhat[qc] = 0.125 * su;
-                    fc[qc] = 0.125 * sd;
-                } else {
-                    const double v = wc[qc];
-                    uc[qc] = v;
-                    uhat[qc] = v;
-                    fc[qc] = 0.0;
-                }
+            return d;
+        };
+        const double dx = residual(X, L[X.c - LK], make_double2(Y.u0, Y.b0), l[FM ? X.c - LK : 0], Y.m0);
+        const double dy = residual(Y, make_double2(X.u0, X.b0), L[Y.c + LK], X.m0, l[FM ? Y.c + LK : 0]);
+        if constexpr (MODE == kRestrict && N == 0) {
+            X.uq = X.u0;
+            X.dq = dx;
+            Y.uq = Y.u0;
+            Y.dq = dy;
+        } else if constexpr (MODE == kRestrict) {
+            const double ux = X.uq + X.u0, uy = Y.uq + Y.u0, ex = X.dq + dx, ey = Y.dq + dy;
+            const double su = ux + k_pair(ux) + uy + k_pair(uy);
+            const double sd = ex + k_pair(ex) + ey + k_pair(ey);
+            if (!(t & 1)) {
+                const double v = cm > 0.0f ? 0.125 * su : cw;
+                uc[qc] = v;
+                uhat[qc] = v;
+                fc[qc] = cm > 0.0f ? 0.125 * sd : 0.0;
             }
         }
-        if (on) {
-            lv[(p + 1 - i0) & 1][t] = make_double2(up, bp);
-            if constexpr (FM) lm[(p + 1 - i0) & 1][t] = fp;
-            mm = mv;
-            mv = fp;
-            um = uv;
-            bm = bv;
-            uv = up;
-            bv = bp;
-            up = ru;
-            fp = rm;
-            bp = signed_b(ru, is_active(rm));
-            ru = ru3;
-            rm = rm3;
-            f0 = f1;
-            w0 = w1;
-        }
+        // stage plane p+1 and shift the planes
+        auto advance = [&](Col& q) {
+            lv[O][q.c] = make_double2(q.up, q.bp);
+            if constexpr (FM) lm[O][q.c] = q.mp;
+            q.mm = q.m0;
+            q.m0 = q.mp;
+            q.um = q.u0;
+            q.bm = q.b0;
+            q.u0 = q.up;
+            q.b0 = q.bp;
+            q.up = q.ru[N];
+            q.mp = q.rm[N];
+            q.bp = signed_b(q.up, is_active(q.mp));
+        };
+        advance(X);
+        advance(Y);
+        if (ring) advance(E);
         __syncthreads();
+    };
+    for (int p = i0; p < i0 + ti; p += 2) {
+        step(std::integral_constant<int, 0>{}, p);
+        step(std::integral_constant<int, 1>{}, p + 1);
     }
     if constexpr (MODE == kNorm) {
+        double* ra = (double*)&lv[0][0];
+        double* rb = ra + NT;
         ra[t] = s;
         rb[t] = mx;
         __syncthreads();
-        for (int h = 512; h > 0; h >>= 1) {
-            if (t < h && t + h < NT) {
+        for (int h = NT / 2; h > 0; h >>= 1) {
+            if (t < h) {
                 ra[t] += ra[t + h];
                 const double o = rb[t + h];
                 if (!(rb[t] >= o)) rb[t] = o;
@@ -776,7 +860,7 @@ __global__ void __launch_bounds__(NT) km_stream(Grid g, const M* __restrict__ fl
     }
 }
 
-constexpr int kSJ = 8, kSK = 32, kST = 384;  // km_stream: 340 columns of 10 x 34
+constexpr int kSJ = 8, kSK = 64, kST = 256;  // tile and threads of km_stream
 
 template <int MODE, class M>
 hipError_t stream(const Grid& g, const M* flags, const double* w, const double* u, const double* src, double* partial,
