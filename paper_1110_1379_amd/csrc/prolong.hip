@@ -3,17 +3,27 @@
 // P is the cell-centred trilinear interpolation with weights 27/9/3/1 over 64 (Sec. V.A.3),
 // periodic.  It factors into an in-plane bilinear part (9/16, 3/16, 3/16, 1/16) on each
 // coarse plane and a 3/4, 1/4 blend of the two coarse planes nearest the fine plane.  A
-// thread owns one fine column (j,k) and a chunk of fine planes: it forms the in-plane
-// interpolant once per coarse plane and reuses it for the two fine planes that need it, so
-// a fine cell costs one load and one store of u plus a share of the coarse reads.  The
-// difference e = u^H - R u^h is formed on the fly from the two coarse arrays (FAS); the
-// linear correction scheme passes the correction itself (no second array).
+// thread owns the two fine columns (j, 2K) and (j, 2K+1), which read and write together and share
+// two of their coarse columns, and a chunk of fine planes: it forms the in-plane interpolants once
+// per coarse plane and reuses them for the two fine planes that need them.  The difference e =
+// u^H - R u^h is formed on the fly from the two coarse arrays (FAS); the linear correction scheme
+// passes the correction itself (no second array).
+// Bound by HBM (u once each way).  Measured at 512^3: 0.577 ms (4.2 TB/s) in
+// double precision with the difference formed, 0.412 ms without (5.5 TB/s), 0.257 ms in single; one fine
+// column per thread, eight coarse reads for every two cells, 0.758, 0.490 and 0.285.
 #include "mgfr_impl.h"
 
 namespace mgfr {
 namespace {
 
-constexpr int kPT = 256;  // threads (fine columns) per workgroup
+constexpr int kPT = 256;  // threads (pairs of fine columns) per workgroup
+
+// Two neighbouring values, no further aligned than one (a caller's field may start anywhere): one
+// access all the same, the hardware takes any multiple of four bytes.
+template <typename T>
+struct Pair {
+    T x, y;
+};
 
 // DIFF: the correction is uc - uhat (else uc itself).  maskf (may be null): add only where
 // the fine mask is positive (the active cells of a masked level).
@@ -23,44 +33,54 @@ __global__ void __launch_bounds__(kPT) k_prolong_stream(int lgc, T* __restrict__
                                                         int ncolblk, const int* __restrict__ halt)
 {
     if (halt && *halt) return;
-    const int lg = lgc + 1, n = 1 << lg, mc = (1 << lgc) - 1;
+    const int lg = lgc + 1, mc = (1 << lgc) - 1;
     const int nb = gridDim.x;
     int lid = blockIdx.x;
     if ((nb & 7) == 0) lid = (lid & 7) * (nb >> 3) + (lid >> 3);
     const int cb = lid % ncolblk, chunk = lid / ncolblk;
-    const unsigned col = (unsigned)cb * kPT + threadIdx.x;
-    if (col >= (1u << (2 * lg))) return;
-    const int j = (int)(col >> lg), k = (int)(col & (unsigned)(n - 1));
-    const int J = j >> 1, K = k >> 1;
-    const int Jn = (J + ((j & 1) ? 1 : -1)) & mc, Kn = (K + ((k & 1) ? 1 : -1)) & mc;
-    const unsigned c00 = ((unsigned)J << lgc) + K, c10 = ((unsigned)Jn << lgc) + K;
-    const unsigned c01 = ((unsigned)J << lgc) + Kn, c11 = ((unsigned)Jn << lgc) + Kn;
+    const unsigned pair = (unsigned)cb * kPT + threadIdx.x;
+    if (pair >= (1u << (2 * lg - 1))) return;
+    const int j = (int)(pair >> lgc), K = (int)(pair & (unsigned)mc);
+    const int J = j >> 1, Jn = (J + ((j & 1) ? 1 : -1)) & mc, Km = (K - 1) & mc, Kp = (K + 1) & mc;
+    const unsigned row = (unsigned)J << lgc, rown = (unsigned)Jn << lgc;
     const int i0 = chunk * PI;
 
     // element offsets fit in 32 bits (n <= 1024)
-    T v[PI];
+    using P2 = Pair<T>;
+    auto fine = [&](int i) -> unsigned { return ((unsigned)i << (2 * lg)) + 2 * pair; };
+    P2 v[PI];
 #pragma unroll
-    for (int t = 0; t < PI; ++t) v[t] = uf[((unsigned)(i0 + t) << (2 * lg)) + col];
+    for (int t = 0; t < PI; ++t) v[t] = *(const P2*)(uf + fine(i0 + t));
 
-    // fine plane i lies between coarse planes (i-1)>>1 and (i+1)>>1; for the chunk these are
-    // coarse planes ib .. ib + PI/2 + 1 (periodic)
-    const int ib = (i0 - 1) >> 1;
-    T ep[PI / 2 + 2];
-#pragma unroll
-    for (int t = 0; t < PI / 2 + 2; ++t) {
-        const unsigned base = (unsigned)((ib + t) & mc) << (2 * lgc);
+    // the in-plane interpolants of the two columns on coarse plane I
+    auto inplane = [&](int I) -> P2 {
+        const unsigned base = (unsigned)(I & mc) << (2 * lgc);
         auto E = [&](unsigned c) -> T { return DIFF ? uc[base + c] - uhat[base + c] : uc[base + c]; };
-        ep[t] = T(9.0 / 16.0) * E(c00) + T(3.0 / 16.0) * (E(c10) + E(c01)) + T(1.0 / 16.0) * E(c11);
-    }
+        const T c0 = E(row + K), c1 = E(rown + K);
+        P2 e;
+        e.x = T(9.0 / 16.0) * c0 + T(3.0 / 16.0) * (c1 + E(row + Km)) + T(1.0 / 16.0) * E(rown + Km);
+        e.y = T(9.0 / 16.0) * c0 + T(3.0 / 16.0) * (c1 + E(row + Kp)) + T(1.0 / 16.0) * E(rown + Kp);
+        return e;
+    };
+    auto add = [&](int t, const P2& near, const P2& far) {
+        const unsigned q = fine(i0 + t);
+        P2 r{v[t].x + (T(0.75) * near.x + T(0.25) * far.x), v[t].y + (T(0.75) * near.y + T(0.25) * far.y)};
+        if (maskf) {
+            const Pair<float> m = *(const Pair<float>*)(maskf + q);
+            if (!(m.x > 0.0f)) r.x = v[t].x;
+            if (!(m.y > 0.0f)) r.y = v[t].y;
+        }
+        *(P2*)(uf + q) = r;
+    };
+    // fine planes 2I and 2I+1 lie nearest coarse plane I and next to I-1 and I+1
+    P2 below = inplane((i0 >> 1) - 1), at = inplane(i0 >> 1);
 #pragma unroll
-    for (int t = 0; t < PI; ++t) {
-        const int i = i0 + t;
-        const int lo = ((i - 1) >> 1) - ib;
-        // odd i: the nearer coarse plane is the lower one
-        const T wlo = (i & 1) ? T(0.75) : T(0.25);
-        const unsigned q = ((unsigned)i << (2 * lg)) + col;
-        if (maskf && !(maskf[q] > 0.0f)) continue;
-        uf[q] = v[t] + (wlo * ep[lo] + (T(1) - wlo) * ep[lo + 1]);
+    for (int t = 0; t < PI; t += 2) {
+        const P2 above = inplane((i0 >> 1) + t / 2 + 1);
+        add(t, at, below);
+        add(t + 1, at, above);
+        below = at;
+        at = above;
     }
 }
 
@@ -69,8 +89,15 @@ hipError_t launch(const Grid& gc, T* uf, const T* uc, const T* uhat, hipStream_t
 {
     const int n = gc.n * 2;
     if (gc.n < 2 || n > 1024) return hipErrorInvalidValue;
-    const int ncolblk = (n * n + kPT - 1) / kPT;
-    if (n >= 8) {
+    const int ncolblk = (n * n / 2 + kPT - 1) / kPT;
+    // of two coarse arrays on the largest levels 16 planes per thread, which read fewer coarse planes
+    // twice: 512^3 double 0.577 against 0.605 ms, single 0.257 against 0.278; of one array 0.417 against
+    // 0.412
+    if (DIFF && n >= 512) {
+        const unsigned nb = (unsigned)(ncolblk * (n / 16));
+        hipLaunchKernelGGL((k_prolong_stream<T, 16, DIFF>), dim3(nb), dim3(kPT), 0, s, gc.lg, uf, uc, uhat, maskf,
+                           ncolblk, gc.halt);
+    } else if (n >= 8) {
         const unsigned nb = (unsigned)(ncolblk * (n / 8));
         hipLaunchKernelGGL((k_prolong_stream<T, 8, DIFF>), dim3(nb), dim3(kPT), 0, s, gc.lg, uf, uc, uhat, maskf,
                            ncolblk, gc.halt);

@@ -327,3 +327,23 @@ def test_exponential_outside_its_range():
     c = mgfr.mgfr_constants(p1, N)
     r = mgfr.mgfr_residual(ctx, rho, u, p1)[2, 2, 2].item()
     assert abs(r - (c["A"] * np.exp(80.0) - c["Sbar"])) <= 1e-13 * c["A"] * np.exp(80.0)
+
+
+@pytest.mark.parametrize("N", [32, 64])
+def test_solution_field_needs_no_more_than_its_own_alignment(N):
+    """A field that starts one value past a 16-byte boundary is solved to the same bits."""
+    import torch
+    from paper_1110_1379_amd import mgfr
+    ctx = mgfr.Context(0)
+    params = mgfr.Params(box_mpc_h=float(N), fr0_abs=1e-5)
+    rho = torch.from_numpy(inputs.small_box(N, 0)).to("cuda:0")
+    store = torch.empty(N ** 3 + 2, dtype=torch.float64, device="cuda:0")
+    first = 1 if store.data_ptr() % 16 == 0 else 0
+    u = store[first:first + N ** 3].view(N, N, N)
+    assert u.data_ptr() % 16 == 8
+    opts = mgfr.mgfr_default_opts(tol=1e-10)
+    ref, href, _ = mgfr.mg_fr_solve(ctx, rho, params, opts)
+    _, h, _ = mgfr.mg_fr_solve(ctx, rho, params, opts, u=u)
+    assert torch.equal(u, ref)
+    assert np.array_equal(np.asarray(h), np.asarray(href))
+    ctx.close()
