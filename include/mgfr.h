@@ -103,15 +103,15 @@ typedef struct mgfr_opts {
                              32, 3 = 16 x 64, 5 = 32 x 64 (one tile column pair per thread),
                              4 = 8 x 32 (column pairs over the tile and its halo).
                              Batched solves, launched sweeps of unit levels of side >=
-                             32: 0 = automatic: periodic boxes walk 16 x 32 column tiles
-                             (16 planes per workgroup), a mixed solve in pairs of fused
-                             two-colour sweeps, double precision one colour per launch,
-                             at multigrid depths with at least 256 such tiles in the
-                             batch (one thread per cell of the colour at the others);
-                             patches run one thread per cell of the colour; 1 = one
-                             thread per cell everywhere; 2 = column tiles one colour per
-                             launch everywhere; 3 = fused pairs at every depth, for
-                             patches too (8 planes per workgroup) in mixed solves; 4, 5
+                             32: 0 = automatic: a mixed solve walks 16 x 32 column tiles
+                             (16 planes per workgroup, patches 8) in pairs of fused
+                             two-colour sweeps, double precision walks those of periodic
+                             boxes one colour per launch, at multigrid depths with at
+                             least 256 such tiles of 16 planes in the batch; one thread
+                             per cell of the colour at the others and on patches in
+                             double precision; 1 = one thread per cell everywhere; 2 =
+                             column tiles one colour per launch everywhere; 3 = the
+                             fused pairs of mixed solves at every depth; 4, 5
                              as 0 (all give the same results, bit for bit)        [0]      */
 } mgfr_opts;
 

@@ -236,7 +236,8 @@ Sweep sweep_tables(Meta& meta, const std::vector<mgfr::BGrid>& f, int tile)
     // Automatic choice: tiles only for a depth that has at least one per compute unit.  A
     // tile's walk is a chain of barrier-separated plane steps; with fewer tiles than CUs the
     // one-thread-per-cell launches finish sooner (16 boxes of 32^3: 64 tiles take 22 us per
-    // fused sweep, the two per-cell colour launches 12 us).
+    // fused sweep, the two per-cell colour launches 12 us; patches with 40 tiles of 16 planes 24
+    // against 13 us, with 320 34 against 47 us, with 1280 79 against 113 us).
     bool few = false;
     if (tile != 1 && tile != 2 && tile != 3) {
         long long total = 0;
@@ -343,12 +344,11 @@ struct Batch {
     const mgfr::BGrid* grids(const Launch& L) const { return (const mgfr::BGrid*)(dmeta + L.grids); }
 
     // A level of side n swept in fused pairs: a level of a mixed solve, side >= 32, swept by
-    // launches (not inside a one-workgroup solve); periodic boxes by default (tile 0, 4, 5),
-    // patches too with tile 3.  (On patches of the sizes of a refinement level the fused pairs
-    // gain nothing over one thread per cell: their launches are few workgroups deep.)
+    // launches (not inside a one-workgroup solve), unless tile 1 or 2 asks for another form.  What
+    // a depth of few tiles runs, sweep_tables decides.
     bool pair_level(const Unit& U, int n) const
     {
-        const bool want = o->tile == 3 || (o->tile != 1 && o->tile != 2 && U.periodic);
+        const bool want = o->tile != 1 && o->tile != 2;
         return o->precision == MGFR_MIXED && want && mgfr::batch_col_tiles(n) > 0 &&
                mgfr::batch_pair_tiles(n, U.periodic) > 0 && (phases || n > W);
     }

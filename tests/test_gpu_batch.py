@@ -393,3 +393,34 @@ def test_two_chunk_sweep_of_a_large_batch_matches_per_cell_sweep(mg, ctx):
         assert torch.equal(a, b)
     for a, b in zip(hists, ref[1]):
         assert np.array_equal(np.asarray(a), np.asarray(b))
+
+
+@pytest.mark.parametrize("pre,post", [(2, 2), (1, 3)])
+def test_fused_pairs_of_many_patches_match_per_cell_sweep(mg, ctx, pre, post):
+    """A depth of patches with 256 column tiles or more is swept in fused pairs by default (an odd
+    sweep of a group in place): the same bits as one thread per cell."""
+    import torch
+    N0 = 128
+    params = mg.Params(box_mpc_h=float(N0), fr0_abs=1e-5)
+    rho0 = inputs.lognormal(N0, 1.5, -1.5, seed=5)
+    ud, _, _ = mg.mg_fr_solve(ctx, dev(rho0), params, mg.mgfr_default_opts(tol=1e-8))
+    corners = [(x, y, z) for x in (0, 64, 128) for y in (64, 192) for z in (0, 128)]
+    assert len(corners) * (64 // 16) * (64 // 16) * (64 // 32) >= 256
+    patches, blocks, offset = [], [], 0
+    for c in corners:
+        patches.append(dict(level=1, parent=-1, origin=c, n=64, offset=offset))
+        lo = [v // 2 for v in c]
+        b = rho0[lo[0]:lo[0] + 32, lo[1]:lo[1] + 32, lo[2]:lo[2] + 32]
+        blocks.append(np.repeat(np.repeat(np.repeat(b, 2, 0), 2, 1), 2, 2).ravel())
+        offset += 64 ** 3
+    rho = dev(np.concatenate(blocks))
+    out = []
+    for tile in (1, 0):
+        opts = mg.mgfr_default_opts(tol=1e-8, precision=mg.MGFR_MIXED, tile=tile, pre=pre, post=post)
+        up, hists, st = mg.mg_fr_solve_patches(ctx, ud, patches, rho, params, opts)
+        assert st == mg.MGFR_OK, ctx.last_error()
+        say(f"[many patches] tile={tile}")
+        out.append((up, [np.asarray(h) for h in hists]))
+    assert torch.equal(out[0][0], out[1][0])
+    for a, b in zip(out[0][1], out[1][1]):
+        assert np.array_equal(a, b)
