@@ -36,9 +36,26 @@ struct Unit {
 };
 
 // Host image of everything the kernels of one batch read from device memory: descriptor
-// arrays and workgroup tables, concatenated into one buffer.
+// arrays, concatenated into one buffer.  The workgroup tables, one entry per workgroup of every
+// launch, are only counted here and written on the device from the runs (batch_expand): for 64 boxes
+// of 64^3 and 16 of 128^3 they are 660 000 entries, whose making, copying and upload on the host took
+// 1.2 ms of every solve.
 struct Meta {
     std::vector<char> bytes;
+    std::vector<mgfr::BlockRun> runs;
+    size_t tables = 0;  // entries of all workgroup tables
+    // Workgroup table of grids with counts[i] workgroups each, grid by grid; the index of its first
+    // entry.
+    size_t blocks(const std::vector<int>& counts, int* total)
+    {
+        const size_t at = tables;
+        for (size_t i = 0; i < counts.size(); ++i) {
+            if (counts[i] > 0) runs.push_back(mgfr::BlockRun{(long long)tables, (int)i, counts[i]});
+            tables += (size_t)counts[i];
+        }
+        *total = (int)(tables - at);
+        return at;
+    }
     template <class T>
     size_t add(const std::vector<T>& v)
     {
@@ -50,7 +67,8 @@ struct Meta {
 };
 
 struct Launch {
-    size_t grids = 0, blk = 0, other = 0;  // offsets into the device meta buffer
+    size_t grids = 0, other = 0;  // offsets into the device meta buffer
+    size_t blk = 0;               // first entry of the workgroup table
     int nblk = 0, ngrid = 0;
 };
 
@@ -142,18 +160,17 @@ Launch table(Meta& meta, const std::vector<mgfr::BGrid>& grids, W work, std::vec
              std::vector<int>* count = nullptr)
 {
     const int B = mgfr::batch_block();
-    std::vector<int2> blk;
+    std::vector<int> nb(grids.size());
+    int at = 0;
     for (size_t i = 0; i < grids.size(); ++i) {
-        const long long w = work(grids[i]);
-        const int nb = (int)((w + B - 1) / B);
-        if (first) first->push_back((int)blk.size());
-        if (count) count->push_back(nb);
-        for (int b = 0; b < nb; ++b) blk.push_back(make_int2((int)i, b));
+        nb[i] = (int)((work(grids[i]) + B - 1) / B);
+        if (first) first->push_back(at);
+        if (count) count->push_back(nb[i]);
+        at += nb[i];
     }
     Launch L;
     L.grids = meta.add(grids);
-    L.blk = meta.add(blk);
-    L.nblk = (int)blk.size();
+    L.blk = meta.blocks(nb, &L.nblk);
     L.ngrid = (int)grids.size();
     return L;
 }
@@ -163,11 +180,11 @@ long long cells3(const mgfr::BGrid& g) { return 1LL << (3 * g.lg); }
 RR rr_tables(Meta& meta, const std::vector<mgfr::BGrid>& f, const std::vector<mgfr::BGrid>& cg)
 {
     std::vector<mgfr::BGrid> tf, tc, cf, cc;
-    std::vector<int2> tb;
+    std::vector<int> tb;
     for (size_t i = 0; i < f.size(); ++i) {
         const long long nt = mgfr::batch_col_tiles(f[i].n);
         if (nt > 0) {
-            for (long long b = 0; b < nt; ++b) tb.push_back(make_int2((int)tf.size(), (int)b));
+            tb.push_back((int)nt);
             tf.push_back(f[i]);
             tc.push_back(cg[i]);
         } else {
@@ -177,8 +194,7 @@ RR rr_tables(Meta& meta, const std::vector<mgfr::BGrid>& f, const std::vector<mg
     }
     RR R;
     R.tile.grids = meta.add(tf);
-    R.tile.blk = meta.add(tb);
-    R.tile.nblk = (int)tb.size();
+    R.tile.blk = meta.blocks(tb, &R.tile.nblk);
     R.tile.ngrid = (int)tf.size();
     R.tile.other = meta.add(tc);
     R.cell = table(meta, cf, [](const mgfr::BGrid& g) { return cells3(g) / 8; });
@@ -189,39 +205,39 @@ RR rr_tables(Meta& meta, const std::vector<mgfr::BGrid>& f, const std::vector<mg
 NormPlan norm_tables(Meta& meta, const std::vector<mgfr::BGrid>& g0)
 {
     std::vector<mgfr::BGrid> tg, cg;
-    std::vector<int2> tb, cb;
-    std::vector<int> first(g0.size()), count(g0.size());
+    std::vector<int> tb, cb, first(g0.size()), count(g0.size());
+    int ntile = 0, ncell = 0;
     const int B = mgfr::batch_block();
     for (size_t u = 0; u < g0.size(); ++u) {
         const long long nt = mgfr::batch_col_tiles(g0[u].n);
         if (nt > 0) {
-            first[u] = (int)tb.size();
+            first[u] = ntile;
             count[u] = (int)nt;
-            for (long long b = 0; b < nt; ++b) tb.push_back(make_int2((int)tg.size(), (int)b));
+            ntile += (int)nt;
+            tb.push_back((int)nt);
             tg.push_back(g0[u]);
         }
     }
     for (size_t u = 0; u < g0.size(); ++u) {
         if (mgfr::batch_col_tiles(g0[u].n) > 0) continue;
         const long long nb = (cells3(g0[u]) + B - 1) / B;
-        first[u] = (int)(tb.size() + cb.size());
+        first[u] = ntile + ncell;
         count[u] = (int)nb;
-        for (long long b = 0; b < nb; ++b) cb.push_back(make_int2((int)cg.size(), (int)b));
+        ncell += (int)nb;
+        cb.push_back((int)nb);
         cg.push_back(g0[u]);
     }
     NormPlan N;
     N.tile.grids = meta.add(tg);
-    N.tile.blk = meta.add(tb);
-    N.tile.nblk = (int)tb.size();
+    N.tile.blk = meta.blocks(tb, &N.tile.nblk);
     N.tile.ngrid = (int)tg.size();
     N.cell.grids = meta.add(cg);
-    N.cell.blk = meta.add(cb);
-    N.cell.nblk = (int)cb.size();
+    N.cell.blk = meta.blocks(cb, &N.cell.nblk);
     N.cell.ngrid = (int)cg.size();
     N.first = meta.add(first);
     N.count = meta.add(count);
     N.ngrid = (int)g0.size();
-    N.nparts = (long long)tb.size() + (long long)cb.size();
+    N.nparts = (long long)N.tile.nblk + N.cell.nblk;
     return N;
 }
 
@@ -231,7 +247,7 @@ NormPlan norm_tables(Meta& meta, const std::vector<mgfr::BGrid>& g0)
 Sweep sweep_tables(Meta& meta, const std::vector<mgfr::BGrid>& f, int tile)
 {
     std::vector<mgfr::BGrid> cell, col, pair[2];
-    std::vector<int2> bcol, bpair[2], bpair1[2];
+    std::vector<int> bcol, bpair[2], bpair1[2];
     std::vector<const double*> box_u;
     // Automatic choice: tiles only for a depth that has at least one per compute unit.  A
     // tile's walk is a chain of barrier-separated plane steps; with fewer tiles than CUs the
@@ -253,8 +269,8 @@ Sweep sweep_tables(Meta& meta, const std::vector<mgfr::BGrid>& f, int tile)
         }
         if (g.e32b && nt > 0 && np > 0) {
             const int w = g.periodic ? 1 : 0;
-            for (long long b = 0; b < np; ++b) bpair[w].push_back(make_int2((int)pair[w].size(), (int)b));
-            for (long long b = 0; b < nt; ++b) bpair1[w].push_back(make_int2((int)pair[w].size(), (int)b));
+            bpair[w].push_back((int)np);
+            bpair1[w].push_back((int)nt);
             pair[w].push_back(g);
             if (g.periodic) box_u.push_back(g.u);
             continue;
@@ -264,15 +280,14 @@ Sweep sweep_tables(Meta& meta, const std::vector<mgfr::BGrid>& f, int tile)
             cell.push_back(g);
             continue;
         }
-        for (long long b = 0; b < nt; ++b) bcol.push_back(make_int2((int)col.size(), (int)b));
+        bcol.push_back((int)nt);
         col.push_back(g);
     }
     Sweep S;
     S.cell = table(meta, cell, [](const mgfr::BGrid& g) { return cells3(g) / 2; });
-    auto tiles = [&](Launch& L, const std::vector<mgfr::BGrid>& gs, const std::vector<int2>& blk) {
+    auto tiles = [&](Launch& L, const std::vector<mgfr::BGrid>& gs, const std::vector<int>& counts) {
         L.grids = meta.add(gs);
-        L.blk = meta.add(blk);
-        L.nblk = (int)blk.size();
+        L.blk = meta.blocks(counts, &L.nblk);
         L.ngrid = (int)gs.size();
     };
     tiles(S.col, col, bcol);
@@ -293,7 +308,9 @@ struct Batch {
     int W = 16;           // workgroup-per-unit engine: units and levels of side <= W in one workgroup
     Plan plan;
     UPlan up;
+    Meta meta;                // host image, until upload()
     char* dmeta = nullptr;
+    int2* dblk = nullptr;     // workgroup tables
     int* dactive = nullptr;
     std::vector<int> active;
     double* dpartial = nullptr;
@@ -337,7 +354,7 @@ struct Batch {
     {
         mgfr::BTable t;
         t.grids = (const mgfr::BGrid*)(dmeta + L.grids);
-        t.blk = (const int2*)(dmeta + L.blk);
+        t.blk = dblk + L.blk;
         t.active = dactive;
         return t;
     }
@@ -440,11 +457,22 @@ struct Batch {
             }
         }
         // tables
-        Meta meta;
         int maxlev = 0;
         for (Unit& U : units) maxlev = std::max(maxlev, U.nlev);
         plan.depth.assign(maxlev, Depth{});
         for (int m = 0; m < maxlev; ++m) {
+            Depth& D = plan.depth[m];
+            std::vector<mgfr::BGrid> pf, pc;  // the patches' boundary faces, for both engines
+            for (Unit& U : units) {
+                if (U.nlev <= m + 1) continue;
+                D.deep = true;
+                if (U.periodic) continue;
+                pf.push_back(U.g[m]);
+                pc.push_back(U.g[m + 1]);
+            }
+            D.faces_c = table(meta, pc, [](const mgfr::BGrid& g) { return 6LL * g.n * g.n; });
+            D.faces_c.other = meta.add(pf);
+            if (!phases) continue;
             std::vector<mgfr::BGrid> f, cgr, crs;
             for (Unit& U : units) {
                 if (U.nlev > m + 1) {
@@ -454,8 +482,6 @@ struct Batch {
                     crs.push_back(U.g[m]);
                 }
             }
-            Depth& D = plan.depth[m];
-            D.deep = !f.empty();
             D.coarsest = !crs.empty();
             if (D.deep) {
                 D.half = sweep_tables(meta, f, o->tile);
@@ -464,14 +490,6 @@ struct Batch {
                 D.coarse_f = table(meta, f, [](const mgfr::BGrid& g) { return cells3(g) / 8; });
                 D.coarse_f.other = D.coarse_c.grids;  // coarse grids, same order
                 D.rr = rr_tables(meta, f, cgr);
-                std::vector<mgfr::BGrid> pf, pc;
-                for (size_t i = 0; i < f.size(); ++i)
-                    if (!f[i].periodic) {
-                        pf.push_back(f[i]);
-                        pc.push_back(cgr[i]);
-                    }
-                D.faces_c = table(meta, pc, [](const mgfr::BGrid& g) { return 6LL * g.n * g.n; });
-                D.faces_c.other = meta.add(pf);
             }
             if (D.coarsest) {
                 D.crs.grids = meta.add(crs);
@@ -483,17 +501,18 @@ struct Batch {
         std::vector<int> first, count;
         plan.cells0 = table(meta, g0, [](const mgfr::BGrid& g) { return cells3(g); }, &first, &count);
         plan.fuse_add = o->precision == MGFR_MIXED && o->post >= 2 && o->post % 2 == 0;
-        plan.add0 = table(meta, add_rest(g0, plan.depth.empty() || !plan.depth[0].deep ? nullptr : &plan.depth[0].half,
-                                         plan.fuse_add),
-                          [](const mgfr::BGrid& g) { return cells3(g); });
         plan.first = meta.add(first);
         plan.count = meta.add(count);
-        plan.norm = norm_tables(meta, g0);
+        if (phases) {
+            plan.add0 = table(meta,
+                              add_rest(g0, plan.depth.empty() || !plan.depth[0].deep ? nullptr : &plan.depth[0].half,
+                                       plan.fuse_add),
+                              [](const mgfr::BGrid& g) { return cells3(g); });
+            plan.norm = norm_tables(meta, g0);
+        }
         plan.nunit = (int)units.size();
         plan.nblk_cells0 = plan.cells0.nblk;
         if (!phases) build_units(meta);
-        setup_offset = meta.bytes.size();
-        meta_image = std::move(meta.bytes);
         return MGFR_OK;
     }
 
@@ -568,33 +587,23 @@ struct Batch {
                         [](const mgfr::BGrid& g) { return cells3(g); });
     }
 
-    std::vector<char> meta_image;
-    size_t setup_offset = 0;
-
-    // Appends extra tables (patch set-up) before the upload.
-    template <class T>
-    size_t add_extra(const std::vector<T>& v)
-    {
-        Meta m;
-        m.bytes = std::move(meta_image);
-        const size_t off = m.add(v);
-        meta_image = std::move(m.bytes);
-        return off;
-    }
-
     int upload()
     {
         // pinned staging: [per-unit (sum, max) | per-unit flags | descriptor image]
         const size_t nu = units.size();
         const size_t meta_at = (sizeof(double) * 2 * nu + sizeof(int) * nu + 255) & ~size_t(255);
-        MGFR_TRY(ensure_pinned(c, meta_at + meta_image.size()));
+        const size_t runs = meta.add(meta.runs);
+        MGFR_TRY(ensure_pinned(c, meta_at + meta.bytes.size()));
         hout = (double*)c->pin;
         hact = (int*)(hout + 2 * nu);
         char* hmeta = (char*)c->pin + meta_at;
-        std::memcpy(hmeta, meta_image.data(), meta_image.size());
-        MGFR_TRY(alloc(&dmeta, meta_image.size()));
-        MGFR_TRY(hip_check(c, hipMemcpyAsync(dmeta, hmeta, meta_image.size(), hipMemcpyHostToDevice, s),
+        std::memcpy(hmeta, meta.bytes.data(), meta.bytes.size());
+        MGFR_TRY(alloc(&dmeta, meta.bytes.size()));
+        MGFR_TRY(alloc(&dblk, meta.tables));
+        MGFR_TRY(hip_check(c, hipMemcpyAsync(dmeta, hmeta, meta.bytes.size(), hipMemcpyHostToDevice, s),
                            "hipMemcpyAsync"));
+        MGFR_TRY(hip_check(c, mgfr::batch_expand((const mgfr::BlockRun*)(dmeta + runs), (int)meta.runs.size(), dblk, s),
+                           "batch_expand"));
         MGFR_TRY(alloc(&dactive, nu));
         active.assign(nu, 1);
         MGFR_TRY(upload_active());
@@ -1009,7 +1018,7 @@ struct Batch {
     {
         mgfr::BTable t;
         t.grids = (const mgfr::BGrid*)(dmeta + L.grids);
-        t.blk = (const int2*)(dmeta + L.blk);
+        t.blk = dblk + L.blk;
         t.active = dactive;
         return t;
     }
@@ -1296,15 +1305,31 @@ int mg_fr_solve_patches(mgfr_ctx* c, const double* u_domain, int N0, const mgfr_
     std::sort(ranges.begin(), ranges.end());
     for (size_t i = 1; i < ranges.size(); ++i)
         if (ranges[i].first < ranges[i - 1].second) return c->fail(MGFR_EINVAL, "patch blocks overlap in the packed arrays");
-    for (int p = 0; p < npatch; ++p)
-        for (int q = p + 1; q < npatch; ++q) {
-            const mgfr_patch &A = patches[p], &B = patches[q];
-            if (A.level != B.level) continue;
-            bool sep = false;
-            for (int d = 0; d < 3; ++d)
-                sep = sep || A.origin[d] + A.n <= B.origin[d] || B.origin[d] + B.n <= A.origin[d];
-            if (!sep) return c->fail(MGFR_EINVAL, "patches %d and %d overlap", p, q);
-        }
+    // patches of one level must not overlap: in the order of (level, first origin) only those that
+    // still reach the next one's origin can (of 2000 patches every pair would be two million tests)
+    auto overlap = [&](int p, int q) {
+        const mgfr_patch &A = patches[p], &B = patches[q];
+        if (A.level != B.level) return false;
+        for (int d = 0; d < 3; ++d)
+            if (A.origin[d] + A.n <= B.origin[d] || B.origin[d] + B.n <= A.origin[d]) return false;
+        return true;
+    };
+    std::vector<int> by(npatch);
+    for (int p = 0; p < npatch; ++p) by[p] = p;
+    std::sort(by.begin(), by.end(), [&](int a, int b) {
+        const mgfr_patch &A = patches[a], &B = patches[b];
+        return A.level != B.level ? A.level < B.level : A.origin[0] < B.origin[0];
+    });
+    bool any = false;
+    for (int x = 0; x < npatch; ++x) {
+        const mgfr_patch& A = patches[by[x]];
+        for (int y = x + 1; y < npatch && patches[by[y]].level == A.level && patches[by[y]].origin[0] < A.origin[0] + A.n; ++y)
+            any = any || overlap(by[x], by[y]);
+    }
+    if (any)  // name the first pair
+        for (int p = 0; p < npatch; ++p)
+            for (int q = p + 1; q < npatch; ++q)
+                if (overlap(p, q)) return c->fail(MGFR_EINVAL, "patches %d and %d overlap", p, q);
     MGFR_TRY(hip_check(c, hipSetDevice(c->device), "hipSetDevice"));
     hipStream_t s = (hipStream_t)stream;
     int worst = MGFR_OK;
@@ -1350,11 +1375,8 @@ int mg_fr_solve_patches(mgfr_ctx* c, const double* u_domain, int N0, const mgfr_
             parents.push_back(pp);
             g0.push_back(units[i].g[0]);
         }
-        Meta extra;
-        extra.bytes = std::move(b.meta_image);
-        Launch setup = table(extra, g0, [](const mgfr::BGrid& g) { return 7LL * g.n * g.n; });
-        const size_t parents_off = extra.add(parents);
-        b.meta_image = std::move(extra.bytes);
+        Launch setup = table(b.meta, g0, [](const mgfr::BGrid& g) { return 7LL * g.n * g.n; });
+        const size_t parents_off = b.meta.add(parents);
         MGFR_TRY(b.upload());
         MGFR_TRY(hip_check(c, mgfr::batch_setup(b.tab(setup), setup.nblk, (const mgfr::PatchParent*)(b.dmeta + parents_off), s),
                            "batch_setup"));

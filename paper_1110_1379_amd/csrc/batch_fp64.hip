@@ -339,9 +339,22 @@ __global__ void __launch_bounds__(kB) kb_add_correction(BTable t)
     if (q < (1LL << (3 * g.lg))) g.u[q] += (double)g.e32[q];
 }
 
+// Workgroup tables from their runs, one workgroup per run.
+__global__ void __launch_bounds__(kB) kb_expand(const BlockRun* __restrict__ runs, int2* __restrict__ blk)
+{
+    const BlockRun r = runs[blockIdx.x];
+    for (int b = threadIdx.x; b < r.count; b += kB) blk[r.at + b] = make_int2(r.grid, b);
+}
+
 }  // namespace
 
 int batch_block() { return kB; }
+
+hipError_t batch_expand(const BlockRun* runs, int nrun, int2* blk, hipStream_t s)
+{
+    if (nrun > 0) hipLaunchKernelGGL(kb_expand, dim3((unsigned)nrun), dim3(kB), 0, s, runs, blk);
+    return hipGetLastError();
+}
 
 hipError_t batch_ngs(const BTable& t, int nblk, hipStream_t s)
 {

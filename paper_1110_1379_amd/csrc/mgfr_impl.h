@@ -118,6 +118,13 @@ struct BGrid {
     float* e32b;       // level swept by pairs of fused sweeps: their second buffer of e, or null
 };
 
+// Entries of a workgroup table: `count` of them from entry `at`, (grid, 0) .. (grid, count - 1).
+struct BlockRun {
+    long long at;
+    int grid, count;
+};
+hipError_t batch_expand(const BlockRun* runs, int nrun, int2* blk, hipStream_t s);
+
 // Workgroup table: blk[b] = (index into grids, block number within that grid).
 struct BTable {
     const BGrid* grids;

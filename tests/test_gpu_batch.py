@@ -424,3 +424,26 @@ def test_fused_pairs_of_many_patches_match_per_cell_sweep(mg, ctx, pre, post):
     assert torch.equal(out[0][0], out[1][0])
     for a, b in zip(out[0][1], out[1][1]):
         assert np.array_equal(a, b)
+
+
+def test_the_first_overlapping_pair_of_patches_is_named(mg, ctx):
+    """Patches in any order and on several levels: an overlap is found wherever the pair stands, and
+    the pair first in the caller's order is the one named; patches that only touch are accepted."""
+    N0 = 32
+    params = mg.Params(box_mpc_h=float(N0), fr0_abs=1e-5)
+    rho0 = inputs.small_box(N0, 0)
+    ud, _, _ = mg.mg_fr_solve(ctx, dev(rho0), params, mg.mgfr_default_opts(tol=1e-8))
+    corners = [(x, y, z) for x in (48, 0, 16, 32) for y in (0, 16) for z in (32, 0, 16)]
+
+    def solve(origins):
+        patches = [dict(level=1, parent=-1, origin=o, n=16, offset=p * 16 ** 3) for p, o in enumerate(origins)]
+        rho = dev(np.ones(len(patches) * 16 ** 3))
+        return mg.mg_fr_solve_patches(ctx, ud, patches, rho, params, mg.mgfr_default_opts(tol=1e-6))
+    _, _, st = solve(corners)
+    assert st == mg.MGFR_OK
+    moved = list(corners)
+    moved[20] = (corners[3][0], corners[3][1] + 2, corners[3][2] + 2)
+    first = min((p, q) for p in range(len(moved)) for q in range(p + 1, len(moved))
+                if all(abs(a - b) < 16 for a, b in zip(moved[p], moved[q])))
+    with pytest.raises(mg.MgfrError, match="patches %d and %d overlap" % first):
+        solve(moved)
