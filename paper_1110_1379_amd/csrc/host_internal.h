@@ -57,6 +57,7 @@ struct Level {
     mgfr::Grid g;
     double* u = nullptr;     // level 0: the caller's u
     double* alt = nullptr;   // second copy for out-of-place (fused) sweeps, n >= 64
+    double* blk = nullptr;   // the same of smaller levels relaxed in blocks (block_level)
     double* uhat = nullptr;  // R u of the finer level (m >= 1); turned into u^H - R u^h
     double* f = nullptr;     // FAS right-hand side (m >= 1)
 };
@@ -67,6 +68,7 @@ struct Level32 {
     float* ub = nullptr;    // base u (level 0: u rounded; coarse: restricted)
     float* e = nullptr;     // correction
     float* ealt = nullptr;  // second copy for the fused sweep (n >= 64)
+    float* eblk = nullptr;  // the same of smaller levels relaxed in blocks
     float* ehat = nullptr;  // R e of the finer level (m >= 1); turned into e^H - R e^h
     float* f = nullptr;     // right-hand side (level 0: r = -d)
 };
@@ -229,6 +231,7 @@ struct mgfr_ctx {
                 (void)hipFree(lv[m].f);
             }
             (void)hipFree(lv[m].alt);
+            (void)hipFree(lv[m].blk);
         }
         lv.clear();
         N = 0;
@@ -241,6 +244,7 @@ struct mgfr_ctx {
             (void)hipFree(L.ub);
             (void)hipFree(L.e);
             (void)hipFree(L.ealt);
+            (void)hipFree(L.eblk);
             (void)hipFree(L.ehat);
             (void)hipFree(L.f);
         }
@@ -382,6 +386,7 @@ inline int ensure_levels(mgfr_ctx* c, int N, int coarsest)
             ok = hipMalloc(&L.u, bytes) == hipSuccess && hipMalloc(&L.uhat, bytes) == hipSuccess &&
                  hipMalloc(&L.f, bytes) == hipSuccess;
         if (ok && n >= mgfr::fused_sweep_min_n()) ok = hipMalloc(&L.alt, bytes) == hipSuccess;
+        if (ok && !L.alt && mgfr::block_level(n)) ok = hipMalloc(&L.blk, bytes) == hipSuccess;
         if (!ok) {
             if (n < N) {
                 (void)hipFree(L.u);
@@ -389,6 +394,7 @@ inline int ensure_levels(mgfr_ctx* c, int N, int coarsest)
                 (void)hipFree(L.f);
             }
             (void)hipFree(L.alt);
+            (void)hipFree(L.blk);
             c->free_levels();
             return c->fail(MGFR_ENOMEM, "hipMalloc of the %d^3 level failed", n);
         }
@@ -411,6 +417,7 @@ inline int ensure_levels32(mgfr_ctx* c, int N, int coarsest)
                   hipMalloc(&L.f, bytes) == hipSuccess;
         if (ok && n < N) ok = hipMalloc(&L.ehat, bytes) == hipSuccess;
         if (ok && n >= mgfr::fused_sweep_min_n()) ok = hipMalloc(&L.ealt, bytes) == hipSuccess;
+        if (ok && !L.ealt && mgfr::block_level(n)) ok = hipMalloc(&L.eblk, bytes) == hipSuccess;
         c->lv32.push_back(L);
         if (!ok) {
             c->free_levels32();

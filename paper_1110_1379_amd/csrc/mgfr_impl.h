@@ -281,11 +281,26 @@ hipError_t prolong_add_masked(const Grid& gc, double* uf, const double* ec, cons
 // side <= 8 swept until rms(L - f) <= rtol x initial, or its rounding floor, or cap sweeps (rtol =
 // 0: exactly cap).  u is relaxed in place; *sweeps is increased by the coarsest level's sweeps.
 int domain_tail_n();
-hipError_t domain_tail(const Grid& g, double* u, const double* src, int nl, int pre, int post, int cap, double rtol,
-                       long long* sweeps, hipStream_t s);
+// fas: src holds R d of the finer level and u its R u; the right-hand side L(u) - R d is formed first.
+hipError_t domain_tail(const Grid& g, double* u, const double* src, bool fas, int nl, int pre, int post, int cap,
+                       double rtol, long long* sweeps, hipStream_t s);
 // The same for the correction equation, e in place; the bases of the levels below come from ub.
-hipError_t domain_tail32(const Grid& g, const float* ub, float* e, const float* f, int nl, int pre, int post, int cap,
-                         double rtol, hipStream_t s);
+hipError_t domain_tail32(const Grid& g, const float* ub, float* e, const float* f, bool fas, int nl, int pre, int post,
+                         int cap, double rtol, hipStream_t s);
+
+// ---- two sweeps of a small level with the transfers beside them, one launch (block.hip) ----
+// block_pre: two red-black sweeps of u = in into out (another array), then uc = uhat = R out and fc =
+// R d of the level below.  block_post: two sweeps of in + P(uc - uhat) into out.  Periodic levels
+// with block_level(n); the same for the correction equation.
+bool block_level(int n);
+hipError_t block_pre(const Grid& g, const double* in, double* out, const double* src, double* uc, double* uhat,
+                     double* fc, hipStream_t s);
+hipError_t block_post(const Grid& g, const double* in, double* out, const double* src, const double* uc,
+                      const double* uhat, hipStream_t s);
+hipError_t block_pre32(const Grid& g, const float* ub, const float* in, float* out, const float* f, float* ec,
+                       float* ehat, float* fc, hipStream_t s);
+hipError_t block_post32(const Grid& g, const float* ub, const float* in, float* out, const float* f, const float* ec,
+                        const float* ehat, hipStream_t s);
 
 // d = L(u) - f at every cell.
 hipError_t residual_field(const Grid& g, const double* u, const double* src, double* d,

@@ -99,6 +99,14 @@ bool tail_from(const mgfr_opts* o, size_t m, int n, size_t nlev)
     return n <= mgfr::domain_tail_n() && !(m == 0 && (o->flags & MGFR_PROFILE));
 }
 
+// Whether level m (side n) of a V-cycle is relaxed in blocks: two sweeps on either side of the coarse
+// step; on the finest level none that are timed or whose form the options choose.
+bool in_blocks(const mgfr_opts* o, size_t m, int n, size_t nlev)
+{
+    return mgfr::block_level(n) && m + 1 < nlev && o->pre == 2 && o->post == 2 &&
+           !(m == 0 && ((o->flags & MGFR_PROFILE) || o->planes > 0 || o->tile > 0));
+}
+
 struct Cycle {
     mgfr_ctx* c;
     const Hier& h;
@@ -160,7 +168,8 @@ struct Cycle {
         return MGFR_OK;
     }
 
-    int vcycle(size_t m)
+    // fas: the level's right-hand side is still R d of the finer one (the tail forms it)
+    int vcycle(size_t m, bool fas = false)
     {
         Level& L = h.lv[m];
         const double* src = m == 0 ? finest_src : L.f;
@@ -170,13 +179,23 @@ struct Cycle {
                 c->stats.cell_updates += n;
                 if (k == 0) c->stats.finest_updates += n;
             }
-            return hip_check(c, mgfr::domain_tail(L.g, L.u, src, (int)(h.nlev - m), o->pre, o->post, o->coarsest_sweeps,
-                                                  o->coarsest_rtol, h.counter, s),
+            return hip_check(c, mgfr::domain_tail(L.g, L.u, src, fas, (int)(h.nlev - m), o->pre, o->post,
+                                                  o->coarsest_sweeps, o->coarsest_rtol, h.counter, s),
                              "domain_tail");
         }
         double* cur = L.u;
-        for (int k = 0; k < o->pre; ++k) MGFR_TRY(sweep(m, src, cur));
         Level& H = h.lv[m + 1];
+        const bool tail = tail_from(o, m + 1, H.g.n, h.nlev);
+        if (!o_simple && !o_fused && in_blocks(o, m, L.g.n, h.nlev)) {
+            double* second = L.alt ? L.alt : L.blk;
+            MGFR_TRY(hip_check(c, mgfr::block_pre(L.g, L.u, second, src, H.u, H.uhat, H.f, s), "block_pre"));
+            if (!tail) MGFR_TRY(hip_check(c, mgfr::fas_rhs(H.g, H.uhat, H.f, s), "fas_rhs"));
+            MGFR_TRY(vcycle(m + 1, tail));
+            c->stats.cell_updates += 4 * mgfr::cells(L.g);
+            if (m == 0) c->stats.finest_updates += 4 * mgfr::cells(L.g);
+            return hip_check(c, mgfr::block_post(L.g, second, L.u, src, H.u, H.uhat, s), "block_post");
+        }
+        for (int k = 0; k < o->pre; ++k) MGFR_TRY(sweep(m, src, cur));
         if (L.alt && !o_simple) {
             mgfr::ResidStream a{};
             a.ti = mgfr::resid_stream_planes(L.g.n);
@@ -187,8 +206,8 @@ struct Cycle {
         } else {
             MGFR_TRY(hip_check(c, mgfr::resid_restrict(L.g, cur, src, H.u, H.uhat, H.f, s), "resid_restrict"));
         }
-        MGFR_TRY(hip_check(c, mgfr::fas_rhs(H.g, H.uhat, H.f, s), "fas_rhs"));
-        MGFR_TRY(vcycle(m + 1));
+        if (!tail) MGFR_TRY(hip_check(c, mgfr::fas_rhs(H.g, H.uhat, H.f, s), "fas_rhs"));
+        MGFR_TRY(vcycle(m + 1, tail));
         // u^h += P(u^H - R u^h)
         MGFR_TRY(hip_check(c, mgfr::prolong_correct(H.g, cur, H.u, H.uhat, s), "prolong_correct"));
         for (int k = 0; k < o->post; ++k) MGFR_TRY(sweep(m, src, cur));
@@ -243,7 +262,7 @@ struct Cycle32 {
         return MGFR_OK;
     }
 
-    int vcycle(size_t m)
+    int vcycle(size_t m, bool fas = false)
     {
         Level32& L = h.lv32[m];
         if (tail_from(o, m, L.g.n, h.nlev32)) {
@@ -252,16 +271,26 @@ struct Cycle32 {
                 c->stats.cell_updates += n;
                 if (k == 0) c->stats.finest_updates += n;
             }
-            return hip_check(c, mgfr::domain_tail32(L.g, L.ub, L.e, L.f, (int)(h.nlev32 - m), o->pre, o->post,
+            return hip_check(c, mgfr::domain_tail32(L.g, L.ub, L.e, L.f, fas, (int)(h.nlev32 - m), o->pre, o->post,
                                                     o->coarsest_sweeps, o->coarsest_rtol, s),
                              "domain_tail32");
         }
         float* cur = L.e;
-        for (int k = 0; k < o->pre; ++k) MGFR_TRY(sweep(m, cur));
         Level32& H = h.lv32[m + 1];
+        const bool tail = tail_from(o, m + 1, H.g.n, h.nlev32);
+        if (in_blocks(o, m, L.g.n, h.nlev32)) {
+            float* second = L.ealt ? L.ealt : L.eblk;
+            MGFR_TRY(hip_check(c, mgfr::block_pre32(L.g, L.ub, L.e, second, L.f, H.e, H.ehat, H.f, s), "block_pre32"));
+            if (!tail) MGFR_TRY(hip_check(c, mgfr::fas_rhs32(H.g, H.ub, H.ehat, H.f, s), "fas_rhs32"));
+            MGFR_TRY(vcycle(m + 1, tail));
+            c->stats.cell_updates += 4 * mgfr::cells(L.g);
+            if (m == 0) c->stats.finest_updates += 4 * mgfr::cells(L.g);
+            return hip_check(c, mgfr::block_post32(L.g, L.ub, second, L.e, L.f, H.e, H.ehat, s), "block_post32");
+        }
+        for (int k = 0; k < o->pre; ++k) MGFR_TRY(sweep(m, cur));
         MGFR_TRY(hip_check(c, mgfr::resid_restrict32(L.g, L.ub, cur, L.f, H.e, H.ehat, H.f, s), "resid_restrict32"));
-        MGFR_TRY(hip_check(c, mgfr::fas_rhs32(H.g, H.ub, H.ehat, H.f, s), "fas_rhs32"));
-        MGFR_TRY(vcycle(m + 1));
+        if (!tail) MGFR_TRY(hip_check(c, mgfr::fas_rhs32(H.g, H.ub, H.ehat, H.f, s), "fas_rhs32"));
+        MGFR_TRY(vcycle(m + 1, tail));
         // e^h += P(e^H - R e^h)
         MGFR_TRY(hip_check(c, mgfr::prolong_correct32(H.g, cur, H.e, H.ehat, s), "prolong_correct32"));
         for (int k = 0; k < o->post; ++k) MGFR_TRY(sweep(m, cur));
@@ -332,6 +361,7 @@ size_t carve(char* base, int N, int coarsest, bool mixed, Hier* h, Level* lv, Le
             L.f = (double*)take(sizeof(double) * n3);
         }
         if (n >= mgfr::fused_sweep_min_n()) L.alt = (double*)take(sizeof(double) * n3);
+        else if (mgfr::block_level(n)) L.blk = (double*)take(sizeof(double) * n3);
         lv[m] = L;
         if (mixed) {
             Level32 E{};
@@ -340,6 +370,7 @@ size_t carve(char* base, int N, int coarsest, bool mixed, Hier* h, Level* lv, Le
             E.f = (float*)take(sizeof(float) * n3);
             if (n < N) E.ehat = (float*)take(sizeof(float) * n3);
             if (n >= mgfr::fused_sweep_min_n()) E.ealt = (float*)take(sizeof(float) * n3);
+            else if (mgfr::block_level(n)) E.eblk = (float*)take(sizeof(float) * n3);
             lv32[m] = E;
         }
     }

@@ -22,8 +22,8 @@ __device__ __forceinline__ int element(int q)
 // the coarsest level's sweeps are added to *sweeps.
 template <int W>
 __global__ void __launch_bounds__(res::threads(W)) kd_tail64(Grid g, double* __restrict__ u,
-                                                            const double* __restrict__ src, int nl, res::Cfg cfg,
-                                                            long long* __restrict__ sweeps)
+                                                            const double* __restrict__ src, bool fas, int nl,
+                                                            res::Cfg cfg, long long* __restrict__ sweeps)
 {
     if (g.halt && *g.halt) return;
     constexpr int NT = res::threads(W);
@@ -36,6 +36,14 @@ __global__ void __launch_bounds__(res::threads(W)) kd_tail64(Grid g, double* __r
     }
     __syncthreads();
     const res::Op64 o{g.C, g.A, g.inv_np1, g.max_step};
+    if (fas) {  // L(R u) - R d
+        for (int q = threadIdx.x; q < cube(W); q += NT) {
+            int i, j, k;
+            res::cell_at<W>(q, i, j, k);
+            m.top.f[q] = res::cell64<W, true>(o, m.top.v, nullptr, q, i, j, k, m.top.f[q]).L;
+        }
+        __syncthreads();
+    }
     const int done = res::vcycle64<W, true, NT>(o, cfg, nl, m.top, m.below, m.red);
     for (int q = threadIdx.x; q < cube(W); q += NT) u[element<W>(q)] = m.top.v[q].x;
     if (threadIdx.x == 0) *sweeps += done;
@@ -45,7 +53,8 @@ __global__ void __launch_bounds__(res::threads(W)) kd_tail64(Grid g, double* __r
 // formed from ub.
 template <int W>
 __global__ void __launch_bounds__(res::threads(W)) kd_tail32(Grid g, const float* __restrict__ ub, float* __restrict__ e,
-                                                            const float* __restrict__ f, int nl, res::Cfg cfg)
+                                                            const float* __restrict__ f, bool fas, int nl,
+                                                            res::Cfg cfg)
 {
     if (g.halt && *g.halt) return;
     constexpr int NT = res::threads(W);
@@ -59,6 +68,14 @@ __global__ void __launch_bounds__(res::threads(W)) kd_tail32(Grid g, const float
         m.top.S_[q] = o.A * __expf(-b * o.inv_np1);
     }
     __syncthreads();
+    if (fas) {  // N(R e) - R d
+        for (int q = threadIdx.x; q < cube(W); q += NT) {
+            int i, j, k;
+            res::cell_at<W>(q, i, j, k);
+            m.top.f[q] = res::cell32<W, true>(o, m.top.v, m.top.S_, nullptr, q, i, j, k, m.top.f[q]).N;
+        }
+        __syncthreads();
+    }
     res::bases32<W, true, NT>(o, nl, m.top, m.below);
     res::vcycle32<W, true, NT>(o, cfg, nl, m.top, m.below, m.red);
     for (int q = threadIdx.x; q < cube(W); q += NT) e[element<W>(q)] = m.top.v[q].y;
@@ -68,12 +85,12 @@ __global__ void __launch_bounds__(res::threads(W)) kd_tail32(Grid g, const float
 
 int domain_tail_n() { return 16; }
 
-hipError_t domain_tail(const Grid& g, double* u, const double* src, int nl, int pre, int post, int cap, double rtol,
+hipError_t domain_tail(const Grid& g, double* u, const double* src, bool fas, int nl, int pre, int post, int cap, double rtol,
                        long long* sweeps, hipStream_t s)
 {
     const res::Cfg cfg{pre, post, cap, rtol};
     auto go = [&](auto kern, int nt) {
-        hipLaunchKernelGGL(kern, dim3(1), dim3(nt), 0, s, g, u, src, nl, cfg, sweeps);
+        hipLaunchKernelGGL(kern, dim3(1), dim3(nt), 0, s, g, u, src, fas, nl, cfg, sweeps);
         return hipGetLastError();
     };
     switch (g.n) {
@@ -85,12 +102,12 @@ hipError_t domain_tail(const Grid& g, double* u, const double* src, int nl, int 
     }
 }
 
-hipError_t domain_tail32(const Grid& g, const float* ub, float* e, const float* f, int nl, int pre, int post, int cap,
+hipError_t domain_tail32(const Grid& g, const float* ub, float* e, const float* f, bool fas, int nl, int pre, int post, int cap,
                          double rtol, hipStream_t s)
 {
     const res::Cfg cfg{pre, post, cap, rtol};
     auto go = [&](auto kern, int nt) {
-        hipLaunchKernelGGL(kern, dim3(1), dim3(nt), 0, s, g, ub, e, f, nl, cfg);
+        hipLaunchKernelGGL(kern, dim3(1), dim3(nt), 0, s, g, ub, e, f, fas, nl, cfg);
         return hipGetLastError();
     };
     switch (g.n) {
