@@ -29,8 +29,9 @@ hipError_t poisson_ngs_fused(const PGrid& g, const double* xin, double* xout, co
 // them automatic.
 int poisson_fused2_min_n();
 int poisson_fused2_planes(int n);
+// xc (may be null): start from xin + P(xc), xc on the level below; ti is even then.
 hipError_t poisson_ngs_fused2(const PGrid& g, const double* xin, double* xout, const double* b, double bmean, int ti,
-                              hipStream_t s);
+                              const double* xc, hipStream_t s);
 // bc = R (b - bmean - lap x) on the level below.
 hipError_t poisson_resid_restrict(const PGrid& g, const double* x, const double* b, double bmean, double* bc,
                                   hipStream_t s);

@@ -60,16 +60,21 @@ struct PCycle {
 
     // `count` sweeps: on levels with a second buffer as many two-sweep passes as fit, and single
     // sweeps (fused from poisson_fused_min_n() up, one launch per colour below) for the rest
-    int sweeps(size_t m, double*& cur, double bm, int count)
+    // xc: the correction of the level below, to be added first (null: none); the first pass adds
+    // it, or a launch of its own where there is none.
+    int sweeps(size_t m, double*& cur, double bm, int count, const double* xc = nullptr)
     {
         int k = 0;
-        if (c->plv[m].alt)
-            for (; k + 2 <= count; k += 2) MGFR_TRY(sweep(m, cur, bm, 2));
+        const bool pass = c->plv[m].alt && count >= 2;
+        if (xc && !pass)
+            MGFR_TRY(hip_check(c, mgfr::prolong_add_direct(coarse_grid(c->plv[m + 1].g), cur, xc, s), "prolong_add_direct"));
+        if (pass)
+            for (; k + 2 <= count; k += 2) MGFR_TRY(sweep(m, cur, bm, 2, k == 0 ? xc : nullptr));
         for (; k < count; ++k) MGFR_TRY(sweep(m, cur, bm, 1));
         return MGFR_OK;
     }
 
-    int sweep(size_t m, double*& cur, double bm, int passes)
+    int sweep(size_t m, double*& cur, double bm, int passes, const double* xc = nullptr)
     {
         mgfr_ctx::PLevel& L = c->plv[m];
         // MGFR_PROFILE: HIP events around every finest-level sweep, on the solve's stream
@@ -90,7 +95,7 @@ struct PCycle {
             const bool opt = m == 0 && o->planes > 0 && o->planes <= L.g.n;
             if (passes == 2) {
                 const int ti = opt ? o->planes : mgfr::poisson_fused2_planes(L.g.n);
-                MGFR_TRY(hip_check(c, mgfr::poisson_ngs_fused2(L.g, cur, out, L.b, bm, ti, s), "poisson_ngs_fused2"));
+                MGFR_TRY(hip_check(c, mgfr::poisson_ngs_fused2(L.g, cur, out, L.b, bm, ti, xc, s), "poisson_ngs_fused2"));
             } else {
                 const int ti = opt ? o->planes : mgfr::fused_sweep_planes(L.g.n);
                 MGFR_TRY(hip_check(c, mgfr::poisson_ngs_fused(L.g, cur, out, L.b, bm, ti, s), "poisson_ngs_fused"));
@@ -127,8 +132,7 @@ struct PCycle {
         MGFR_TRY(hip_check(c, mgfr::poisson_resid_restrict(L.g, cur, L.b, bm, H.b, s), "poisson_resid_restrict"));
         MGFR_TRY(hip_check(c, mgfr::fill(H.x, 0.0, 1LL << (3 * H.g.lg), s), "fill"));
         MGFR_TRY(vcycle(m + 1));
-        MGFR_TRY(hip_check(c, mgfr::prolong_add_direct(coarse_grid(H.g), cur, H.x, s), "prolong_add_direct"));
-        MGFR_TRY(sweeps(m, cur, bm, o->post));
+        MGFR_TRY(sweeps(m, cur, bm, o->post, H.x));
         if (cur != x)
             MGFR_TRY(hip_check(c, hipMemcpyAsync(x, cur, sizeof(double) * ((size_t)1 << (3 * L.g.lg)),
                                                  hipMemcpyDeviceToDevice, s),
@@ -209,8 +213,8 @@ int mg_poisson_solve(mgfr_ctx* c, const double* rho, const double* u, int N, con
     MGFR_TRY(cyc.norm(nullptr, &ref, &mx));  // rms of the source about its mean
     const double target = o->tol * ref;
     int k = 0, status = MGFR_OK;
-    double rms;
-    MGFR_TRY(cyc.norm(phi, &rms, &mx));
+    double rms = ref;  // the residual of a zero potential
+    if (o->flags & MGFR_WARM_START) MGFR_TRY(cyc.norm(phi, &rms, &mx));
     if (res_hist) res_hist[0] = rms;
     while (rms > target) {
         if (!std::isfinite(rms)) {
@@ -277,7 +281,7 @@ int mg_poisson_smooth(mgfr_ctx* c, const double* rho, const double* u, int N, co
             MGFR_TRY(hip_check(c, mgfr::poisson_ngs_fused(L0.g, cur, out, L0.b, mean, mgfr::fused_sweep_planes(N), s),
                                "poisson_ngs_fused"));
         else
-            MGFR_TRY(hip_check(c, mgfr::poisson_ngs_fused2(L0.g, cur, out, L0.b, mean, mgfr::poisson_fused2_planes(N), s),
+            MGFR_TRY(hip_check(c, mgfr::poisson_ngs_fused2(L0.g, cur, out, L0.b, mean, mgfr::poisson_fused2_planes(N), nullptr, s),
                                "poisson_ngs_fused2"));
         if (variant > 0) cur = out;
     }
