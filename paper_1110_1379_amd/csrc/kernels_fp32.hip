@@ -252,7 +252,9 @@ __device__ __forceinline__ float k_pair(float v)
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xb1, 0xf, 0xf, true));  // [1,0,3,2]
 }
 
-template <int TJ, int NT>
+// FAS: instead of the restriction fc = N(e) - fc in place, the right-hand side of a coarse level (f is
+// not read): 256^3 64 us, 142 with one thread per cell.
+template <int TJ, int NT, bool FAS = false>
 __global__ void __launch_bounds__(NT) k32_resid_stream(Grid g, const float* __restrict__ ub, const float* __restrict__ e,
                                                        const float* __restrict__ f, float* __restrict__ ec,
                                                        float* __restrict__ ehat, float* __restrict__ fc, int ti,
@@ -274,10 +276,11 @@ __global__ void __launch_bounds__(NT) k32_resid_stream(Grid g, const float* __re
     const int lg = g.lg, m = g.n - 1;
     const int last = i0 + ti;  // last plane read
     const int t = threadIdx.x;
+    const float* fsrc = FAS ? fc : f;
 
     // A plane's pointer is scalar and a column's byte offset fits in 32 bits (n <= 1024); both are
     // opaque, or the compiler keeps a 64-bit pointer per column and array and adds to it.
-    auto at2 = [&](const float* a, int p, unsigned col) -> float {
+    auto at2 = [&](const float* a, int p, unsigned col) -> auto& {
         using gptr = __attribute__((address_space(1))) char*;
         gptr b = (gptr)(a + ((size_t)(p & m) << (2 * lg)));
         unsigned d = col * (unsigned)sizeof(float);
@@ -310,8 +313,8 @@ __global__ void __launch_bounds__(NT) k32_resid_stream(Grid g, const float* __re
         q.v0 = make_v(at2(ub, i0, q.col), at2(e, i0, q.col));
         q.vp = make_v(at2(ub, i0 + 1, q.col), at2(e, i0 + 1, q.col));
         request(q, 0, i0 + 2);
-        q.f[0] = at2(f, i0, q.col);
-        q.f[1] = at2(f, i0 + 1, q.col);
+        q.f[0] = at2(fsrc, i0, q.col);
+        q.f[1] = at2(fsrc, i0 + 1, q.col);
         lv[0][q.c] = q.v0;
     };
     prologue(X);
@@ -335,14 +338,17 @@ __global__ void __launch_bounds__(NT) k32_resid_stream(Grid g, const float* __re
         const V32* L = lv[N];
         auto residual = [&](const ColR32& q, const V32& jm, const V32& jp) -> float {
             const V32 nbv[6] = {q.vm, q.vp, jm, jp, L[q.c - 1], L[q.c + 1]};
-            return dev32::corr_op(o, q.v0, nbv, q.f[N]).N;
+            const float d = dev32::corr_op(o, q.v0, nbv, FAS ? 0.0f : q.f[N]).N;
+            if constexpr (FAS) at2(fc, p, q.col) = d - q.f[N];
+            return d;
         };
         const float dx = residual(X, L[X.c - LK], Y.v0);
         const float dy = residual(Y, X.v0, L[Y.c + LK]);
         const int pf = p + 2 < last ? p + 2 : last - 1;
-        X.f[N] = at2(f, pf, X.col);
-        Y.f[N] = at2(f, pf, Y.col);
-        if constexpr (N == 0) {
+        X.f[N] = at2(fsrc, pf, X.col);
+        Y.f[N] = at2(fsrc, pf, Y.col);
+        if constexpr (FAS) {
+        } else if constexpr (N == 0) {
             X.eq = X.v0.e;
             X.dq = dx;
             Y.eq = Y.v0.e;
@@ -499,19 +505,23 @@ hipError_t ngs_sweep32_fused(const Grid& g, const float* ub, const float* ein, f
     return hipGetLastError();
 }
 
+template <bool FAS>
+hipError_t stream32(const Grid& g, const float* ub, const float* e, const float* f, float* ec, float* ehat, float* fc,
+                    hipStream_t s)
+{
+    constexpr int TJ = 8, NT = 256;
+    const int ntj = g.n / TJ, ntk = g.n / kTK;
+    int ti = 8;
+    while (ti < g.n && (long long)ntj * ntk * (g.n / ti) > 8192) ti *= 2;
+    const unsigned nb = (unsigned)((g.n / ti) * ntj * ntk);
+    hipLaunchKernelGGL((k32_resid_stream<TJ, NT, FAS>), dim3(nb), dim3(NT), 0, s, g, ub, e, f, ec, ehat, fc, ti, ntj, ntk);
+    return hipGetLastError();
+}
+
 hipError_t resid_restrict32(const Grid& g, const float* ub, const float* e, const float* f, float* ec,
                             float* ehat, float* fc, hipStream_t s)
 {
-    if (g.n >= kTK) {
-        constexpr int TJ = 8, NT = 256;
-        const int ntj = g.n / TJ, ntk = g.n / kTK;
-        int ti = 8;
-        while (ti < g.n && (long long)ntj * ntk * (g.n / ti) > 8192) ti *= 2;
-        const unsigned nb = (unsigned)((g.n / ti) * ntj * ntk);
-        hipLaunchKernelGGL((k32_resid_stream<TJ, NT>), dim3(nb), dim3(NT), 0, s, g, ub, e, f, ec, ehat, fc, ti, ntj,
-                           ntk);
-        return hipGetLastError();
-    }
+    if (g.n >= kTK) return stream32<false>(g, ub, e, f, ec, ehat, fc, s);
     hipLaunchKernelGGL(k32_resid_restrict, dim3(blocks_for(cells(g) / 8)), dim3(kBlock), 0, s, g, ub, e, f, ec,
                        ehat, fc);
     return hipGetLastError();
@@ -519,6 +529,9 @@ hipError_t resid_restrict32(const Grid& g, const float* ub, const float* e, cons
 
 hipError_t fas_rhs32(const Grid& gc, const float* ubc, const float* ehat, float* f, hipStream_t s)
 {
+    // one thread per cell forms seven cells' exponentials; streamed each cell's are formed once.  At
+    // 64^3 the 64 workgroups of that are too few (a solve at 128^3 1.97 ms against 1.93).
+    if (gc.n >= 2 * kTK) return stream32<true>(gc, ubc, ehat, nullptr, nullptr, nullptr, f, s);
     hipLaunchKernelGGL(k32_fas_rhs, dim3(blocks_for(cells(gc))), dim3(kBlock), 0, s, gc, ubc, ehat, f);
     return hipGetLastError();
 }

@@ -334,6 +334,9 @@ hipError_t resid_restrict(const Grid& g, const double* u, const double* src, dou
 
 hipError_t fas_rhs(const Grid& gc, const double* uhat, double* f, hipStream_t s)
 {
+    // one thread per cell forms seven exponentials; streamed each is formed once: 256^3 80 against 147
+    // us.  At 64^3 the 64 workgroups of that are too few.
+    if (gc.n >= 128 && gc.n <= 1024) return fas_stream(gc, uhat, f, s);
     hipLaunchKernelGGL(k_fas_rhs, dim3(blocks_for(cells(gc))), dim3(kBlock), 0, s, gc, uhat, f);
     return hipGetLastError();
 }

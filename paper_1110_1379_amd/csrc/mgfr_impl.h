@@ -267,6 +267,8 @@ hipError_t resid_restrict(const Grid& g, const double* u, const double* src, dou
 
 // FAS right-hand side on a coarse level: f = L^H(uhat) - f (f holds R d on entry).
 hipError_t fas_rhs(const Grid& gc, const double* uhat, double* f, hipStream_t s);
+// The same streamed (resid_fp64.hip), 64 <= gc.n <= 1024.
+hipError_t fas_stream(const Grid& gc, const double* uhat, double* f, hipStream_t s);
 
 // Coarse-grid correction uf += P(uc - uhat), cell-centred trilinear 27/9/3/1 over 64,
 // periodic; gc is the coarse level, 2 <= gc.n <= 512 (prolong.hip).

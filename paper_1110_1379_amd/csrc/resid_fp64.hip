@@ -10,6 +10,7 @@
 //             loop) for every loaded cell; the updated tile is written to uout
 //   CAST      r = -d and ub = u rounded to single precision (right-hand side and base of
 //             the next single-precision correction solve)
+//   FAS       f = L(u) - f in place (fc), the right-hand side of a coarse level
 #include <type_traits>
 
 #include "device_fp64.h"
@@ -55,7 +56,7 @@ __device__ __forceinline__ double k_pair(double v)
 // cast 0.730 ms, with the correction 1.002 ms (4.4 and 4.8 TB/s); with the tile and its halo in three
 // slots of a thread, a third of whose lanes evaluated nothing, and the loads behind branches 0.655,
 // 0.779, 0.908 and 1.129 ms.
-template <int TJ, int NT, bool NORM, bool RESTRICT, bool UPDATE, bool CAST>
+template <int TJ, int NT, bool NORM, bool RESTRICT, bool UPDATE, bool CAST, bool FAS = false>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4)))
 k_resid_stream(Grid g, const double* __restrict__ uin, const double* __restrict__ src, ResidStream a)
 {
@@ -75,6 +76,7 @@ k_resid_stream(Grid g, const double* __restrict__ uin, const double* __restrict_
     const int lg = g.lg, m = g.n - 1;
     const int last = i0 + a.ti;  // last plane read
     const int t = threadIdx.x;
+    const double* fsrc = FAS ? a.fc : src;
 
     // A plane's pointer is scalar and a column's byte offset fits in 32 bits (n <= 1024); both are
     // opaque, or the compiler keeps a 64-bit pointer per column and array and adds to it.
@@ -121,8 +123,8 @@ k_resid_stream(Grid g, const double* __restrict__ uin, const double* __restrict_
         q.u0 = load_u(i0, q.col);
         q.up = load_u(i0 + 1, q.col);
         request(q, 0, i0 + 2);
-        q.f[0] = ref(src, i0, q.col);
-        q.f[1] = ref(src, i0 + 1, q.col);
+        q.f[0] = ref(fsrc, i0, q.col);
+        q.f[1] = ref(fsrc, i0 + 1, q.col);
         q.bm = dev::exp_(q.um);
         q.b0 = dev::exp_(q.u0);
         q.bp = dev::exp_(q.up);
@@ -153,8 +155,9 @@ k_resid_stream(Grid g, const double* __restrict__ uin, const double* __restrict_
             const double2 km = L[q.c - 1], kp = L[q.c + 1];
             const double un[6] = {q.um, q.up, jm.x, jp.x, km.x, kp.x};
             const double bn[6] = {q.bm, q.bp, jm.y, jp.y, km.y, kp.y};
-            double d = dev::cell_op_b(g, q.u0, q.b0, un, bn, dev::rhs_value(g, q.f[N])).L;
+            double d = dev::cell_op_b(g, q.u0, q.b0, un, bn, FAS ? 0.0 : dev::rhs_value(g, q.f[N])).L;
             asm volatile("" : "+v"(d));  // one column after the other: interleaved, they spill
+            if constexpr (FAS) ref(a.fc, p, q.col) = d - q.f[N];
             if constexpr (NORM) {
                 acc += d * d;
                 const double ad = fabs(d);
@@ -170,8 +173,8 @@ k_resid_stream(Grid g, const double* __restrict__ uin, const double* __restrict_
         const double dx = residual(X, L[X.c - LK], make_double2(Y.u0, Y.b0));
         const double dy = residual(Y, make_double2(X.u0, X.b0), L[Y.c + LK]);
         const int pf = p + 2 < last ? p + 2 : last - 1;
-        X.f[N] = ref(src, pf, X.col);
-        Y.f[N] = ref(src, pf, Y.col);
+        X.f[N] = ref(fsrc, pf, X.col);
+        Y.f[N] = ref(fsrc, pf, Y.col);
         if constexpr (RESTRICT) {
             if constexpr (N == 0) {
                 X.uq = X.u0;
@@ -260,6 +263,18 @@ int resid_stream_planes(int n)
 }
 
 long long resid_stream_blocks(int n) { return (long long)(n / resid_stream_planes(n)) * (n / kTJ) * (n / kTK); }
+
+hipError_t fas_stream(const Grid& g, const double* uhat, double* f, hipStream_t s)
+{
+    ResidStream a{};
+    a.ti = resid_stream_planes(g.n);
+    a.fc = f;
+    a.ntj = g.n / kTJ;
+    a.ntk = g.n / kTK;
+    hipLaunchKernelGGL((k_resid_stream<kTJ, kNT, false, false, false, false, true>),
+                       dim3((unsigned)resid_stream_blocks(g.n)), dim3(kNT), 0, s, g, uhat, (const double*)nullptr, a);
+    return hipGetLastError();
+}
 
 hipError_t resid_stream(const Grid& g, const double* uin, const double* src, ResidStream a, hipStream_t s)
 {
