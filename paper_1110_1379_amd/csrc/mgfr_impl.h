@@ -35,10 +35,12 @@ hipError_t poisson_ngs_fused2(const PGrid& g, const double* xin, double* xout, c
 // bc = R (b - bmean - lap x) on the level below.
 hipError_t poisson_resid_restrict(const PGrid& g, const double* x, const double* b, double bmean, double* bc,
                                   hipStream_t s);
-// Coarsest level (n <= 8) in one workgroup: x relaxed against b - bmean until rms <= rtol x
-// initial (or its rounding floor, or cap sweeps).
-hipError_t poisson_coarsest(const PGrid& g, double* x, const double* b, double bmean, int cap, double rtol,
-                            hipStream_t s);
+// One V-cycle of the nl levels from g (side <= poisson_tail_n()) down in one launch (poisson_tail.hip),
+// the coarsest (side 2 - 8) relaxed until rms <= rtol x initial, or its rounding floor, or cap sweeps;
+// x starts from zero if `zero`.
+int poisson_tail_n();
+hipError_t poisson_tail(const PGrid& g, double* x, const double* b, double bmean, bool zero, int nl, int pre, int post,
+                        int cap, double rtol, hipStream_t s);
 // x += v.
 hipError_t poisson_add(double* x, double v, long long n, hipStream_t s);
 

@@ -118,19 +118,33 @@ struct PCycle {
 
     double* finest_x = nullptr;
 
+    bool in_tail(size_t m) const
+    {
+        return m + 1 == c->plv.size() ||
+               (c->plv[m].g.n <= mgfr::poisson_tail_n() && !(m == 0 && (o->flags & MGFR_PROFILE)));
+    }
+
     int vcycle(size_t m)
     {
         mgfr_ctx::PLevel& L = c->plv[m];
         double* x = m == 0 ? finest_x : L.x;
         const double bm = m == 0 ? mean0 : 0.0;
-        if (m + 1 == c->plv.size())
-            return hip_check(c, mgfr::poisson_coarsest(L.g, x, L.b, bm, o->coarsest_sweeps, o->coarsest_rtol, s),
-                             "poisson_coarsest");
+        // the levels of side <= 16 (a finest one only if its launches are not timed) in one launch
+        if (in_tail(m)) {
+            for (size_t k = m; k + 1 < c->plv.size(); ++k) {
+                const long long n = (long long)(o->pre + o->post) * (1LL << (3 * c->plv[k].g.lg));
+                c->stats.cell_updates += n;
+                if (k == 0) c->stats.finest_updates += n;
+            }
+            return hip_check(c, mgfr::poisson_tail(L.g, x, L.b, bm, m > 0, (int)(c->plv.size() - m), o->pre, o->post,
+                                                   o->coarsest_sweeps, o->coarsest_rtol, s),
+                             "poisson_tail");
+        }
         mgfr_ctx::PLevel& H = c->plv[m + 1];
         double* cur = x;
         MGFR_TRY(sweeps(m, cur, bm, o->pre));
         MGFR_TRY(hip_check(c, mgfr::poisson_resid_restrict(L.g, cur, L.b, bm, H.b, s), "poisson_resid_restrict"));
-        MGFR_TRY(hip_check(c, mgfr::fill(H.x, 0.0, 1LL << (3 * H.g.lg), s), "fill"));
+        if (!in_tail(m + 1)) MGFR_TRY(hip_check(c, mgfr::fill(H.x, 0.0, 1LL << (3 * H.g.lg), s), "fill"));
         MGFR_TRY(vcycle(m + 1));
         MGFR_TRY(sweeps(m, cur, bm, o->post, H.x));
         if (cur != x)

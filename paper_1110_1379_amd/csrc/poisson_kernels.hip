@@ -626,70 +626,6 @@ __global__ void __launch_bounds__(NT) kp_resid_stream(PGrid g, const double* __r
     }
 }
 
-// ---- coarsest level in one workgroup (n <= 8) --------------------------------------------
-// Gauss-Seidel until rms(residual) <= rtol x initial, or down to its rounding floor, or cap
-// sweeps.  The periodic Laplacian has the constant null mode; the restricted residual has
-// zero mean, and the constant part of x is irrelevant (the potential's mean is fixed last).
-__global__ void __launch_bounds__(kB) kp_coarsest(PGrid g, double* __restrict__ x, const double* __restrict__ b,
-                                                  double bmean, int cap, double rtol)
-{
-    __shared__ double sx[512], sb[512];
-    __shared__ double ra[kB], rb[kB];
-    const int nc = 1 << (3 * g.lg), m = g.n - 1;
-    for (int q = threadIdx.x; q < nc; q += kB) {
-        sx[q] = x[q];
-        sb[q] = b[q] - bmean;
-    }
-    __syncthreads();
-    auto nsum = [&](int q) {
-        const int i = q >> (2 * g.lg), j = (q >> g.lg) & m, k = q & m;
-        return sx[at3(g.lg, (i + 1) & m, j, k)] + sx[at3(g.lg, (i - 1) & m, j, k)] + sx[at3(g.lg, i, (j + 1) & m, k)] +
-               sx[at3(g.lg, i, (j - 1) & m, k)] + sx[at3(g.lg, i, j, (k + 1) & m)] + sx[at3(g.lg, i, j, (k - 1) & m)];
-    };
-    auto rms = [&](double& floor) {
-        double s = 0.0, fl = 0.0;
-        for (int q = threadIdx.x; q < nc; q += kB) {
-            const double ns = nsum(q);
-            const double r = sb[q] - (ns - 6.0 * sx[q]) * g.inv_hh;
-            s += r * r;
-            const double f1 = 2.220446049250313e-16 * ((fabs(ns) + 6.0 * fabs(sx[q])) * g.inv_hh + fabs(sb[q]));
-            fl += f1 * f1;
-        }
-        ra[threadIdx.x] = s;
-        rb[threadIdx.x] = fl;
-        __syncthreads();
-        for (int w = kB / 2; w > 0; w >>= 1) {
-            if (threadIdx.x < w) {
-                ra[threadIdx.x] += ra[threadIdx.x + w];
-                rb[threadIdx.x] += rb[threadIdx.x + w];
-            }
-            __syncthreads();
-        }
-        const double ts = ra[0], tf = rb[0];
-        __syncthreads();
-        floor = sqrt(tf / nc);
-        return sqrt(ts / nc);
-    };
-    double fl0;
-    const double r0 = rtol > 0.0 ? rms(fl0) : 0.0;
-    for (int sweep = 0; sweep < cap; ++sweep) {
-        if (rtol > 0.0) {
-            double fl;
-            const double r = rms(fl);
-            if (r <= rtol * r0 || r <= fl) break;
-        }
-        for (int colour = 0; colour < 2; ++colour) {
-            for (int q = threadIdx.x; q < nc; q += kB) {
-                const int i = q >> (2 * g.lg), j = (q >> g.lg) & m, k = q & m;
-                if (((i + j + k) & 1) != colour) continue;
-                sx[q] = (nsum(q) - g.hh * sb[q]) * (1.0 / 6.0);
-            }
-            __syncthreads();
-        }
-    }
-    for (int q = threadIdx.x; q < nc; q += kB) x[q] = sx[q];
-}
-
 __global__ void __launch_bounds__(kB) kp_add(double* __restrict__ x, double v, long long n)
 {
     for (long long q = (long long)blockIdx.x * kB + threadIdx.x; q < n; q += (long long)gridDim.x * kB) x[q] += v;
@@ -804,14 +740,6 @@ hipError_t poisson_resid_restrict(const PGrid& g, const double* x, const double*
     }
     const long long ncell = 1LL << (3 * (g.lg - 1));
     hipLaunchKernelGGL(kp_resid_restrict, dim3((unsigned)((ncell + kB - 1) / kB)), dim3(kB), 0, s, g, x, b, bmean, bc);
-    return hipGetLastError();
-}
-
-hipError_t poisson_coarsest(const PGrid& g, double* x, const double* b, double bmean, int cap, double rtol,
-                            hipStream_t s)
-{
-    if (g.n > 8) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(kp_coarsest, dim3(1), dim3(kB), 0, s, g, x, b, bmean, cap, rtol);
     return hipGetLastError();
 }
 

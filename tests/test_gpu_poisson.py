@@ -215,3 +215,24 @@ def test_two_sweep_pass_does_not_depend_on_its_plane_chunks(mg, ctx, N):
         say(f"[poisson] N={N} planes={planes}")
         ref = phi if ref is None else ref
         assert torch.equal(phi, ref)
+
+
+@pytest.mark.parametrize("N", [16, 32])
+@pytest.mark.parametrize("coarsest,pre,post", [(2, 2, 2), (4, 1, 2), (8, 3, 1)])
+def test_small_levels_in_one_launch_match_oracle(mg, ctx, N, coarsest, pre, post):
+    """The levels of side <= 16 in one launch: a coarsest level within a wavefront (2 and 4) and one
+    of 512 cells, the finest level among them (16) and not, from zero and from a warm start."""
+    model = O.Model(box_mpc_h=2.0 * N, fr0_abs=1e-5)
+    params = mg.Params(box_mpc_h=2.0 * N, fr0_abs=1e-5)
+    rho = inputs.small_box(N, 0)
+    u = synthetic_u(model, N, seed=N)
+    ref = P.solve(P.source(rho, u, model))
+    opts = mg.mgfr_default_opts(tol=1e-12, max_cycles=60, coarsest_n=coarsest, pre=pre, post=post)
+    phi, hist, st = mg.mg_poisson_solve(ctx, dev(rho), dev(u), params, opts)
+    assert st == mg.MGFR_OK, (ctx.last_error(), hist)
+    assert np.abs(phi.cpu().numpy() - ref).max() <= 1e-10 * np.abs(ref).max()
+    warm = mg.mgfr_default_opts(tol=1e-12, max_cycles=60, coarsest_n=coarsest, pre=pre, post=post,
+                                flags=mg.MGFR_WARM_START)
+    again, hist, st = mg.mg_poisson_solve(ctx, dev(rho), dev(u), params, warm, phi=dev(0.5 * ref))
+    assert st == mg.MGFR_OK, (ctx.last_error(), hist)
+    assert np.abs(again.cpu().numpy() - ref).max() <= 1e-10 * np.abs(ref).max()
