@@ -38,28 +38,28 @@ METRIC = "f(R) MG time-to-residual 1e-8 & cell-updates/s, 512^3, FP64 vs mixed"
 # by-value kernel types): when any of them differs the figure no longer describes the kernel
 # that runs and `traffic` is reported as null.
 MEASURED_TRAFFIC = {
-    # per finest launch (one red-black sweep of the correction, 16 x 64 tiles), at 64 and 32
+    # per finest launch (one red-black sweep of the correction, 16 x 64 tiles), at 256 and 128
     # planes per workgroup
-    "mixed": {"points": [({"planes": 64, "tile": 3}, 3.5597e9), ({"planes": 32, "tile": 3}, 3.0682e9)],
+    "mixed": {"points": [({"planes": 256, "tile": 3}, 3.0097e9), ({"planes": 128, "tile": 3}, 2.9247e9)],
               "sources": {
-                  "kernels_fp32.hip": "3e2d5fa7b74c8e9e8695fb1c7fd7f008127e8b020b552ac5893de6581d7cd948",
-                  "fused_fp32.h": "b9ed53a6627e0abd80a493c36476053bfd8d2a934debc47118343d03e6ed03ca",
-                  "device_fp32.h": "d5b6a8e51761f987af9084e51f4c3970ee35457c72c0a474d5c42afb25ff1921",
+                  "kernels_fp32.hip": "b7d7786d045b6a4ca853e6cf2dfa4d3ba612eca34c8aeae6156c99b924089f79",
+                  "fused_fp32.h": "488b5d6971b3849dde3ba5e430a632b7e3cf7795719f750d03e891bbe6eb37f5",
+                  "device_fp32.h": "c1d418ffe3a2ac7a1c4af35beb1a85ee0f04ea283dc943ae4683c431f992ed16",
                   "kernel_types.h": "21ac1843e9d4b3e18646111fcbd3ff3b7e20b75086410058eb389d6397f79ef6"}},
     # per finest launch (one red-black sweep, 16 x 64 tiles, 128 planes per workgroup)
-    "fp64": {"points": [({"planes": 128, "tile": 1}, 3.4275e9)], "sources": {
-        "sweep_fp64.hip": "52fc69d7da60d3ca2f99db208d943e175ded4ad6bf8ace4cd379e03154f184c8",
-        "device_fp64.h": "45739fd671f614d6a70c9201b41df3c5734bf39dd756f08db278f61fa5027ac7",
+    "fp64": {"points": [({"planes": 128, "tile": 1}, 4.0327e9)], "sources": {
+        "sweep_fp64.hip": "b1ff22b6883fb25a408feccaeeb902de200d32f6b16c493b1c0af74b12734402",
+        "device_fp64.h": "402e5f8d6911312325571bcbba1f25300ddfc9d029d3b26c8591b7a4a735b0f6",
         "kernel_types.h": "21ac1843e9d4b3e18646111fcbd3ff3b7e20b75086410058eb389d6397f79ef6"}},
     # per sweep (one launch of the fused masked sweep, byte flags)
-    "masked": {"bytes": 4.995e9, "sources": {
-        "masked.hip": "6d044054bb4f6a7c5c48cc0c85298a8667acd115f241463a6694d6092d87489c",
-        "masked_solver.hip": "966744ac3561f1ca7912ab5e2f3f4cb699879477b5a7f0d61b1cdd7d0d0be3ad",
-        "device_fp64.h": "45739fd671f614d6a70c9201b41df3c5734bf39dd756f08db278f61fa5027ac7",
+    "masked": {"bytes": 4.612e9, "sources": {
+        "masked.hip": "252aadb2eee339ffb453d65a21c6f8a6e388781aba9c0195b84690cb519db95b",
+        "masked_solver.hip": "65bbb87cdd4d4aa594023601babe2b80a775da2e451fe846b2ba7efd2551f9aa",
+        "device_fp64.h": "402e5f8d6911312325571bcbba1f25300ddfc9d029d3b26c8591b7a4a735b0f6",
         "kernel_types.h": "21ac1843e9d4b3e18646111fcbd3ff3b7e20b75086410058eb389d6397f79ef6"}},
     # per pass of two sweeps
-    "poisson": {"bytes": 3.6313e9, "sources": {
-        "poisson_kernels.hip": "8ef270f9a78d0ee210179a3dab0de7499c9764aa3bab3ed9d665d4bd122c4738",
+    "poisson": {"bytes": 3.7322e9, "sources": {
+        "poisson_kernels.hip": "901f046dc27443fcb5e3b827925816b5805e0d65d8a06134d2bbb229afed3a49",
         "kernel_types.h": "21ac1843e9d4b3e18646111fcbd3ff3b7e20b75086410058eb389d6397f79ef6"}},
 }
 
@@ -69,16 +69,16 @@ MEASURED_TRAFFIC = {
 # settings counted (FETCH_SIZE x 2 + WRITE_SIZE, copy-calibrated): mixed, the fused two-colour
 # launches (the last of each outer iteration also adds u += e); FP64, the one-colour launches
 BATCH_TRAFFIC = {
-    "mixed": {"bytes": 0.4292e9, "settings": (2, 2, 3), "sources": {
-        "batch_col.hip": "1c3ac948bf60869a2c8ef3224e9c0f6d227552121414c5f25f895ad53f76efdd",
-        "batch.hip": "d4f88b9b651180a5616915b3f59d1d0ad76b9174d50ddcf080ec8f068b5792b9",
-        "fused_fp32.h": "b9ed53a6627e0abd80a493c36476053bfd8d2a934debc47118343d03e6ed03ca",
-        "device_fp32.h": "d5b6a8e51761f987af9084e51f4c3970ee35457c72c0a474d5c42afb25ff1921",
-        "batch_dev.h": "de43e35ad4c4670dc0ee3196ac06e4ee6a59cd2320f45743b1b175dbf70de6f3"}},
-    "fp64": {"bytes": 0.9508e9, "settings": (1, 1, 1), "sources": {
-        "batch_col.hip": "1c3ac948bf60869a2c8ef3224e9c0f6d227552121414c5f25f895ad53f76efdd",
-        "batch.hip": "d4f88b9b651180a5616915b3f59d1d0ad76b9174d50ddcf080ec8f068b5792b9",
-        "batch_dev.h": "de43e35ad4c4670dc0ee3196ac06e4ee6a59cd2320f45743b1b175dbf70de6f3"}},
+    "mixed": {"bytes": 0.4538e9, "settings": (2, 2, 3), "sources": {
+        "batch_col.hip": "df07ee6829189cd0542c0af086d7d5fc3d4b66615c6f220fb68eed14fdf29228",
+        "batch.hip": "9d121d4eb2d78326ba57b0093e8c210bd7c7d0525a297b1ec587f0d66050fc57",
+        "fused_fp32.h": "488b5d6971b3849dde3ba5e430a632b7e3cf7795719f750d03e891bbe6eb37f5",
+        "device_fp32.h": "c1d418ffe3a2ac7a1c4af35beb1a85ee0f04ea283dc943ae4683c431f992ed16",
+        "batch_dev.h": "fdca5bf40d95d14b12e4f3f1fabcd46e32694cbf54b33679d66d5f6e0917dd58"}},
+    "fp64": {"bytes": 0.9509e9, "settings": (1, 1, 1), "sources": {
+        "batch_col.hip": "df07ee6829189cd0542c0af086d7d5fc3d4b66615c6f220fb68eed14fdf29228",
+        "batch.hip": "9d121d4eb2d78326ba57b0093e8c210bd7c7d0525a297b1ec587f0d66050fc57",
+        "batch_dev.h": "fdca5bf40d95d14b12e4f3f1fabcd46e32694cbf54b33679d66d5f6e0917dd58"}},
 }
 
 
@@ -735,8 +735,8 @@ def _batched_roofline(s, prec_name, unit_n=0, phases=False):
             "kernel": ("kc_ngs<P64> / kb_ngs (red-black Newton-Gauss-Seidel, one launch per colour: column tiles "
                        "for periodic boxes, one thread per cell for patches)" if fp64 else
                        "kf32_ngs / kb32_ngs (red-black Newton-Gauss-Seidel: periodic boxes both colours in one "
-                       "pass over column tiles, two launches per pair of sweeps; patches one launch per colour, "
-                       "one thread per cell)") +
+                       "pass over column tiles, one launch per sweep; patches alike, or one thread per "
+                       "cell where few tiles are at work)") +
                       " over the finest level of every unit" + ("" if phases else f" larger than {unit_n or 16}^3"),
             "bytes_per_cell": 24 if fp64 else 12, "launches": launches,
             "avg_launch_ms": s["sweep_ms"] / launches if launches else None,
