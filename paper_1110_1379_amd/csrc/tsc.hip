@@ -575,8 +575,12 @@ int mgfr_tsc_force(mgfr_ctx* c, const double* phi, int N, const double* pos, lon
     // the staging cost 0.12 - 0.15 ms more than the direct kernel at up to 2^18 particles and
     // nothing at 2^24.  So: at least 375 thousand jumps, 1% of the particles (in cell order
     // the direct kernel is the faster one, 5.9 against 6.2 ms at 512^3 without the sort), and
-    // 32 particles to a tile (62.5 KB staged for each).
-    bool tiles = N >= 64 && np < (1LL << 31) && np >= 32 * ntile && far >= 375000.0 && far > 0.01 * (double)np;
+    // 32 particles to a tile (62.5 KB staged for each).  At 64^3 from 2^20 particles on, where the
+    // sort takes its faster form: assignment and interpolation together 652 -> 440 us for 2^20
+    // scattered particles, but 464 -> 534 for 3 2^18 in lattice order with 30% in clumps and
+    // 412 -> 461 for 400 thousand scattered; at 128^3 2^19 scattered ones 745 -> 621.
+    bool tiles = N >= 64 && (N > 64 || np >= (1LL << 20)) && np < (1LL << 31) && np >= 32 * ntile &&
+                 far >= 375000.0 && far > 0.01 * (double)np;
     mgfr::SortBuffers b;
     if (tiles) {
         MGFR_TRY(hip_check(c, mgfr::sort_buffers(np, ntile, 3 * (lg - 4), s, &b), "radix_sort_pairs (size query)"));

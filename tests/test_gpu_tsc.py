@@ -86,15 +86,16 @@ def test_density_rows_of_several_segments(mg, ctx, N):
     assert err <= 1e-12 * ref.max()
 
 
-@pytest.mark.parametrize("N,layout", [(64, "uniform"), (128, "uniform"), (64, "two tiles"), (256, "corners")])
+@pytest.mark.parametrize("N,layout", [(64, "uniform"), (128, "uniform"), (64, "two tiles"), (256, "corners"),
+                                      (64, "many"), (128, "two tiles")])
 def test_force_of_scattered_particles(mg, ctx, N, layout):
-    """Particles in no order go through tiles of the potential staged in LDS (N >= 64, at least
-    375 thousand jumps and 32 particles per tile): every tile of a grid, more particles in a
-    tile than a workgroup takes, empty tiles between, particles on the tile and box edges, and
-    a ragged count; the sums are those of the direct path, so the bar is the same 1e-13."""
+    """Particles in no order go through tiles of the potential staged in LDS (N >= 128, or 64
+    from 2^20 particles; at least 375 thousand jumps and 32 particles per tile): every tile of
+    a grid, more particles in a tile than a workgroup takes, empty tiles between, particles on
+    the tile and box edges, and a ragged count; the sums are those of the direct path, so the bar is the same 1e-13."""
     say(f"[tsc] scattered {layout} on {N}^3")
     rng = np.random.default_rng(N)
-    n = 420_001
+    n = 1_048_577 if layout == "many" else 420_001
     pos = rng.random((n, 3))
     if layout == "two tiles":
         pos = pos * (16.0 / N)
