@@ -164,10 +164,11 @@ struct Op64 {
     double C, A, inv_np1, max_step;
 };
 
-// S = A exp(-u/(n+1)): for n = 1 through 1 / sqrt(b), as dev::curvature.
+// S = A exp(-u/(n+1)): for n = 1 through 1 / sqrt(b), as dev::curvature, but from u itself where b
+// is denormal or zero (u < -708), whose root has lost what u still holds.
 __device__ __forceinline__ double curvature(const Op64& o, double u, double b)
 {
-    if (o.inv_np1 == 0.5) {
+    if (o.inv_np1 == 0.5 && !(b < 2.2250738585072014e-308)) {
         double y = __builtin_amdgcn_rsq(b);
         double e = fma(-b * y, y, 1.0);
         y = fma(0.5 * y, e, y);

@@ -447,3 +447,29 @@ def test_the_first_overlapping_pair_of_patches_is_named(mg, ctx):
                 if all(abs(a - b) < 16 for a, b in zip(moved[p], moved[q])))
     with pytest.raises(mg.MgfrError, match="patches %d and %d overlap" % first):
         solve(moved)
+
+
+@pytest.mark.parametrize("engine", ENGINES, ids=[e[0] for e in ENGINES])
+def test_curvature_where_the_exponential_underflows(mg, ctx, engine):
+    """Boxes whose solution lies at u < -708, where b = exp(u) is denormal, and below -745, where it
+    is zero: the flux vanishes and every cell solves A exp(-u/2) = f by itself, also with n = 1,
+    whose curvature term is otherwise taken from b.  u has a spacing of 1.1e-13 there, and half of
+    that in u/2 moves the solution by as much: a Newton iteration ends within a few spacings, so the
+    bar is 1e-12."""
+    fr0 = 1e-306
+    sides, means = [8, 16, 16, 32, 64], [1e3, 1e9, 1e13, 1e11, 1e12]
+    rng = np.random.default_rng(21)
+    rhos = [m * (1.0 + 0.1 * rng.random((N, N, N))) for N, m in zip(sides, means)]
+    params = [mg.Params(box_mpc_h=float(N), fr0_abs=fr0) for N in sides]
+    opts = mg.mgfr_default_opts(tol=0.0, max_cycles=40, flags=engine[1], unit_n=engine[2])
+    us, hists, st = mg.mg_fr_solve_batch(ctx, [dev(r) for r in rhos], params, opts, raise_on_error=False)
+    assert st == mg.MGFR_ENOTCONV, (st, ctx.last_error())   # tol = 0 is never reached
+    lowest = 0.0
+    for N, rho, p, u in zip(sides, rhos, params, us):
+        c = mg.mgfr_constants(p, N)
+        ref = -2.0 * np.log((c["D"] * (rho - 1.0) + c["Sbar"]) / c["A"])
+        err = np.abs(u.cpu().numpy() - ref).max()
+        say(f"[underflow] {engine[0]} N={N} u in [{ref.min():.0f}, {ref.max():.0f}] max err {err:.1e}")
+        assert err <= 1e-12, (N, err)
+        lowest = min(lowest, ref.min())
+    assert lowest < -746.0
