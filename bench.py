@@ -51,12 +51,6 @@ MEASURED_TRAFFIC = {
         "sweep_fp64.hip": "b1ff22b6883fb25a408feccaeeb902de200d32f6b16c493b1c0af74b12734402",
         "device_fp64.h": "402e5f8d6911312325571bcbba1f25300ddfc9d029d3b26c8591b7a4a735b0f6",
         "kernel_types.h": "21ac1843e9d4b3e18646111fcbd3ff3b7e20b75086410058eb389d6397f79ef6"}},
-    # per sweep (one launch of the fused masked sweep, byte flags)
-    "masked": {"bytes": 4.612e9, "sources": {
-        "masked.hip": "252aadb2eee339ffb453d65a21c6f8a6e388781aba9c0195b84690cb519db95b",
-        "masked_solver.hip": "65bbb87cdd4d4aa594023601babe2b80a775da2e451fe846b2ba7efd2551f9aa",
-        "device_fp64.h": "402e5f8d6911312325571bcbba1f25300ddfc9d029d3b26c8591b7a4a735b0f6",
-        "kernel_types.h": "21ac1843e9d4b3e18646111fcbd3ff3b7e20b75086410058eb389d6397f79ef6"}},
     # per pass of two sweeps
     "poisson": {"bytes": 3.7322e9, "sources": {
         "poisson_kernels.hip": "901f046dc27443fcb5e3b827925816b5805e0d65d8a06134d2bbb229afed3a49",

@@ -292,3 +292,26 @@ def test_masked_maximum_size_all_active_sine(mg, ctx):
     assert err <= 1e-10
     del ud, u0
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("N", [32, 64, 128])
+@pytest.mark.parametrize("contrast", [1e20, -1e20])
+@pytest.mark.parametrize("fractional", [False, True])
+def test_diverged_solve_is_reported(mg, ctx, N, contrast, fractional):
+    """A density that throws the unbounded Newton steps out of range leaves NaN in every active
+    cell, half or all of them with the sign set: the cells stay active, the residual norm sees them
+    and the solve ends with MGFR_ENONFINITE; masked cells are unchanged."""
+    import torch
+    say(f"[masked] diverging N={N} contrast={contrast} fractional={fractional}")
+    mask = -np.ones((N, N, N), dtype=np.float32)
+    mask[8:24, 8:24, 8:24] = 1.0
+    if fractional:
+        mask *= 0.75
+    u0 = np.full((N, N, N), -11.0)
+    ud, hist, st = mg.mg_fr_solve_masked(ctx, dev(np.full((N, N, N), contrast)), dev(mask, torch.float32), dev(u0),
+                                         mg.Params(box_mpc_h=float(N), fr0_abs=1e-5),
+                                         mg.mgfr_default_opts(max_step=0.0), raise_on_error=False)
+    u = ud.cpu().numpy()
+    assert np.isnan(u[mask > 0]).all()
+    assert st == mg.MGFR_ENONFINITE and np.isnan(hist[-1])
+    assert np.array_equal(u[mask <= 0], u0[mask <= 0])
