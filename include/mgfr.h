@@ -380,7 +380,7 @@ int mgfr_tsc_density(mgfr_ctx* ctx, const double* pos, long long np, int N, doub
  * the same 27 TSC weights as mgfr_tsc_density, which makes the pair momentum conserving.
  * phi   device, N^3 doubles (e.g. from mg_poisson_solve), read.
  * pos   device, np x 3 doubles, read; acc: device, np x 3 doubles, written.
- * Many particles in an order that jumps about the box are sorted by tiles of the grid first
+ * Many particles, for the size of the grid, in an order that jumps about it are sorted by tiles first
  * (scratch of about 20 B per particle, kept in the context; without that much memory they are
  * taken as they come, with the same result).
  * Returns MGFR_ENONFINITE for a non-finite coordinate.  Synchronises once. */

@@ -64,8 +64,10 @@ __device__ __forceinline__ void tsc_weights(const double* __restrict__ p, int N,
 }
 
 // Block partials of one pass over the particles: the number of non-finite coordinates and the
-// number of particles that lie far (over kNear cells along i or j, 4 kNear along k) from the
-// particle before them in their wavefront.  KEYS: also the key (flat index of the nearest
+// number of particles that jump: that lie far (over kNear cells along i or j, 4 kNear along k) along
+// two axes or all from the particle before them in their wavefront.  (A step along one axis alone
+// is the order's own: few particles sorted by cell lie far apart in their rows, and share the
+// cache lines of the rows beside.)  KEYS: also the key (flat index of the nearest
 // cell) and identity index of every particle; a non-finite one gets some key of the grid.
 // Reading the positions bounds it (3.2 GB at 512^3 particles): one pass where the check and
 // the keys took one each (0.61 + 0.74 -> 0.88 ms).
@@ -102,13 +104,13 @@ __global__ void __launch_bounds__(kB) k_tsc_scan(const double* __restrict__ pos,
         }
         if (!KEYS) {
             // distance to the lane below, modulo N
-            bool away = false;
+            int away = 0;
 #pragma unroll
             for (int ax = 0; ax < 3; ++ax) {
                 const int d = (c[ax] - __shfl_up(c[ax], 1)) & m, near = ax < 2 ? kNear : 4 * kNear;
-                away = away || (d > near && d < N - near);
+                away += d > near && d < N - near;
             }
-            if (live && lane > 0 && away) ++nfar;
+            if (live && lane > 0 && away >= 2) ++nfar;
         }
     }
 #pragma unroll
@@ -423,8 +425,8 @@ int check_args(mgfr_ctx* c, const double* pos, long long np, int N)
 }
 
 // The pass over the positions (k_tsc_scan): non-finite ones would give arbitrary cells and are
-// refused; *far gets the number of particles far from the one before them, counted where no
-// keys are asked for (synchronises).
+// refused; *far gets the number of particles that jump, counted where no keys are asked for
+// (synchronises).
 int scan_positions(mgfr_ctx* c, const double* pos, long long np, int N, unsigned* key, unsigned* idx, double* far,
                    hipStream_t s)
 {
@@ -570,17 +572,25 @@ int mgfr_tsc_force(mgfr_ctx* c, const double* phi, int N, const double* pos, lon
     MGFR_TRY(mgfr::scan_positions(c, pos, np, N, nullptr, nullptr, &far, s));
     const int lg = ilog2(N);
     const long long ntile = (long long)(N / mgfr::kFT) * (N / mgfr::kFT) * (N / mgfr::kFT);
-    // Scattered particles go through the tiles: each costs the direct kernel 0.2 (64^3, the
-    // potential in L2) to 1 ns (256^3) for cache lines of its own, while the keys, the sort and
-    // the staging cost 0.12 - 0.15 ms more than the direct kernel at up to 2^18 particles and
-    // nothing at 2^24.  So: at least 375 thousand jumps, 1% of the particles (in cell order
-    // the direct kernel is the faster one, 5.9 against 6.2 ms at 512^3 without the sort), and
-    // 32 particles to a tile (62.5 KB staged for each).  At 64^3 from 2^20 particles on, where the
-    // sort takes its faster form: assignment and interpolation together 652 -> 440 us for 2^20
-    // scattered particles, but 464 -> 534 for 3 2^18 in lattice order with 30% in clumps and
-    // 412 -> 461 for 400 thousand scattered; at 128^3 2^19 scattered ones 745 -> 621.
-    bool tiles = N >= 64 && (N > 64 || np >= (1LL << 20)) && np < (1LL << 31) && np >= 32 * ntile &&
-                 far >= 375000.0 && far > 0.01 * (double)np;
+    // Scattered particles go through the tiles.  A jump costs the direct kernel 0.25 (128^3) to 1.1
+    // ns (512^3, no order at all) for cache lines of its own; the tiles cost the sort, 0.13 ms up to
+    // 2^20 particles and a fraction of that from there on, where it takes its faster form, and the
+    // staging, 7.5 ps for every cell of the grid however few particles it holds, and save 0.17 ns a
+    // particle besides.  So, direct and tile times in ms for one side and the other of each line:
+    //  - 375 thousand jumps: lattice order with clumps, 1.05 M particles, 64^3 with 169 thousand jumps
+    //    0.128, 0.144 and with 452 thousand 0.190, 0.146; 256^3 with 194 thousand 0.279, 0.313 and
+    //    with 522 thousand 0.391, 0.342; and 1% of the particles (in cell order 134 M at 512^3 take
+    //    6.45, 7.24, with 1% jumps among them 10.0, 7.52);
+    //  - a jump for every 50 cells, less 0.4 for every particle: 512^3 with 4 M particles and 0.75 M jumps
+    //    1.11, 1.19, with 1.41 M 1.45, 1.28; 1.05 M without order 1.17, 1.61, 2 M 2.17, 1.11; 1024^3 with
+    //    30 M and 5.6 M jumps 7.37, 8.41, with 15 M 12.8, 8.90;
+    //  - below 2^20 particles nine tenths of them and 128 particles to a tile, and none at 64^3: 256^3
+    //    with 800 thousand in lattice order with clumps, 82% jumps 0.40, 0.59, without order 0.87,
+    //    0.41, with 600 thousand 0.67, 0.45, with 400 thousand 0.46, 0.55; 64^3 without order 0.28, 0.24,
+    //    with assignment before it 400 thousand 0.41, 0.46.
+    bool tiles = N >= 64 && np < (1LL << 31) && far >= 375000.0 && far > 0.01 * (double)np &&
+                 far >= 0.02 * (double)N * N * N - 0.4 * (double)np &&
+                 (np >= (1LL << 20) || (N > 64 && far >= 0.9 * (double)np && np >= 128 * ntile));
     mgfr::SortBuffers b;
     if (tiles) {
         MGFR_TRY(hip_check(c, mgfr::sort_buffers(np, ntile, 3 * (lg - 4), s, &b), "radix_sort_pairs (size query)"));

@@ -209,3 +209,83 @@ def test_tsc_full_size(mg, ctx):
     ferr = np.abs(G[idx] - F).max()
     say(f"  sampled force max err {ferr:.2e}, bit-identical {np.array_equal(G[idx], F)}")
     assert ferr <= 1e-13 * N * np.abs(phi).max()
+
+
+def scattered(torch, N, n, order):
+    """n particle positions, uniform ("none"), sorted by cell ("cell"), or a lattice of them in its
+    order ("lattice") with 30% moved into 64 clumps two cells wide."""
+    g = torch.Generator(device="cuda:0").manual_seed(N)
+    pos = torch.rand((n, 3), generator=g, device="cuda:0", dtype=torch.float64)
+    if order == "cell":
+        c = (pos * N).to(torch.int64)
+        pos = pos[((c[:, 0] * N + c[:, 1]) * N + c[:, 2]).argsort()].contiguous()
+    elif order == "lattice":
+        side = int(np.ceil(n ** (1 / 3)))
+        i = torch.arange(n, device="cuda:0")
+        moved = pos[:, 0] < 0.3
+        clump = torch.randint(64, (n,), generator=g, device="cuda:0")
+        centre = torch.rand((64, 3), generator=g, device="cuda:0", dtype=torch.float64)
+        at = (torch.stack((i // side ** 2, i // side % side, i % side), 1).to(torch.float64) + 0.5) / side
+        pos = torch.where(moved[:, None], (centre[clump] + pos * (2.0 / N)).remainder(1.0), at)
+    return pos
+
+
+@pytest.mark.parametrize("N,n,order,tiles", [
+    (64, 1_048_577, "none", True), (64, 1_048_575, "none", False), (128, 400_001, "none", True),
+    (128, 350_001, "none", False), (128, 1_048_577, "lattice", True), (128, 1_048_575, "lattice", False),
+    (256, 800_001, "none", True), (256, 800_001, "lattice", False),
+    (256, 450_001, "none", False), (256, 4_000_001, "cell", False),
+    (512, 4_000_001, "cell", False), (512, 1_100_001, "none", False), (512, 4_000_001, "none", True)])
+def test_force_path_follows_the_order_and_the_density_of_the_particles(mg, N, n, order, tiles):
+    """Tiles for particles that jump about the box, if there are enough of them for the grid; the direct
+    kernel, which keeps no scratch, for the others: few particles sorted by cell, which lie far
+    apart in their rows, few in a large grid, and a set of less than 2^20 not wholly without order.
+    The tile path keeps its sort's buffers, 16 B a particle and more, in the context."""
+    import torch
+    warm, ctx = mg.Context(0), mg.Context(0)
+    g = torch.Generator(device="cuda:0").manual_seed(3)
+    phi = torch.randn((N, N, N), generator=g, device="cuda:0", dtype=torch.float64)
+    pos = scattered(torch, N, n, order)
+    few = pos[:1000].contiguous()
+    acc, acc_few = torch.empty_like(pos), torch.empty_like(few)
+    mg.mgfr_tsc_force(warm, phi, pos, acc=acc)     # the kernels are loaded
+    mg.mgfr_tsc_force(ctx, phi, few, acc=acc_few)  # and the context's reduction scratch is there
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    mg.mgfr_tsc_force(ctx, phi, pos, acc=acc)
+    torch.cuda.synchronize()
+    kept = before - torch.cuda.mem_get_info()[0]
+    say(f"[tsc path] {order} {n} on {N}^3: {kept / n:.1f} B a particle kept")
+    assert torch.equal(acc[:1000], acc_few)        # the sums do not depend on the path
+    assert kept >= 16 * n if tiles else kept < 4 * n
+    warm.close()
+    ctx.close()
+
+
+@pytest.mark.parametrize("N,layout", [(64, "two tiles"), (64, "one tile"), (512, "corners")])
+def test_force_through_wrapped_and_mostly_empty_tiles(mg, ctx, N, layout):
+    """The tile path with more particles than the 64^3 rule asks for, in two tiles of opposite corners
+    (the smallest tile grid, wrapped on all sides), in one, where nothing jumps and the direct
+    kernel runs, and on the cell and tile edges of a large grid; the bar is 1e-13 as for the others."""
+    import torch
+    rng = np.random.default_rng(N)
+    n = 1_048_577 if N == 64 else 3_000_001
+    pos = rng.random((n, 3))
+    if N == 512:
+        pos = np.round(pos * (N // 16)) / (N // 16)
+        pos[1::3] = np.nextafter(pos[1::3], 2.0)
+        pos[2::3] = np.nextafter(pos[2::3], -1.0)
+    else:
+        pos *= 16.0 / N
+        if layout == "two tiles":
+            pos[1::2] += 1.0 - 16.0 / N
+    phi = rng.standard_normal((N, N, N)) if N == 64 else None
+    if phi is None:  # a smooth field of the coordinates, cheap to make
+        x = np.sin(2 * np.pi * np.arange(N) / N)
+        phi = x[:, None, None] + 0.5 * x[None, ::-1, None] * x[:, None, None] + 0.25 * np.cos(x)[None, None, :]
+    pick = np.concatenate([np.arange(60_000), rng.integers(0, n, 60_000)])
+    F = tsc.force(phi, pos[pick])
+    G = mg.mgfr_tsc_force(ctx, dev(phi), dev(pos)).cpu().numpy()[pick]
+    ferr = np.abs(G - F).max()
+    say(f"[tsc] {layout} on {N}^3: force max err {ferr:.2e}")
+    assert ferr <= 1e-13 * N * np.abs(phi).max()
