@@ -1177,21 +1177,30 @@ hipError_t norm_t(const Grid& g, const M* mask, const double* w, const double* u
     return hipGetLastError();
 }
 
+// Streamed from 64^3 up: with one thread per cell every neighbour's exponential is formed again.  A
+// float mask's at 512^3, 2% of the cells active: 0.55 ms, 1.92 per cell; 256^3 98 against 220 us.
+template <class M>
+hipError_t norm_any(const Grid& g, const M* mask, const double* w, const double* u, const double* src, double* partial,
+                    int* nparts, hipStream_t s)
+{
+    if (g.n < kMK) return norm_t(g, mask, w, u, src, partial, nparts, s);
+    const int ti = stream_planes(g.n);
+    const long long nb = (long long)(g.n / ti) * (g.n / kSJ) * (g.n / kSK);
+    if (nb > masked_norm_partials(g)) return hipErrorInvalidValue;
+    *nparts = (int)nb;
+    return stream<kNorm>(g, mask, w, u, src, partial, nullptr, nullptr, nullptr, nullptr, nullptr, ti, s);
+}
+
 hipError_t masked_norm(const Grid& g, const float* mask, const double* w, const double* u, const double* src,
                        double* partial, int* nparts, hipStream_t s)
 {
-    return norm_t(g, mask, w, u, src, partial, nparts, s);
+    return norm_any(g, mask, w, u, src, partial, nparts, s);
 }
 
 hipError_t masked_norm(const Grid& g, const unsigned char* flags, const double* w, const double* u,
                        const double* src, double* partial, int* nparts, hipStream_t s)
 {
-    if (g.n < kMK) return norm_t(g, flags, w, u, src, partial, nparts, s);
-    const int ti = stream_planes(g.n);
-    const long long nb = (long long)(g.n / ti) * (g.n / kSJ) * (g.n / kSK);
-    if (nb > masked_norm_partials(g)) return hipErrorInvalidValue;
-    *nparts = (int)nb;
-    return stream<kNorm>(g, flags, w, u, src, partial, nullptr, nullptr, nullptr, nullptr, nullptr, ti, s);
+    return norm_any(g, flags, w, u, src, partial, nparts, s);
 }
 
 hipError_t masked_coarsest(const Grid& g, const float* mask, const double* w, double* u, const double* f, int cap,

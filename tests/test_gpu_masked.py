@@ -315,3 +315,27 @@ def test_diverged_solve_is_reported(mg, ctx, N, contrast, fractional):
     assert np.isnan(u[mask > 0]).all()
     assert st == mg.MGFR_ENONFINITE and np.isnan(hist[-1])
     assert np.array_equal(u[mask <= 0], u0[mask <= 0])
+
+
+@pytest.mark.parametrize("N", [32, 64, 128, 256])
+def test_residual_norm_of_fractional_masks(mg, ctx, N):
+    """The rms residual over the active cells of a fractional mask (per cell below 64^3, streamed
+    from there on, in chunks of 8 and 32 planes) against the oracle's operator.  Each cell's residual
+    rounds some 20 times in terms of at most 12 C b |du|, whose size the bar takes: 1e-13 of
+    their rms."""
+    import torch
+    say(f"[masked] norm of fractional masks N={N}")
+    rng = np.random.default_rng(N)
+    rho = inputs.lognormal(N, 1.0, -2.0, seed=N)
+    mask = np.repeat(np.repeat(np.repeat(rng.integers(-4, 5, size=(N // 4,) * 3) / 4.0, 4, 0), 4, 1), 4, 2)
+    m = O.Model(box_mpc_h=float(N), fr0_abs=1e-5)
+    c = O.constants(m, N)
+    u0 = c["ubar"] + 0.3 * rng.standard_normal((N, N, N))
+    L, _ = O.masked_operator(u0, u0, mask, m, rho=rho)
+    active = mask > 0
+    ref = np.sqrt((L[active] ** 2).mean())
+    _, hist, _ = mg.mg_fr_solve_masked(ctx, dev(rho), dev(mask.astype(np.float32), torch.float32), dev(u0),
+                                       mg.Params(box_mpc_h=float(N), fr0_abs=1e-5), mg.mgfr_default_opts(max_cycles=0))
+    size = 12 * c["C"] * np.sqrt((np.exp(2 * u0[active])).mean()) * 6.0 + c["Sbar"]
+    say(f"  rms {hist[0]:.6e}, off by {abs(hist[0] - ref):.1e}")
+    assert abs(hist[0] - ref) <= 1e-13 * size
