@@ -46,6 +46,16 @@ int ensure_masked(mgfr_ctx* c, int N, int coarsest)
     return MGFR_OK;
 }
 
+// Whether the sweeps of a level with a float mask are fused (both colours in one pass, out of place).
+// A colour launch returns at once at a masked cell, the fused pass walks every plane of every tile:
+// us per sweep, colour launches and fused, 128^3 with 3% of the cells active 32, 43, 30% 44.6, 45.6, 50%
+// 48, 46; 256^3 with 3% 153, 166, 6% 201, 190, 50% 358, 231; 512^3 with 0.2% 429, 741, 1% 846, 878, 3%
+// 1412, 1054, 50% 2834, 1755.  So from 786432 active cells, and 1 in 96, up.
+bool fused_float(const mgfr_ctx::MLevel& L)
+{
+    return L.g.n > mgfr::fused_sweep_min_n() && L.active >= 3LL << 18 && 96 * L.active >= mgfr::cells(L.g);
+}
+
 struct MCycle {
     mgfr_ctx* c;
     const mgfr_opts* o;
@@ -70,10 +80,9 @@ struct MCycle {
             MGFR_TRY(hip_check(c, hipEventRecord(c->ev[c->ev_used], s), "hipEventRecord"));
         }
         // the finest level: both colours in one pass, out of place between the caller's u and the
-        // context's second buffer (opts->tile = 1: per colour), from 64^3 up on byte flags and, like
-        // the coarse levels of fractional masks, from 128^3 on a float mask (256^3: 264 us against
-        // 443 for the two colour launches)
-        const bool fused = m == 0 && c->malt && o->tile != 1 && (L.flags || L.g.n > mgfr::fused_sweep_min_n());
+        // context's second buffer (opts->tile = 1: per colour), from 64^3 up on byte flags, and on
+        // a float mask, like the coarse levels, where that is the faster form
+        const bool fused = m == 0 && c->malt && o->tile != 1 && (L.flags || fused_float(L));
         if (fused) {
             double* out = L.u == c->malt ? user_u : c->malt;
             const int ti = o->planes > 0 && o->planes <= L.g.n ? o->planes : mgfr::fused_sweep_planes(L.g.n);
@@ -84,7 +93,7 @@ struct MCycle {
                 MGFR_TRY(hip_check(c, mgfr::masked_ngs_fused(L.g, L.mask, L.w, L.u, out, src(m), ti, s),
                                    "masked_ngs_fused"));
             L.u = out;
-        } else if (L.alt) {
+        } else if (L.alt && fused_float(L)) {
             MGFR_TRY(hip_check(c, mgfr::masked_ngs_fused(L.g, L.mask, L.w, L.u, L.alt, src(m),
                                                          mgfr::fused_sweep_planes(L.g.n), s),
                                "masked_ngs_fused"));

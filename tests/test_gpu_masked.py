@@ -339,3 +339,26 @@ def test_residual_norm_of_fractional_masks(mg, ctx, N):
     size = 12 * c["C"] * np.sqrt((np.exp(2 * u0[active])).mean()) * 6.0 + c["Sbar"]
     say(f"  rms {hist[0]:.6e}, off by {abs(hist[0] - ref):.1e}")
     assert abs(hist[0] - ref) <= 1e-13 * size
+
+
+@pytest.mark.parametrize("N,active,launches", [(128, 0.1, 2), (128, 0.6, 1), (256, 0.03, 2), (256, 0.1, 1), (64, 0.9, 2)])
+def test_sweep_of_fractional_masks_follows_the_active_cells(mg, ctx, N, active, launches):
+    """Few active cells are swept by colour launches, which skip the others, many by the fused pass;
+    either way the cycles are the same to the rounding of their sweeps (1e-9 of the residual, as
+    for the oracle's histories at 1e-6, which the first cycle of a solve does not amplify)."""
+    import torch
+    say(f"[masked] sweep form N={N} active={active}")
+    rng = np.random.default_rng(N)
+    rho = inputs.lognormal(N, 1.0, -2.0, seed=N)
+    on = rng.random((N // 8,) * 3) < active
+    mask = np.repeat(np.repeat(np.repeat(np.where(on, 0.75, -0.5), 8, 0), 8, 1), 8, 2).astype(np.float32)
+    p = mg.Params(box_mpc_h=float(N), fr0_abs=1e-5)
+    u0 = O.constants(O.Model(box_mpc_h=float(N), fr0_abs=1e-5), N)["ubar"] + 0.1 * inputs.gaussian_field(N, 1.0, -2.0, seed=3)
+    hists = []
+    for tile in (0, 1):
+        opts = mg.mgfr_default_opts(tol=0.0, max_cycles=2, tile=tile, flags=mg.MGFR_PROFILE)
+        ud, hist, st = mg.mg_fr_solve_masked(ctx, dev(rho), dev(mask, torch.float32), dev(u0), p, opts)
+        assert st == mg.MGFR_ENOTCONV, ctx.last_error()
+        assert mg.mgfr_get_stats(ctx)["sweep_launches"] == (launches if tile == 0 else 2) * 8
+        hists.append(np.asarray(hist))
+    assert np.all(np.abs(hists[0] - hists[1]) <= 1e-9 * hists[1][0])
