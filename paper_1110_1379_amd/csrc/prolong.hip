@@ -67,6 +67,7 @@ __global__ void __launch_bounds__(kPT) k_prolong_stream(int lgc, T* __restrict__
         P2 r{v[t].x + (T(0.75) * near.x + T(0.25) * far.x), v[t].y + (T(0.75) * near.y + T(0.25) * far.y)};
         if (maskf) {
             const Pair<float> m = *(const Pair<float>*)(maskf + q);
+            if (!(m.x > 0.0f) && !(m.y > 0.0f)) return;  // 512^3, 2% active 0.404 ms, 0.539 if stored
             if (!(m.x > 0.0f)) r.x = v[t].x;
             if (!(m.y > 0.0f)) r.y = v[t].y;
         }
