@@ -48,7 +48,14 @@ extern "C" {
 #define MGFR_WARM_START 2    /* start from the u passed in instead of the background u      */
 #define MGFR_PROFILE 4       /* time every finest-level smoother launch with HIP events
                                 (batched solves: every sweep of the finest level of every
-                                unit, both colour launches, when MGFR_GRAPH is not set)      */
+                                unit, both colour launches, when MGFR_GRAPH is not set).  The
+                                launches, and the results, are those of a solve without it:
+                                where the finest level's sweeps are part of a launch that does
+                                more, that launch is timed and counts once, with the bytes of
+                                one pass over the level (domain of 32^3 and 64^3 at pre = post
+                                = 2: two sweeps and the transfer beside them, two launches a
+                                V-cycle; domain and Poisson grid of side <= 16, coarsest_n <
+                                N: the whole V-cycle)                                         */
 #define MGFR_GRAPH 8         /* batched solves: capture one cycle's launches in a HIP graph
                                 on first use and replay it for every later cycle of the call.
                                 mg_fr_solve: capture two cycles, each ending in the stop test

@@ -267,6 +267,28 @@ inline int hip_check(mgfr_ctx* c, hipError_t e, const char* what)
         if (rc_ != MGFR_OK) return rc_;      \
     } while (0)
 
+// Runs launch(), if `timed` between two HIP events on s: the interval goes into the stats' sweep time
+// and counts as `launches` launches and `bytes` bytes there.
+template <class Launch>
+int timed_launch(mgfr_ctx* c, hipStream_t s, bool timed, int launches, double bytes, Launch launch)
+{
+    if (!timed) return launch();
+    if ((size_t)c->ev_used + 2 > c->ev.size()) {
+        for (int k = 0; k < 64; ++k) {
+            hipEvent_t ev;
+            MGFR_TRY(hip_check(c, hipEventCreate(&ev), "hipEventCreate"));
+            c->ev.push_back(ev);
+        }
+    }
+    MGFR_TRY(hip_check(c, hipEventRecord(c->ev[c->ev_used], s), "hipEventRecord"));
+    MGFR_TRY(launch());
+    MGFR_TRY(hip_check(c, hipEventRecord(c->ev[c->ev_used + 1], s), "hipEventRecord"));
+    c->ev_used += 2;
+    c->stats.sweep_launches += launches;
+    c->stats.sweep_bytes += bytes;
+    return MGFR_OK;
+}
+
 inline int check_opts(mgfr_ctx* c, const mgfr_opts* o)
 {
     if (!o) return c->fail(MGFR_EINVAL, "opts is NULL");

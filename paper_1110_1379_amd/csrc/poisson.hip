@@ -74,43 +74,26 @@ struct PCycle {
         return MGFR_OK;
     }
 
+    // MGFR_PROFILE times what relaxes the finest level, on the solve's stream
+    bool timed(size_t m) const { return m == 0 && (o->flags & MGFR_PROFILE); }
+
     int sweep(size_t m, double*& cur, double bm, int passes, const double* xc = nullptr)
     {
         mgfr_ctx::PLevel& L = c->plv[m];
-        // MGFR_PROFILE: HIP events around every finest-level sweep, on the solve's stream
-        const bool timed = m == 0 && (o->flags & MGFR_PROFILE);
-        if (timed) {
-            if ((size_t)c->ev_used + 2 > c->ev.size()) {
-                for (int k = 0; k < 64; ++k) {
-                    hipEvent_t ev;
-                    MGFR_TRY(hip_check(c, hipEventCreate(&ev), "hipEventCreate"));
-                    c->ev.push_back(ev);
-                }
-            }
-            MGFR_TRY(hip_check(c, hipEventRecord(c->ev[c->ev_used], s), "hipEventRecord"));
-        }
         const bool fused = L.alt && (passes == 2 || L.g.n >= mgfr::poisson_fused_min_n());
-        if (fused) {
-            double* out = cur == L.alt ? (m == 0 ? finest_x : L.x) : L.alt;
-            const bool opt = m == 0 && o->planes > 0 && o->planes <= L.g.n;
+        double* out = !fused ? cur : cur == L.alt ? (m == 0 ? finest_x : L.x) : L.alt;
+        const bool opt = m == 0 && o->planes > 0 && o->planes <= L.g.n;
+        // read x, b; write x: once per launch, also for a two-sweep pass
+        MGFR_TRY(timed_launch(c, s, timed(m), fused ? 1 : 2, 24.0 * (double)(1LL << (3 * L.g.lg)), [&] {
+            if (!fused) return hip_check(c, mgfr::poisson_ngs(L.g, cur, L.b, bm, s), "poisson_ngs");
             if (passes == 2) {
                 const int ti = opt ? o->planes : mgfr::poisson_fused2_planes(L.g.n);
-                MGFR_TRY(hip_check(c, mgfr::poisson_ngs_fused2(L.g, cur, out, L.b, bm, ti, xc, s), "poisson_ngs_fused2"));
-            } else {
-                const int ti = opt ? o->planes : mgfr::fused_sweep_planes(L.g.n);
-                MGFR_TRY(hip_check(c, mgfr::poisson_ngs_fused(L.g, cur, out, L.b, bm, ti, s), "poisson_ngs_fused"));
+                return hip_check(c, mgfr::poisson_ngs_fused2(L.g, cur, out, L.b, bm, ti, xc, s), "poisson_ngs_fused2");
             }
-            cur = out;
-        } else {
-            MGFR_TRY(hip_check(c, mgfr::poisson_ngs(L.g, cur, L.b, bm, s), "poisson_ngs"));
-        }
-        if (timed) {
-            MGFR_TRY(hip_check(c, hipEventRecord(c->ev[c->ev_used + 1], s), "hipEventRecord"));
-            c->ev_used += 2;
-            c->stats.sweep_launches += fused ? 1 : 2;
-            // read x, b; write x: once per launch, also for a two-sweep pass
-            c->stats.sweep_bytes += 24.0 * (double)(1LL << (3 * L.g.lg));
-        }
+            const int ti = opt ? o->planes : mgfr::fused_sweep_planes(L.g.n);
+            return hip_check(c, mgfr::poisson_ngs_fused(L.g, cur, out, L.b, bm, ti, s), "poisson_ngs_fused");
+        }));
+        cur = out;
         c->stats.cell_updates += passes * (1LL << (3 * L.g.lg));
         if (m == 0) c->stats.finest_updates += passes * (1LL << (3 * L.g.lg));
         return MGFR_OK;
@@ -118,27 +101,25 @@ struct PCycle {
 
     double* finest_x = nullptr;
 
-    bool in_tail(size_t m) const
-    {
-        return m + 1 == c->plv.size() ||
-               (c->plv[m].g.n <= mgfr::poisson_tail_n() && !(m == 0 && (o->flags & MGFR_PROFILE)));
-    }
+    bool in_tail(size_t m) const { return m + 1 == c->plv.size() || c->plv[m].g.n <= mgfr::poisson_tail_n(); }
 
     int vcycle(size_t m)
     {
         mgfr_ctx::PLevel& L = c->plv[m];
         double* x = m == 0 ? finest_x : L.x;
         const double bm = m == 0 ? mean0 : 0.0;
-        // the levels of side <= 16 (a finest one only if its launches are not timed) in one launch
+        // the levels of side <= 16 in one launch
         if (in_tail(m)) {
             for (size_t k = m; k + 1 < c->plv.size(); ++k) {
                 const long long n = (long long)(o->pre + o->post) * (1LL << (3 * c->plv[k].g.lg));
                 c->stats.cell_updates += n;
                 if (k == 0) c->stats.finest_updates += n;
             }
-            return hip_check(c, mgfr::poisson_tail(L.g, x, L.b, bm, m > 0, (int)(c->plv.size() - m), o->pre, o->post,
-                                                   o->coarsest_sweeps, o->coarsest_rtol, s),
-                             "poisson_tail");
+            return timed_launch(c, s, timed(m) && c->plv.size() > 1, 1, 24.0 * (double)(1LL << (3 * L.g.lg)), [&] {
+                return hip_check(c, mgfr::poisson_tail(L.g, x, L.b, bm, m > 0, (int)(c->plv.size() - m), o->pre, o->post,
+                                                       o->coarsest_sweeps, o->coarsest_rtol, s),
+                                 "poisson_tail");
+            });
         }
         mgfr_ctx::PLevel& H = c->plv[m + 1];
         double* cur = x;

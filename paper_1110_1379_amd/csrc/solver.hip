@@ -92,19 +92,15 @@ bool fused32(const mgfr_opts* o, size_t m, int n)
 }
 
 // Whether the V-cycle runs from level m (side n) down in one launch: the levels of side <= 16, and
-// the coarsest one in any case.  A finest level whose launches are timed keeps them.
-bool tail_from(const mgfr_opts* o, size_t m, int n, size_t nlev)
-{
-    if (m + 1 == nlev) return true;
-    return n <= mgfr::domain_tail_n() && !(m == 0 && (o->flags & MGFR_PROFILE));
-}
+// the coarsest one in any case.
+bool tail_from(size_t m, int n, size_t nlev) { return m + 1 == nlev || n <= mgfr::domain_tail_n(); }
 
 // Whether level m (side n) of a V-cycle is relaxed in blocks: two sweeps on either side of the coarse
-// step; on the finest level none that are timed or whose form the options choose.
+// step; on the finest level none whose form the options choose.
 bool in_blocks(const mgfr_opts* o, size_t m, int n, size_t nlev)
 {
     return mgfr::block_level(n) && m + 1 < nlev && o->pre == 2 && o->post == 2 &&
-           !(m == 0 && ((o->flags & MGFR_PROFILE) || o->planes > 0 || o->tile > 0));
+           !(m == 0 && (o->planes > 0 || o->tile > 0));
 }
 
 struct Cycle {
@@ -114,8 +110,11 @@ struct Cycle {
     hipStream_t s;
     const double* finest_src = nullptr;
 
+    // MGFR_PROFILE times what relaxes the finest level
+    bool timed(size_t m) const { return m == 0 && (o->flags & MGFR_PROFILE); }
+
     // One smoother sweep on level m, from *cur into the other buffer for the fused kernel
-    // (cur is updated) or in place.  Finest-level sweeps are timed under MGFR_PROFILE.
+    // (cur is updated) or in place.
     int sweep(size_t m, const double* src, double*& cur)
     {
         Level& L = h.lv[m];
@@ -123,32 +122,14 @@ struct Cycle {
         // colour launches 7.7 us; from 128^3 (20.5 against 29.4 us) it is the faster one.
         const bool fused = L.alt != nullptr && !o_simple &&
                            (L.g.n > mgfr::fused_sweep_min_n() || o_fused || (m == 0 && (o->planes > 0 || o->tile > 0)));
-        const bool timed = m == 0 && (o->flags & MGFR_PROFILE);
-        if (timed) {
-            if ((size_t)c->ev_used + 2 > c->ev.size()) {
-                for (int k = 0; k < 64; ++k) {
-                    hipEvent_t ev;
-                    MGFR_TRY(hip_check(c, hipEventCreate(&ev), "hipEventCreate"));
-                    c->ev.push_back(ev);
-                }
-            }
-            MGFR_TRY(hip_check(c, hipEventRecord(c->ev[c->ev_used], s), "hipEventRecord"));
-        }
-        if (fused) {
-            double* out = cur == L.u ? L.alt : L.u;
-            MGFR_TRY(hip_check(c, mgfr::ngs_sweep_fused(L.g, cur, out, src, planes_for(o, m, L.g.n),
-                                                          m == 0 && o->tile > 0 ? o->tile : mgfr::kTile64x16x64, s),
-                               "ngs_sweep_fused"));
-            cur = out;
-        } else {
-            MGFR_TRY(hip_check(c, mgfr::ngs_sweep(L.g, cur, src, s), "ngs_sweep"));
-        }
-        if (timed) {
-            MGFR_TRY(hip_check(c, hipEventRecord(c->ev[c->ev_used + 1], s), "hipEventRecord"));
-            c->ev_used += 2;
-            c->stats.sweep_launches += fused ? 1 : 2;
-            c->stats.sweep_bytes += 24.0 * (double)mgfr::cells(L.g);
-        }
+        double* out = !fused ? cur : cur == L.u ? L.alt : L.u;
+        MGFR_TRY(timed_launch(c, s, timed(m), fused ? 1 : 2, 24.0 * (double)mgfr::cells(L.g), [&] {
+            if (!fused) return hip_check(c, mgfr::ngs_sweep(L.g, cur, src, s), "ngs_sweep");
+            return hip_check(c, mgfr::ngs_sweep_fused(L.g, cur, out, src, planes_for(o, m, L.g.n),
+                                                      m == 0 && o->tile > 0 ? o->tile : mgfr::kTile64x16x64, s),
+                             "ngs_sweep_fused");
+        }));
+        cur = out;
         c->stats.cell_updates += mgfr::cells(L.g);
         if (m == 0) c->stats.finest_updates += mgfr::cells(L.g);
         return MGFR_OK;
@@ -173,27 +154,34 @@ struct Cycle {
     {
         Level& L = h.lv[m];
         const double* src = m == 0 ? finest_src : L.f;
-        if (tail_from(o, m, L.g.n, h.nlev)) {
+        if (tail_from(m, L.g.n, h.nlev)) {
             for (size_t k = m; k + 1 < h.nlev; ++k) {
                 const long long n = (long long)(o->pre + o->post) * mgfr::cells(h.lv[k].g);
                 c->stats.cell_updates += n;
                 if (k == 0) c->stats.finest_updates += n;
             }
-            return hip_check(c, mgfr::domain_tail(L.g, L.u, src, fas, (int)(h.nlev - m), o->pre, o->post,
-                                                  o->coarsest_sweeps, o->coarsest_rtol, h.counter, s),
-                             "domain_tail");
+            return timed_launch(c, s, timed(m) && h.nlev > 1, 1, 24.0 * (double)mgfr::cells(L.g), [&] {
+                return hip_check(c, mgfr::domain_tail(L.g, L.u, src, fas, (int)(h.nlev - m), o->pre, o->post,
+                                                      o->coarsest_sweeps, o->coarsest_rtol, h.counter, s),
+                                 "domain_tail");
+            });
         }
         double* cur = L.u;
         Level& H = h.lv[m + 1];
-        const bool tail = tail_from(o, m + 1, H.g.n, h.nlev);
+        const bool tail = tail_from(m + 1, H.g.n, h.nlev);
         if (!o_simple && !o_fused && in_blocks(o, m, L.g.n, h.nlev)) {
             double* second = L.alt ? L.alt : L.blk;
-            MGFR_TRY(hip_check(c, mgfr::block_pre(L.g, L.u, second, src, H.u, H.uhat, H.f, s), "block_pre"));
+            const double bytes = 24.0 * (double)mgfr::cells(L.g);
+            MGFR_TRY(timed_launch(c, s, timed(m), 1, bytes, [&] {
+                return hip_check(c, mgfr::block_pre(L.g, L.u, second, src, H.u, H.uhat, H.f, s), "block_pre");
+            }));
             if (!tail) MGFR_TRY(hip_check(c, mgfr::fas_rhs(H.g, H.uhat, H.f, s), "fas_rhs"));
             MGFR_TRY(vcycle(m + 1, tail));
             c->stats.cell_updates += 4 * mgfr::cells(L.g);
             if (m == 0) c->stats.finest_updates += 4 * mgfr::cells(L.g);
-            return hip_check(c, mgfr::block_post(L.g, second, L.u, src, H.u, H.uhat, s), "block_post");
+            return timed_launch(c, s, timed(m), 1, bytes, [&] {
+                return hip_check(c, mgfr::block_post(L.g, second, L.u, src, H.u, H.uhat, s), "block_post");
+            });
         }
         for (int k = 0; k < o->pre; ++k) MGFR_TRY(sweep(m, src, cur));
         if (L.alt && !o_simple) {
@@ -228,35 +216,21 @@ struct Cycle32 {
     const mgfr_opts* o;
     hipStream_t s;
 
+    // MGFR_PROFILE times what relaxes the finest level
+    bool timed(size_t m) const { return m == 0 && (o->flags & MGFR_PROFILE); }
+
     int sweep(size_t m, float*& cur)
     {
         Level32& L = h.lv32[m];
-        const bool timed = m == 0 && (o->flags & MGFR_PROFILE);
-        if (timed) {
-            if ((size_t)c->ev_used + 2 > c->ev.size()) {
-                for (int k = 0; k < 64; ++k) {
-                    hipEvent_t ev;
-                    MGFR_TRY(hip_check(c, hipEventCreate(&ev), "hipEventCreate"));
-                    c->ev.push_back(ev);
-                }
-            }
-            MGFR_TRY(hip_check(c, hipEventRecord(c->ev[c->ev_used], s), "hipEventRecord"));
-        }
         const bool fused = L.ealt && fused32(o, m, L.g.n);
-        if (fused) {
-            float* out = cur == L.e ? L.ealt : L.e;
-            MGFR_TRY(hip_check(c, mgfr::ngs_sweep32_fused(L.g, L.ub, cur, out, L.f, planes_for32(o, m, L.g.n), tile_for32(o, m), s),
-                               "ngs_sweep32_fused"));
-            cur = out;
-        } else {
-            MGFR_TRY(hip_check(c, mgfr::ngs_sweep32(L.g, L.ub, cur, L.f, s), "ngs_sweep32"));
-        }
-        if (timed) {
-            MGFR_TRY(hip_check(c, hipEventRecord(c->ev[c->ev_used + 1], s), "hipEventRecord"));
-            c->ev_used += 2;
-            c->stats.sweep_launches += fused ? 1 : 2;
-            c->stats.sweep_bytes += 12.0 * (double)mgfr::cells(L.g);
-        }
+        float* out = !fused ? cur : cur == L.e ? L.ealt : L.e;
+        MGFR_TRY(timed_launch(c, s, timed(m), fused ? 1 : 2, 12.0 * (double)mgfr::cells(L.g), [&] {
+            if (!fused) return hip_check(c, mgfr::ngs_sweep32(L.g, L.ub, cur, L.f, s), "ngs_sweep32");
+            return hip_check(c, mgfr::ngs_sweep32_fused(L.g, L.ub, cur, out, L.f, planes_for32(o, m, L.g.n),
+                                                        tile_for32(o, m), s),
+                             "ngs_sweep32_fused");
+        }));
+        cur = out;
         c->stats.cell_updates += mgfr::cells(L.g);
         if (m == 0) c->stats.finest_updates += mgfr::cells(L.g);
         return MGFR_OK;
@@ -265,27 +239,34 @@ struct Cycle32 {
     int vcycle(size_t m, bool fas = false)
     {
         Level32& L = h.lv32[m];
-        if (tail_from(o, m, L.g.n, h.nlev32)) {
+        if (tail_from(m, L.g.n, h.nlev32)) {
             for (size_t k = m; k + 1 < h.nlev32; ++k) {
                 const long long n = (long long)(o->pre + o->post) * mgfr::cells(h.lv32[k].g);
                 c->stats.cell_updates += n;
                 if (k == 0) c->stats.finest_updates += n;
             }
-            return hip_check(c, mgfr::domain_tail32(L.g, L.ub, L.e, L.f, fas, (int)(h.nlev32 - m), o->pre, o->post,
-                                                    o->coarsest_sweeps, o->coarsest_rtol, s),
-                             "domain_tail32");
+            return timed_launch(c, s, timed(m) && h.nlev32 > 1, 1, 12.0 * (double)mgfr::cells(L.g), [&] {
+                return hip_check(c, mgfr::domain_tail32(L.g, L.ub, L.e, L.f, fas, (int)(h.nlev32 - m), o->pre, o->post,
+                                                        o->coarsest_sweeps, o->coarsest_rtol, s),
+                                 "domain_tail32");
+            });
         }
         float* cur = L.e;
         Level32& H = h.lv32[m + 1];
-        const bool tail = tail_from(o, m + 1, H.g.n, h.nlev32);
+        const bool tail = tail_from(m + 1, H.g.n, h.nlev32);
         if (in_blocks(o, m, L.g.n, h.nlev32)) {
             float* second = L.ealt ? L.ealt : L.eblk;
-            MGFR_TRY(hip_check(c, mgfr::block_pre32(L.g, L.ub, L.e, second, L.f, H.e, H.ehat, H.f, s), "block_pre32"));
+            const double bytes = 12.0 * (double)mgfr::cells(L.g);
+            MGFR_TRY(timed_launch(c, s, timed(m), 1, bytes, [&] {
+                return hip_check(c, mgfr::block_pre32(L.g, L.ub, L.e, second, L.f, H.e, H.ehat, H.f, s), "block_pre32");
+            }));
             if (!tail) MGFR_TRY(hip_check(c, mgfr::fas_rhs32(H.g, H.ub, H.ehat, H.f, s), "fas_rhs32"));
             MGFR_TRY(vcycle(m + 1, tail));
             c->stats.cell_updates += 4 * mgfr::cells(L.g);
             if (m == 0) c->stats.finest_updates += 4 * mgfr::cells(L.g);
-            return hip_check(c, mgfr::block_post32(L.g, L.ub, second, L.e, L.f, H.e, H.ehat, s), "block_post32");
+            return timed_launch(c, s, timed(m), 1, bytes, [&] {
+                return hip_check(c, mgfr::block_post32(L.g, L.ub, second, L.e, L.f, H.e, H.ehat, s), "block_post32");
+            });
         }
         for (int k = 0; k < o->pre; ++k) MGFR_TRY(sweep(m, cur));
         MGFR_TRY(hip_check(c, mgfr::resid_restrict32(L.g, L.ub, cur, L.f, H.e, H.ehat, H.f, s), "resid_restrict32"));
@@ -669,30 +650,13 @@ int mgfr_smooth32(mgfr_ctx* c, const float* ub, float* e, const float* f, int N,
     c->ev_used = 0;
     float* cur = e;
     for (int k = 0; k < nsweeps; ++k) {
-        if (timed) {
-            if ((size_t)c->ev_used + 2 > c->ev.size()) {
-                for (int q = 0; q < 64; ++q) {
-                    hipEvent_t ev;
-                    MGFR_TRY(hip_check(c, hipEventCreate(&ev), "hipEventCreate"));
-                    c->ev.push_back(ev);
-                }
-            }
-            MGFR_TRY(hip_check(c, hipEventRecord(c->ev[c->ev_used], s), "hipEventRecord"));
-        }
-        if (fused) {
-            float* out = cur == e ? c->lv32[0].ealt : e;
-            MGFR_TRY(hip_check(c, mgfr::ngs_sweep32_fused(g, ub, cur, out, f, planes_for32(o, 0, N), tile_for32(o, 0), s),
-                               "ngs_sweep32_fused"));
-            cur = out;
-        } else {
-            MGFR_TRY(hip_check(c, mgfr::ngs_sweep32(g, ub, cur, f, s), "ngs_sweep32"));
-        }
-        if (timed) {
-            MGFR_TRY(hip_check(c, hipEventRecord(c->ev[c->ev_used + 1], s), "hipEventRecord"));
-            c->ev_used += 2;
-            c->stats.sweep_launches += fused ? 1 : 2;
-            c->stats.sweep_bytes += 12.0 * (double)mgfr::cells(g);
-        }
+        float* out = !fused ? cur : cur == e ? c->lv32[0].ealt : e;
+        MGFR_TRY(timed_launch(c, s, timed, fused ? 1 : 2, 12.0 * (double)mgfr::cells(g), [&] {
+            if (!fused) return hip_check(c, mgfr::ngs_sweep32(g, ub, cur, f, s), "ngs_sweep32");
+            return hip_check(c, mgfr::ngs_sweep32_fused(g, ub, cur, out, f, planes_for32(o, 0, N), tile_for32(o, 0), s),
+                             "ngs_sweep32_fused");
+        }));
+        cur = out;
         c->stats.cell_updates += mgfr::cells(g);
         c->stats.finest_updates += mgfr::cells(g);
     }
@@ -922,7 +886,7 @@ int solve_body(mgfr_ctx* c, const Hier& h, const Model& md, const double* rho, i
         const bool stream = N >= mgfr::fused_sweep_min_n();
         // levels whose base is restricted by a launch (the tail forms those below its own)
         size_t nbase = 1;
-        while (nbase < h.nlev32 && !tail_from(o, nbase - 1, h.lv32[nbase - 1].g.n, h.nlev32)) ++nbase;
+        while (nbase < h.nlev32 && !tail_from(nbase - 1, h.lv32[nbase - 1].g.n, h.nlev32)) ++nbase;
         double* ucur = u;
         // residual of ucur (+ e when `update`), cast to the single-precision right-hand side
         auto outer_residual = [&](bool update) -> int {

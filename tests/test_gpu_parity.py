@@ -370,3 +370,28 @@ def test_block_passes_match_the_launches_they_replace(N, coarsest):
     scale = res[0][0].abs().max().item()
     assert (res[0][0] - res[1][0]).abs().max().item() <= 4 * max(N, 64) ** 2 * 2.2e-16 * scale
     ctx.close()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("N", [4, 8, 16, 32, 64, 128])
+def test_timings_do_not_change_the_solve(N, precision):
+    """With MGFR_PROFILE a solve gives the same bits, and times the launches that it makes: the whole
+    V-cycle in one up to 16^3, two passes of two sweeps at 32^3 and 64^3, four sweeps at 128^3."""
+    import torch
+    from paper_1110_1379_amd import mgfr
+    ctx = mgfr.Context(0)
+    params = mgfr.Params(box_mpc_h=float(max(N, 32)), fr0_abs=1e-5)
+    rho = torch.from_numpy(inputs.lognormal(N, 1.0, -1.5, seed=N)).to("cuda:0")
+    mixed = precision == "mixed"
+    res = []
+    for flags in (0, mgfr.MGFR_PROFILE):
+        opts = mgfr.mgfr_default_opts(tol=1e-8, flags=flags, precision=mgfr.MGFR_MIXED if mixed else mgfr.MGFR_FP64)
+        u, h, _ = mgfr.mg_fr_solve(ctx, rho, params, opts)
+        res.append((u, np.asarray(h)))
+    assert torch.equal(res[0][0], res[1][0]) and np.array_equal(res[0][1], res[1][1])
+    s = mgfr.mgfr_get_stats(ctx)
+    launches = {4: 0, 8: 1, 16: 1, 32: 2, 64: 2, 128: 4}[N] * (s["inner_cycles"] if mixed else s["cycles"])
+    assert launches > 0 or N == 4
+    assert s["sweep_launches"] == launches and (s["sweep_ms"] > 0.0) == (launches > 0)
+    assert s["sweep_bytes"] == launches * (12 if mixed else 24) * N ** 3
+    ctx.close()

@@ -236,3 +236,21 @@ def test_small_levels_in_one_launch_match_oracle(mg, ctx, N, coarsest, pre, post
     again, hist, st = mg.mg_poisson_solve(ctx, dev(rho), dev(u), params, warm, phi=dev(0.5 * ref))
     assert st == mg.MGFR_OK, (ctx.last_error(), hist)
     assert np.abs(again.cpu().numpy() - ref).max() <= 1e-10 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("N", [8, 16, 32, 64])
+def test_timings_do_not_change_the_solve(mg, ctx, N):
+    """With MGFR_PROFILE a solve gives the same bits and times the launches that it makes."""
+    import torch
+    say(f"[poisson] timed N={N}")
+    p = mg.Params(box_mpc_h=64.0, fr0_abs=1e-5)
+    rho = dev(inputs.lognormal(N, 1.0, -1.5, seed=N))
+    u = torch.full_like(rho, -11.5)
+    res = []
+    for flags in (0, mg.MGFR_PROFILE):
+        phi, h, _ = mg.mg_poisson_solve(ctx, rho, u, p, mg.mgfr_default_opts(tol=1e-10, flags=flags))
+        res.append((phi, np.asarray(h)))
+    assert torch.equal(res[0][0], res[1][0]) and np.array_equal(res[0][1], res[1][1])
+    s = mg.mgfr_get_stats(ctx)
+    # one launch a V-cycle up to 16^3; eight colour launches; two passes of two sweeps
+    assert s["sweep_launches"] == {8: 1, 16: 1, 32: 8, 64: 2}[N] * s["cycles"] > 0 and s["sweep_ms"] > 0.0
