@@ -46,11 +46,6 @@ MEASURED_TRAFFIC = {
                   "fused_fp32.h": "488b5d6971b3849dde3ba5e430a632b7e3cf7795719f750d03e891bbe6eb37f5",
                   "device_fp32.h": "c1d418ffe3a2ac7a1c4af35beb1a85ee0f04ea283dc943ae4683c431f992ed16",
                   "kernel_types.h": "21ac1843e9d4b3e18646111fcbd3ff3b7e20b75086410058eb389d6397f79ef6"}},
-    # per finest launch (one red-black sweep, 16 x 64 tiles, 128 planes per workgroup)
-    "fp64": {"points": [({"planes": 128, "tile": 1}, 4.0327e9)], "sources": {
-        "sweep_fp64.hip": "b1ff22b6883fb25a408feccaeeb902de200d32f6b16c493b1c0af74b12734402",
-        "device_fp64.h": "402e5f8d6911312325571bcbba1f25300ddfc9d029d3b26c8591b7a4a735b0f6",
-        "kernel_types.h": "21ac1843e9d4b3e18646111fcbd3ff3b7e20b75086410058eb389d6397f79ef6"}},
     # per pass of two sweeps
     "poisson": {"bytes": 3.7322e9, "sources": {
         "poisson_kernels.hip": "901f046dc27443fcb5e3b827925816b5805e0d65d8a06134d2bbb229afed3a49",

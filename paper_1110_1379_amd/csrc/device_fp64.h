@@ -15,8 +15,8 @@ struct OpVal {
 // exp(x) to within one unit in the last place: x = k ln 2 + r with |r| <= ln 2 / 2 (Cody and
 // Waite, ln 2 in two parts), exp(r) = 1 + r + r^2 q(r), q of degree 9 interpolated at the
 // Chebyshev nodes of the interval (relative error 1.6e-17).  Overflows to infinity, is zero
-// below -746 (the smallest denormal is exp(-745.13...)) and NaN at NaN: k is capped so that r
-// stays positive above the range.  The polynomial is written out with its coefficients in
+// below -746 (the smallest denormal is exp(-745.13...)) and NaN at NaN, always with the sign clear:
+// k is capped so that r stays positive above the range.  The polynomial is written out with its coefficients in
 // scalar registers because the compiler turns such a chain into v_fmac, whose addend is its
 // destination, and copies each constant into vector registers first.  21 instructions against
 // the library function's 31; the sweeps evaluate three per thread and step.
@@ -41,7 +41,7 @@ __device__ __forceinline__ double exp_(double x)
         : "v"(r), "v"(0x1.af38d53857513p-26), "s"(0x1.2891a8c1d838dp-22), "s"(0x1.71de0d9c145d0p-19),
           "s"(0x1.a019b8ef67c6cp-16), "s"(0x1.a01a01a7c8d47p-13), "s"(0x1.6c16c17893833p-10),
           "s"(0x1.11111111109adp-7), "s"(0x1.5555555553d4fp-5), "s"(0x1.5555555555556p-3));
-    q = __builtin_amdgcn_ldexp(q, (int)k);
+    q = __builtin_amdgcn_ldexp(__builtin_fabs(q), (int)k);
     return x < -746.0 ? 0.0 : q;
 }
 

@@ -47,12 +47,12 @@ __device__ __forceinline__ void masked_face(double r, double wn, double wi, doub
 
 // ---- masks of +1 and -1 ---------------------------------------------------------------------
 // A cell's value travels with b = exp(u), its sign set where the cell is masked (then u is its fixed
-// value w, which it keeps for the whole solve) and clear where it is active, also in the NaN of a
-// diverged cell, whose own sign may be either.
+// value w, which it keeps for the whole solve).  An active cell's is clear, also in the NaN of a
+// diverged one, as exp_ has it.
 __device__ __forceinline__ double signed_b(double u, int active)
 {
     const double b = dev::exp_(u);
-    return __hiloint2double((__double2hiint(b) & 0x7fffffff) | (active ? 0 : (int)0x80000000), __double2loint(b));
+    return __hiloint2double(__double2hiint(b) | (active ? 0 : (int)0x80000000), __double2loint(b));
 }
 __device__ __forceinline__ bool masked_b(double b) { return __double2hiint(b) < 0; }
 
