@@ -40,15 +40,27 @@ METRIC = "f(R) MG time-to-residual 1e-8 & cell-updates/s, 512^3, FP64 vs mixed"
 MEASURED_TRAFFIC = {
     # per finest launch (one red-black sweep of the correction, 16 x 64 tiles), at 256 and 128
     # planes per workgroup
-    "mixed": {"points": [({"planes": 256, "tile": 3}, 3.0097e9), ({"planes": 128, "tile": 3}, 2.9247e9)],
+    "mixed": {"points": [({"planes": 256, "tile": 3}, 3.0110e9), ({"planes": 128, "tile": 3}, 2.9205e9)],
               "sources": {
                   "kernels_fp32.hip": "b7d7786d045b6a4ca853e6cf2dfa4d3ba612eca34c8aeae6156c99b924089f79",
-                  "fused_fp32.h": "488b5d6971b3849dde3ba5e430a632b7e3cf7795719f750d03e891bbe6eb37f5",
+                  "fused_fp32.h": "2768355672899e4f2df0d19f715fdfdf3aa15bdd32cb9902ea4c352f7274d80a",
                   "device_fp32.h": "c1d418ffe3a2ac7a1c4af35beb1a85ee0f04ea283dc943ae4683c431f992ed16",
                   "kernel_types.h": "21ac1843e9d4b3e18646111fcbd3ff3b7e20b75086410058eb389d6397f79ef6"}},
-    # per pass of two sweeps
-    "poisson": {"bytes": 3.7322e9, "sources": {
-        "poisson_kernels.hip": "901f046dc27443fcb5e3b827925816b5805e0d65d8a06134d2bbb229afed3a49",
+    # per finest launch (one red-black sweep, 16 x 64 tiles, 128 planes per workgroup)
+    "fp64": {"points": [({"planes": 128, "tile": 1}, 4.0088e9)], "sources": {
+        "sweep_fp64.hip": "b1ff22b6883fb25a408feccaeeb902de200d32f6b16c493b1c0af74b12734402",
+        "device_fp64.h": "4d592479ee6c18b9d7cb8ed04bc28ca15a86195294debbe7037d837d74391b53",
+        "kernel_types.h": "21ac1843e9d4b3e18646111fcbd3ff3b7e20b75086410058eb389d6397f79ef6"}},
+    # per sweep (one launch of the fused masked sweep, byte flags)
+    "masked": {"bytes": 4.5840e9, "sources": {
+        "masked.hip": "4ebdf05b6a8f5c900971706ae172d8849b0ba269c883baf868ee12a8b5b33848",
+        "masked_solver.hip": "f23095f99dc0e0d1383ba8cea235beae836cca396ca6138aecec8ef3f9d18451",
+        "device_fp64.h": "4d592479ee6c18b9d7cb8ed04bc28ca15a86195294debbe7037d837d74391b53",
+        "kernel_types.h": "21ac1843e9d4b3e18646111fcbd3ff3b7e20b75086410058eb389d6397f79ef6"}},
+    # per pass of two sweeps, the mean of the pass that adds the correction (3.753) and the one that
+    # does not (3.717)
+    "poisson": {"bytes": 3.7351e9, "sources": {
+        "poisson_kernels.hip": "dea6274c0d2402699bb8ce71d70e174dc305bb30a96351a3fc4ab700238bd163",
         "kernel_types.h": "21ac1843e9d4b3e18646111fcbd3ff3b7e20b75086410058eb389d6397f79ef6"}},
 }
 
@@ -61,7 +73,7 @@ BATCH_TRAFFIC = {
     "mixed": {"bytes": 0.4538e9, "settings": (2, 2, 3), "sources": {
         "batch_col.hip": "df07ee6829189cd0542c0af086d7d5fc3d4b66615c6f220fb68eed14fdf29228",
         "batch.hip": "9d121d4eb2d78326ba57b0093e8c210bd7c7d0525a297b1ec587f0d66050fc57",
-        "fused_fp32.h": "488b5d6971b3849dde3ba5e430a632b7e3cf7795719f750d03e891bbe6eb37f5",
+        "fused_fp32.h": "2768355672899e4f2df0d19f715fdfdf3aa15bdd32cb9902ea4c352f7274d80a",
         "device_fp32.h": "c1d418ffe3a2ac7a1c4af35beb1a85ee0f04ea283dc943ae4683c431f992ed16",
         "batch_dev.h": "fdca5bf40d95d14b12e4f3f1fabcd46e32694cbf54b33679d66d5f6e0917dd58"}},
     "fp64": {"bytes": 0.9509e9, "settings": (1, 1, 1), "sources": {

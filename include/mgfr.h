@@ -105,10 +105,13 @@ typedef struct mgfr_opts {
                              to 16 with every level in LDS); 0 = 16; rounded down to a power
                              of two; values below coarsest_n count as coarsest_n    [0]      */
     int tile;             /* tile of the finest level's fused sweeps (N >= 64).  FP64: 0 =
-                             automatic (16 x 64), 1 = 16 x 64, 2 = 16 x 32 (3 - 5 as 0).  Mixed, the single-precision
-                             correction sweep: 0 = automatic (16 x 64), 1 = 16 x 32, 2 = 32 x
-                             32, 3 = 16 x 64, 5 = 32 x 64 (one tile column pair per thread),
-                             4 = 8 x 32 (column pairs over the tile and its halo).
+                             automatic (16 x 64), 1 = 16 x 64, 2 = 16 x 32 (8 x 64 in earlier
+                             versions), 3 - 5 as 0.  Mixed, the single-precision correction
+                             sweep: 0 = automatic (16 x 64), 1 = 16 x 32, 2 = 32 x 32, 3 = 16
+                             x 64, 5 = 32 x 64 (one tile column pair per thread), 4 = 8 x 32
+                             (column pairs over the tile and its halo).  On a finest level of
+                             32^3 or 64^3 a tile or planes above 0 also asks for single sweeps
+                             instead of two in one launch: the same updates to rounding.
                              Batched solves, launched sweeps of unit levels of side >=
                              32: 0 = automatic: a mixed solve walks 16 x 32 column tiles
                              (16 planes per workgroup, patches 8) in pairs of fused
@@ -198,8 +201,10 @@ int mgfr_residual(mgfr_ctx* ctx, const double* rho, const double* u, int N,
 /* Single-grid relaxation (Sec. VI.D.1's comparison; also the smoother on its own):
  * nsweeps red-black Newton-Gauss-Seidel sweeps of the periodic N^3 grid, in place on u
  * (device, N^3), with opts->max_step and opts->flags (MGFR_SUBTRACT_MEAN, MGFR_PROFILE).
- * variant: 0 = the kernel the solver uses for this N, 1 = one kernel per colour (in place),
- * 2 = the fused red-black sweep (N >= 64; out of place through context scratch).
+ * variant: 0 = the faster of the two for single sweeps of this N (the solver's own where it
+ * sweeps once at a time: from 128^3 up; smaller levels it relaxes two sweeps or a whole
+ * V-cycle at a time), 1 = one kernel per colour (in place), 2 = the fused red-black sweep
+ * (N >= 64; out of place through context scratch); all give the same results, bit for bit.
  * Does not synchronise unless MGFR_PROFILE is set. */
 int mgfr_smooth(mgfr_ctx* ctx, const double* rho, double* u, int N, const mgfr_params* params,
                 const mgfr_opts* opts, int nsweeps, int variant, void* stream);
@@ -211,8 +216,8 @@ int mgfr_smooth(mgfr_ctx* ctx, const double* rho, double* u, int N, const mgfr_p
  *   N_i(e) = C sum_nb [(M_nb + M_i)(ub_nb - ub_i) + (B_nb + B_i)(e_nb - e_i)]
  *          + A exp(-ub_i/(n+1)) expm1(-e_i/(n+1)),   b = exp(ub), M = b expm1(e), B = b + M.
  * nsweeps sweeps in place on e (device, N^3 float); ub and f (device, N^3 float) are read.
- * variant: 0 = the kernel the mixed solver uses on its finest level for this N, 1 = one kernel
- * per colour (in place), 2 = the fused red-black sweep (N >= 64, out of place through context
+ * variant: 0 = the faster of the two for this N (the mixed solver's finest-level kernel from
+ * 128^3 up), 1 = one kernel per colour (in place), 2 = the fused red-black sweep (N >= 64, out of place through context
  * scratch), opts->planes planes per workgroup (0: the mixed solver's automatic choice; else a
  * multiple of 4 that is <= N).  opts->max_step bounds each step; MGFR_PROFILE times every
  * launch (12 B per cell: read ub and f, read and write e).  Returns MGFR_EINVAL for other N,

@@ -187,8 +187,8 @@ hipError_t pass(const Grid& g, const typename P::T* ub, const typename P::T* in,
 }  // namespace
 
 // Levels that take the block passes: below 32 the V-cycle is one launch (tail.hip), from 128 up a
-// sweep's launches are no longer what it costs and the halos are (each pass relaxes 6 cells for one
-// of its own at 8^3).
+// sweep's launches are no longer what it costs and the halos are (with 8^3 blocks the first pass relaxes
+// 4.7 cells for each of its own and the second 2.9).
 bool block_level(int n) { return n == 32 || n == 64; }
 
 hipError_t block_pre(const Grid& g, const double* in, double* out, const double* src, double* uc, double* uhat,

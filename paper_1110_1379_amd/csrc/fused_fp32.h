@@ -14,7 +14,7 @@
 // cell's (B, M) are formed again from (ub, e) as the per-colour kernel forms them, so both
 // sweeps give the same bits.
 //
-// Bound by its arithmetic (VALU busy 72 % of the cycles, about 235 instructions per wavefront and
+// Bound by its arithmetic (vector units busy 67 % of the cycles, 223 instructions per wavefront and
 // plane), then by its barriers.  Measured on the domain grid in 16 x 64 tiles, us per sweep: 512^3 653
 // (3.3 TB/s at the 16 B per cell it cannot do without), 256^3 73.5, 128^3 18.4; with the loads of the next
 // planes behind their branch, which waited for them at every plane, a 64-bit address each, and the

@@ -280,7 +280,8 @@ __global__ void __launch_bounds__(kB) km_ngs_colour(Grid g, const M* __restrict_
 // Bound by its double-precision arithmetic, the ghosts' on top of the domain sweep's.  Measured at
 // 512^3 with 61% of the cells active: 1.26 ms per sweep; with the loads behind branches and a 64-bit
 // address each 1.31, with the column pairs laid over tile and halo (704 threads) and an exponential and
-// a branch per masked neighbour 2.19 ms.  Float mask at 256^3: 272 us, the two colour launches 443 us.
+// a branch per masked neighbour 2.19 ms.  Float mask at 256^3, half of the cells active: 231 us, the two
+// colour launches 358 us.
 constexpr int kMK = 64;  // tile width along k
 
 // A flag byte or a mask value: whether the cell is active, and whether its update needs w.
@@ -388,7 +389,7 @@ km_ngs_fused(Grid g, const M* __restrict__ flags, const double* __restrict__ w, 
     auto buf = [&](int p) { return (p - i0 + 3) % 3; };
     // the density and w of a cell of flag byte fl on plane p, where an update needs them, else the
     // tile's corner's: no load stands behind a branch (but for a float mask, whose registers
-    // would spill: 287 us instead of 272 at 256^3)
+    // would spill: 5% slower at 256^3)
     const unsigned corner = (unsigned)((j0 << lg) | k0);
     auto fetch = [&](int p, const Col& q, V fl, double& fv, double& wv) {
         if constexpr (FM) {

@@ -92,7 +92,7 @@ __global__ void __launch_bounds__(kB) kp_resid_norm(PGrid g, const double* __res
     }
 }
 
-// ---- one colour of a Gauss-Seidel sweep, in place (levels below 64) ----------------------
+// ---- one colour of a Gauss-Seidel sweep, in place (levels of 32^3; single sweeps below 256^3) ----
 __global__ void __launch_bounds__(kB) kp_ngs_colour(PGrid g, double* __restrict__ x, const double* __restrict__ b,
                                                     double bmean, int colour)
 {
@@ -110,7 +110,7 @@ __global__ void __launch_bounds__(kB) kp_ngs_colour(PGrid g, double* __restrict_
     x[q] = (sum - g.hh * (b[q] - bmean)) * (1.0 / 6.0);
 }
 
-// ---- fused red-black sweep (n >= 64), out of place ----------------------------------------
+// ---- fused red-black sweep (n >= 64; the solver's single sweeps from 256^3 up), out of place ----
 // Same scheme as the nonlinear fused sweep: a workgroup streams the planes of a TJ x 64
 // tile; per plane the tile plus a 2-cell in-plane halo is staged in LDS (three buffers, one
 // barrier per plane), the i-neighbours stay in registers; at step p the red cells of plane
@@ -253,11 +253,11 @@ __global__ void __launch_bounds__(NT) kp_fused(PGrid g, const double* __restrict
 // that nothing valid reads: a cell's validity shrinks by one ring per update, and the tile is
 // written after four.
 // Bound by latency: a step of 14 wavefronts is one barrier, four dependent updates and the wait for
-// the loads of two steps before (VALU busy 20 %, LDS conflicts 7 % of the cycles).  97 VGPRs let one
-// workgroup run on a compute unit; at 64 for a second one it spills (1.06 ms), 8 x 64 and 16 x 32
-// tiles at two or three a unit re-read more halo (1.07 ms), and 32 x 64 with two pairs per thread
-// spills (1.02 ms).  Measured at 512^3: 0.853 ms per pass, 3.8 TB/s of the 3.2 GB it cannot do
-// without; with a slot for every cell of tile and halo, half of them idle in each phase, and
+// the loads of two steps before (vector units busy 17 - 20%, LDS conflicts 12 - 14% of the cycles).
+// 97 VGPRs let one workgroup run on a compute unit; at 64 for a second one it spills (1.06 ms), 8 x
+// 64 and 16 x 32 tiles at two or three a unit re-read more halo (1.07 ms), and 32 x 64 with two pairs
+// per thread spills (1.02 ms).  Measured at 512^3: 0.853 ms per pass, 3.8 TB/s of the 3.2 GB it cannot
+// do without; with a slot for every cell of tile and halo, half of them idle in each phase, and
 // six planes of x in registers (157 VGPRs) 1.18 ms.  256^3: 0.112 against 0.154 ms.
 struct Col2 {
     double xr[2], vr;     // plane q of x in xr[(q - p0) & 1]; the last value of sweep B
