@@ -165,15 +165,19 @@ struct Op64 {
 };
 
 // S = A exp(-u/(n+1)): for n = 1 through 1 / sqrt(b), as dev::curvature, but from u itself where b
-// is denormal or zero (u < -708), whose root has lost what u still holds.
+// is denormal or zero (u < -708), whose root has lost what u still holds.  The wavefront branches,
+// not the lane: 40 boxes of 32^3 2.50 ms against 2.53, 300 of 16^3 1.445 against 1.451 (without the
+// test 1.440).
 __device__ __forceinline__ double curvature(const Op64& o, double u, double b)
 {
-    if (o.inv_np1 == 0.5 && !(b < 2.2250738585072014e-308)) {
+    if (o.inv_np1 == 0.5) {
         double y = __builtin_amdgcn_rsq(b);
         double e = fma(-b * y, y, 1.0);
         y = fma(0.5 * y, e, y);
         e = fma(-b * y, y, 1.0);
         y = fma(0.5 * y, e, y);
+        const bool small = b < 2.2250738585072014e-308;
+        if (__builtin_expect(__any(small), 0)) y = small ? dev::exp_(-0.5 * u) : y;
         return o.A * y;
     }
     return o.A * dev::exp_(-u * o.inv_np1);
